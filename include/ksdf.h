@@ -68,10 +68,8 @@ enum { KSDF_C_FP64 = 1, KSDF_C_FAILED = 2 };
  * ln f') (App. D scaling by the nearest sample d).  KSDF_KERNEL_MATERN32: k(r) =
  * (1 + c r) exp(-c r) with c = sqrt(3) / l, u = d - ln(f') / c; u < 0 clamps to 0.
  * The UDF gradient is w/|w| with w = sum a_i e_i (x* - x_i), e_i the scaled k_i (RBF)
- * or exp(-c (z_i - d)) (Matern 3/2).  Matern 3/2 models: FP32 queries run the plain
- * one-thread-per-query kernel in FP32 (the wave-cooperative kernels carry RBF-specific
- * error bounds), ksdf_fit_query runs fit and query as separate launches, and the
- * backward runs one thread per query in FP64 for either precision. */
+ * or exp(-c (z_i - d)) (Matern 3/2).  ksdf_fit_query runs a Matern 3/2 model's fit and
+ * query as separate launches. */
 enum { KSDF_KERNEL_RBF = 0, KSDF_KERNEL_MATERN32 = 1 };
 
 /* Hyperparameters (host struct).  ell: length-scale l (m), > 0.  noise_var:
@@ -79,7 +77,7 @@ enum { KSDF_KERNEL_RBF = 0, KSDF_KERNEL_MATERN32 = 1 };
  * given).  alpha: softmin temperature; <= 0 ties it to the length-scale as
  * alpha = 1/(2 l^2), which the backward then differentiates through.  k_fuse:
  * number of nearest cells fused by the min, 1..KSDF_MAX_K.  precision: KSDF_FP64
- * (every step in double, one block per cell and one thread per query) or KSDF_FP32
+ * (every step in double) or KSDF_FP32
  * (FP32 bulk; cells whose condition estimate exceeds cond_fp64_threshold, or whose
  * FP32 pivot fails, are factored in FP64). */
 typedef struct ksdf_hyper {
@@ -174,11 +172,14 @@ void ksdf_model_destroy(ksdf_model* model);
  * fit_min_bucket: FP32 cells with m <= this run in the fit kernel sized for it
  *   (16, 32 or 64): larger values merge small cells into fewer launches.
  * query_split: the FP32 query runs as two kernels with the queries regrouped by
- *   argmin cell between them (1), or as one kernel (0).  Outputs are identical.
- * query_lanes, backward_lanes: each lane reads its own cells (1) instead of the
- *   wave sharing a cell through scalar loads (0); for sparse query sets, whose waves
- *   span many cells.  query_lanes applies to the two-kernel query.  Outputs are
+ *   argmin cell between them, or, up to 196,608 points, as one kernel with eight lanes
+ *   per query (1), or as one kernel of wave-shared cells (0).  Outputs are identical.
+ * query_lanes: each lane of the two-kernel query reads its own cells (1), or the wave
+ *   shares a cell through scalar loads where there are at least 96 queries per cell (0;
+ *   sparser sets, whose waves span many cells, take the per-lane form too).  Outputs are
  *   identical.
+ * backward_lanes: accepted (0 or 1) and without effect: the backward takes eight lanes
+ *   per point up to 196,608 points (FP64: 65,536) and with a var_f cotangent, else one.
  * query_pairs: the first kernel of the two-kernel query evaluates each (query,
  *   candidate cell) pair once, with the pairs grouped by cell (1), instead of each
  *   wave walking the union of its lanes' candidates (0).  Every candidate is then

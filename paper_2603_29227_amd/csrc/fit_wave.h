@@ -24,19 +24,10 @@
 #include <type_traits>
 
 #include "fit_dev.h"
+#include "wave_ops.h"
 
 namespace ksdf {
 namespace {
-
-// f(integral_constant<int, I>) for I = B .. E-1, each index a compile-time constant
-// (so that register arrays indexed by it are never placed in memory)
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
 
 // The per-lane slots are sized for the whole wave: every lane writes its own slot
 // (lanes past m carry zeros), whatever MB.  The packed factor has room for the
@@ -58,13 +49,6 @@ struct WaveFitLds {
   alignas(16) float col[64];               // the column of the factorisation step
   alignas(16) float L[wave_lds_l_floats<MB>()];   // packed factor rows, reciprocal diagonal
 };
-
-// LDS traffic between the lanes of one wave: order the writes before the reads.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // whether packed index e (row-major lower triangle) is a diagonal entry
 __device__ __forceinline__ bool packed_diag(int e) {

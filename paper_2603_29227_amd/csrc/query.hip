@@ -12,13 +12,12 @@
 // the transform by u = d - ln(f')/c (App. D scaling gamma = exp(c d)) and e_i in w
 // by exp(-c (z_i - d)), since dk/dr = -c^2 r exp(-c r); u < 0 clamps to 0.
 //
-// This file holds the plain path: one thread per query, every read straight from
-// the per-cell store (no staging, no bucketing), in the model's precision.  It serves
-// FP64 models and FP32 Matern models; FP32 RBF models use the wave-cooperative
-// kernels of query_fast.hip.
+// This file holds the plain path of FP64 models: every candidate evaluated, every read
+// straight from the per-cell store (no bucketing).
 #include <cmath>
 
 #include "ksdf_internal.h"
+#include "group_dev.h"
 
 namespace ksdf {
 
@@ -59,8 +58,6 @@ struct QueryArgs {
 
 namespace {
 
-constexpr int QT = 256;
-
 // Candidate distances: an integer decision, so both precisions use a fixed
 // rounding sequence (float: sub, mul, two fma; double: sub, mul, add in order).
 __device__ __forceinline__ float cand_d2(float qx, float qy, float qz, const float* c) {
@@ -79,41 +76,6 @@ template <> __device__ __forceinline__ const float* centre_of(const QueryArgs<fl
 }
 template <> __device__ __forceinline__ const double* centre_of(const QueryArgs<double>& A, int c) {
   return A.centre64 + 3L * c;
-}
-
-template <class T>
-__device__ int select_candidates(const QueryArgs<T>& A, T qx, T qy, T qz, int* cid, bool* outside) {
-  T cd[KSDF_MAX_K];
-  int n = 0;
-  const long key[3] = {(long)floor(((double)qx - A.origin[0]) / A.h) - A.lo[0],
-                       (long)floor(((double)qy - A.origin[1]) / A.h) - A.lo[1],
-                       (long)floor(((double)qz - A.origin[2]) / A.h) - A.lo[2]};
-  const bool inside = A.n_boxes > 0 && key[0] >= 0 && key[0] < A.dims[0] && key[1] >= 0 &&
-                      key[1] < A.dims[1] && key[2] >= 0 && key[2] < A.dims[2];
-  *outside = !inside;
-  int beg = 0, end = A.n_cells;
-  const int* list = nullptr;
-  if (inside) {
-    const long b = (key[0] * A.dims[1] + key[1]) * A.dims[2] + key[2];
-    beg = A.box_off[b];
-    end = A.box_off[b + 1];
-    list = A.box_list;
-  }
-  for (int t = beg; t < end; ++t) {
-    const int c = list ? list[t] : t;
-    const T d2 = cand_d2(qx, qy, qz, centre_of(A, c));
-    if (n < A.k || d2 < cd[n - 1]) {   // ids ascend, so an equal distance never displaces
-      int j = n < A.k ? n++ : n - 1;
-      while (j > 0 && cd[j - 1] > d2) {
-        cd[j] = cd[j - 1];
-        cid[j] = cid[j - 1];
-        --j;
-      }
-      cd[j] = d2;
-      cid[j] = c;
-    }
-  }
-  return n;
 }
 
 template <class T>
@@ -158,126 +120,231 @@ __device__ T cell_udf(const QueryArgs<T>& A, int c, T qx, T qy, T qz, bool* clam
   return sqrt(u2);
 }
 
+// Eight lanes per query (group_dev.h): each lane scans every eighth entry of the candidate
+// list and evaluates one or two of the candidates, and the argmin cell's sums and its
+// triangular solve are shared as in query_group.hip.  One thread per query had to keep the
+// kernel vector of m doubles in memory and left most of the chip idle below some hundred
+// thousand queries (room of 64-sample cells: 4,000 points 1.21 ms, 64,000 1.48 and 1e6
+// 22.3; eight lanes take 0.074, 0.63 and 9.1; a 128^3 grid 11.7 and 9.7).
 template <class T>
-__global__ void __launch_bounds__(QT) query_plain_kernel(QueryArgs<T> A) {
-  const long q = (long)blockIdx.x * QT + threadIdx.x;
-  if (q >= A.Q) return;
-  const T qx = A.pts[3 * q], qy = A.pts[3 * q + 1], qz = A.pts[3 * q + 2];
-  const T sgn = A.sign ? (T)A.sign[q] : T(1);
-  int cid[KSDF_MAX_K];
-  bool outside = false;
-  const int n = select_candidates(A, qx, qy, qz, cid, &outside);
-  T best = (T)INFINITY;
-  int bc = -1;
-  bool bclamp = false;
-  for (int t = 0; t < n; ++t) {
-    bool cl;
-    const T u = cell_udf(A, cid[t], qx, qy, qz, &cl);
-    if (u < best || (u == best && u < (T)INFINITY && cid[t] < bc)) {
-      best = u;
-      bc = cid[t];
-      bclamp = cl;
+struct QueryGroupLds {
+  alignas(16) T t[8 * GT_STRIDE];
+  alignas(16) T k[GQ * GK_STRIDE];
+};
+
+template <class T, int KM>
+__global__ void __launch_bounds__(64) query_plain_kernel(QueryArgs<T> A) {
+  __shared__ QueryGroupLds<T> S;
+  constexpr int NC = KM / GL;
+  const int lane = threadIdx.x & 63, g = lane & (GL - 1), base = lane - g;
+  const long q = (long)blockIdx.x * GQ + lane / GL;
+  const bool active = q < A.Q;
+  const long qq = active ? q : 0;
+  const T qx = A.pts[3 * qq], qy = A.pts[3 * qq + 1], qz = A.pts[3 * qq + 2];
+  // the K nearest centres: sorted private lists, then group-wide minima of (distance, id)
+  T cd[KM];
+  int ci[KM];
+#pragma unroll
+  for (int r = 0; r < KM; ++r) {
+    cd[r] = (T)INFINITY;
+    ci[r] = 0x7fffffff;
+  }
+  const long key[3] = {(long)floor(((double)qx - A.origin[0]) / A.h) - A.lo[0],
+                       (long)floor(((double)qy - A.origin[1]) / A.h) - A.lo[1],
+                       (long)floor(((double)qz - A.origin[2]) / A.h) - A.lo[2]};
+  const bool inside = A.n_boxes > 0 && key[0] >= 0 && key[0] < A.dims[0] && key[1] >= 0 &&
+                      key[1] < A.dims[1] && key[2] >= 0 && key[2] < A.dims[2];
+  int beg = 0, end = active ? A.n_cells : 0;
+  if (active && inside) {
+    const long bx = (key[0] * A.dims[1] + key[1]) * A.dims[2] + key[2];
+    beg = A.box_off[bx];
+    end = A.box_off[bx + 1];
+  }
+  for (int t = beg + g; t < end; t += GL) {
+    int xi = inside ? A.box_list[t] : t;
+    T x = cand_d2(qx, qy, qz, centre_of(A, xi));
+    if (x < cd[KM - 1] || (x == cd[KM - 1] && xi < ci[KM - 1])) {
+#pragma unroll
+      for (int r = 0; r < KM; ++r) {
+        if (x < cd[r] || (x == cd[r] && xi < ci[r])) {
+          const T tx = cd[r];
+          const int ti = ci[r];
+          cd[r] = x;
+          ci[r] = xi;
+          x = tx;
+          xi = ti;
+        }
+      }
     }
   }
+  const int n = min(A.k, end - beg);
+  int mine[NC];   // the lane's candidates: ranks g and g + 8
+#pragma unroll
+  for (int s = 0; s < NC; ++s) mine[s] = 0x7fffffff;
+#pragma unroll
+  for (int r = 0; r < KM; ++r) {
+    T d = cd[0];
+    int id = ci[0];
+    group_min(d, id);
+    if (r % GL == g && r < n) mine[r / GL] = id;
+    if (ci[0] == id) {   // ids are unique: one lane drops its head
+#pragma unroll
+      for (int j = 0; j + 1 < KM; ++j) {
+        cd[j] = cd[j + 1];
+        ci[j] = ci[j + 1];
+      }
+      cd[KM - 1] = (T)INFINITY;
+      ci[KM - 1] = 0x7fffffff;
+    }
+  }
+  // min-fusion, ties to the lower id
+  T best = (T)INFINITY;
+  int bc = 0x7fffffff;
+  bool cl = false;
+#pragma unroll
+  for (int s = 0; s < NC; ++s) {
+    if (mine[s] != 0x7fffffff) {
+      bool c1;
+      const T u = cell_udf(A, mine[s], qx, qy, qz, &c1);
+      if (u < best || (u == best && u < (T)INFINITY && mine[s] < bc)) {
+        best = u;
+        bc = mine[s];
+        cl = c1;
+      }
+    }
+  }
+  const int own = bc;
+  group_min(best, bc);
+  const bool bclamp = ((__ballot(cl && own == bc) >> base) & 0xffull) != 0ull;
+  const T sgn = active && A.sign ? (T)A.sign[qq] : T(1);
+  const bool outside = !inside;
   uint8_t st = outside ? KSDF_Q_OUTSIDE_INDEX : 0;
-  if (bc < 0) {
-    A.mean[q] = (T)INFINITY;
-    for (int d = 0; d < 3; ++d) A.grad[3 * q + d] = T(0);
-    A.var[q] = (T)INFINITY;
-    if (A.var_f) A.var_f[q] = T(1);
-    if (A.grad_var)
-      for (int d = 0; d < 3; ++d) A.grad_var[3 * q + d] = (T)INFINITY;
-    if (A.argmin) A.argmin[q] = -1;
-    if (A.qst) A.qst[q] = st | KSDF_Q_NO_VALID_CELL;
+  if (bc == 0x7fffffff) {   // uniform over each group
+    if (active && g == 0) {
+      A.mean[q] = (T)INFINITY;
+      for (int d = 0; d < 3; ++d) A.grad[3 * q + d] = T(0);
+      A.var[q] = (T)INFINITY;
+      if (A.var_f) A.var_f[q] = T(1);
+      if (A.grad_var)
+        for (int d = 0; d < 3; ++d) A.grad_var[3 * q + d] = (T)INFINITY;
+      if (A.argmin) A.argmin[q] = -1;
+      if (A.qst) A.qst[q] = st | KSDF_Q_NO_VALID_CELL;
+    }
     return;
   }
   if (bclamp) st |= KSDF_Q_CLAMPED;
-  // argmin cell: gradient, GP variance, softmin variance
   const int b = A.offsets[bc], m = A.offsets[bc + 1] - b;
   const double* cc = A.centre64 + 3L * bc;
   const T lx = qx - (T)cc[0], ly = qy - (T)cc[1], lz = qz - (T)cc[2];
   const T* p = A.ps + 4L * b;
   const T* sv = A.sv + b;
-  const T* L = A.L + A.loff[bc];
+  T* row = S.t + lane;
+  T* k = S.k + lane / GL * GK_STRIDE;
+  auto put = [&](int r, T v) { row[r * GT_STRIDE] = v; };
+  auto offset = [&](int i, T e[3]) {
+    e[0] = lx - p[4 * i];
+    e[1] = ly - p[4 * i + 1];
+    e[2] = lz - p[4 * i + 2];
+    return e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
+  };
   T d2 = (T)INFINITY;
-  for (int i = 0; i < m; ++i) {
-    const T dx = lx - p[4 * i], dy = ly - p[4 * i + 1], dz = lz - p[4 * i + 2];
-    d2 = min(d2, dx * dx + dy * dy + dz * dz);
+  for (int i = g; i < m; i += GL) {
+    T e[3];
+    d2 = min(d2, offset(i, e));
   }
-  T w0 = 0, w1 = 0, w2 = 0;
-  T v[KSDF_MAX_M];
-  T vv = T(0);
-  const T g = exp(-d2 * A.inv2l2);   // 1/gamma: k_i = e_i / gamma
+  d2 = min(d2, dpp<DPP_XOR1>(d2));
+  d2 = min(d2, dpp<DPP_XOR2>(d2));
+  d2 = min(d2, dpp<DPP_MIRROR8>(d2));
+  const T gs = exp(-d2 * A.inv2l2);   // 1/gamma: k_i = e_i / gamma
   const T zmin = sqrt(d2);
-  T S = 0, H = 0;
   const bool matern = A.kernel == KSDF_KERNEL_MATERN32;
-  for (int i = 0; i < m; ++i) {
-    const T dx = lx - p[4 * i], dy = ly - p[4 * i + 1], dz = lz - p[4 * i + 2];
-    const T z2 = dx * dx + dy * dy + dz * dz;
+  // w (3), S, H and the kernel vector
+  T acc = T(0);
+  put(7, T(1));
+  for (int i0 = 0; i0 < m; i0 += GL) {
+    const int i = i0 + g;
+    const bool in = i < m;
+    const int j = in ? i : 0;
+    T d[3];
+    const T z2 = offset(j, d);
     const T z = sqrt(z2);
-    // e_i of the gradient (scaled) and the unscaled kernel value k_i
     T e, t;
     if (matern) {
       e = exp(-A.mc * (z - zmin));
       t = (T(1) + A.mc * z) * exp(-A.mc * z);
     } else {
       e = exp(-(z2 - d2) * A.inv2l2);
-      t = e * g;
+      t = e * gs;
     }
-    const T ae = p[4 * i + 3] * e;
-    w0 += ae * dx;
-    w1 += ae * dy;
-    w2 += ae * dz;
-    // forward substitution L v = k
-    const T* row = L + (long)i * (i + 1) / 2;
-    for (int j = 0; j < i; ++j) t -= row[j] * v[j];
-    v[i] = t * row[i];
-    vv += v[i] * v[i];
-    const T s = exp(-A.alpha * (z - zmin));
-    S += s;
-    H += s * z;
+    put(0, in ? p[4 * j + 3] * e : T(0));
+    put(1, d[0]);
+    put(2, d[1]);
+    put(3, d[2]);
+    put(4, in ? exp(-A.alpha * (z - zmin)) : T(0));
+    put(5, z);
+    if (in) k[i] = t;
+    wave_lds_sync();
+    group_fma(S.t, lane_entry(lanes8(0, 0, 0, 7, 4, 7, 7, 7)),
+              lane_entry(lanes8(1, 2, 3, 4, 5, 7, 7, 7)), acc);
+    wave_lds_sync();
   }
-  const T h = H / S;
-  T var = 0;
-  // sums for the gradient variance: Vs = sum s_i v_i, g = sum l_i v_i (l_i = c_i)
-  T Vs[3] = {0, 0, 0}, gs[3] = {0, 0, 0};
-  for (int i = 0; i < m; ++i) {
-    const T dx = lx - p[4 * i], dy = ly - p[4 * i + 1], dz = lz - p[4 * i + 2];
-    const T z = sqrt(dx * dx + dy * dy + dz * dz);
-    const T s = exp(-A.alpha * (z - zmin)) / S;
-    const T ci = s * (A.alpha * h - A.alpha * z + T(1));
-    var += ci * ci * sv[i];
-    if (z > T(0)) {
-      const T vd[3] = {dx / z, dy / z, dz / z};
-      for (int d = 0; d < 3; ++d) {
-        Vs[d] += s * vd[d];
-        gs[d] += ci * vd[d];
-      }
-    }
+  const T w0 = group_lane<0>(acc), w1 = group_lane<1>(acc), w2 = group_lane<2>(acc);
+  const T Ss = group_lane<3>(acc);
+  const T h = group_lane<4>(acc) / Ss;
+  const T vv = A.var_f ? group_forward_subst(k, A.L + A.loff[bc], m) : T(0);
+  // the softmin variance, and the sums Vs = sum s_i v_i, g = sum c_i v_i of the gradient's
+  acc = T(0);
+  for (int i0 = 0; i0 < m; i0 += GL) {
+    const int i = i0 + g;
+    const bool in = i < m;
+    const int j = in ? i : 0;
+    T d[3];
+    const T z = sqrt(offset(j, d));
+    const T s = in ? exp(-A.alpha * (z - zmin)) / Ss : T(0);
+    const T c = s * (A.alpha * h - A.alpha * z + T(1));
+    const T rz = z > T(0) ? T(1) : T(0);
+    put(0, c * c);
+    put(1, sv[j]);
+    put(2, rz > T(0) ? d[0] / z : T(0));
+    put(3, rz > T(0) ? d[1] / z : T(0));
+    put(4, rz > T(0) ? d[2] / z : T(0));
+    put(5, s);
+    put(6, c);
+    wave_lds_sync();
+    group_fma(S.t, lane_entry(lanes8(0, 5, 5, 5, 6, 6, 6, 7)),
+              lane_entry(lanes8(1, 2, 3, 4, 2, 3, 4, 7)), acc);
+    wave_lds_sync();
   }
+  const T var = group_lane<0>(acc);
   if (A.grad_var) {
-    // V[grad_k u] = sum_i sigma_i^2 |row k of J_i|^2 with J_i the derivative of the
-    // softmin gradient g with respect to sample i (App. C):
-    //   J_i = alpha w_i v_i^T + (l_i / z_i)(v_i v_i^T - I),
-    //   w_i = l_i (v_i - Vs) + s_i (v_i - g).
-    // As |v_i| = 1 the cross term of row k vanishes and
-    //   |row k|^2 = alpha^2 w_ik^2 + (l_i / z_i)^2 (1 - v_ik^2).
-    T gv[3] = {0, 0, 0};
-    for (int i = 0; i < m; ++i) {
-      const T dx = lx - p[4 * i], dy = ly - p[4 * i + 1], dz = lz - p[4 * i + 2];
-      const T z = sqrt(dx * dx + dy * dy + dz * dz);
-      if (!(z > T(0))) continue;   // a sample at the query has no direction
-      const T s = exp(-A.alpha * (z - zmin)) / S;
+    const T Vs[3] = {group_lane<1>(acc), group_lane<2>(acc), group_lane<3>(acc)};
+    const T gg[3] = {group_lane<4>(acc), group_lane<5>(acc), group_lane<6>(acc)};
+    acc = T(0);
+    for (int i0 = 0; i0 < m; i0 += GL) {
+      const int i = i0 + g;
+      const bool in = i < m;
+      const int j = in ? i : 0;
+      T dd[3];
+      const T z = sqrt(offset(j, dd));
+      const bool ok = in && z > T(0);   // a sample at the query has no direction
+      const T s = exp(-A.alpha * (z - zmin)) / Ss;
       const T li = s * (A.alpha * h - A.alpha * z + T(1));
-      const T vd[3] = {dx / z, dy / z, dz / z};
       const T lz2 = (li / z) * (li / z);
+      put(0, ok ? sv[j] : T(0));
       for (int d = 0; d < 3; ++d) {
-        const T w = li * (vd[d] - Vs[d]) + s * (vd[d] - gs[d]);
-        gv[d] += sv[i] * (A.alpha * A.alpha * w * w + lz2 * (T(1) - vd[d] * vd[d]));
+        const T vd = dd[d] / z;
+        const T w = li * (vd - Vs[d]) + s * (vd - gg[d]);
+        put(1 + d, ok ? A.alpha * A.alpha * w * w + lz2 * (T(1) - vd * vd) : T(0));
       }
+      wave_lds_sync();
+      group_fma(S.t, 0, lane_entry(lanes8(1, 2, 3, 1, 1, 1, 1, 1)), acc);
+      wave_lds_sync();
     }
-    for (int d = 0; d < 3; ++d) A.grad_var[3 * q + d] = gv[d];
+    const T gv[3] = {group_lane<0>(acc), group_lane<1>(acc), group_lane<2>(acc)};
+    if (g == 0)
+      for (int d = 0; d < 3; ++d) A.grad_var[3 * q + d] = gv[d];
   }
+  if (g != 0) return;
   const T wn = sqrt(w0 * w0 + w1 * w1 + w2 * w2);
   T gx = 0, gy = 0, gz = 0;
   if (wn > T(0)) {
@@ -345,14 +412,15 @@ int launch_query(const ksdf_model* m, const void* points, long Q, const int8_t* 
                  void* grad, void* var, void* var_f, void* grad_var, int* argmin, uint8_t* q_status, void* ws,
                  size_t ws_bytes, hipStream_t s, bool prebucketed) {
   if (Q == 0) return KSDF_OK;
-  const unsigned grid = (unsigned)((Q + QT - 1) / QT);
+  const unsigned grid = (unsigned)((Q + GQ - 1) / GQ);
   if (m->precision == KSDF_FP64) {
     QueryArgs<double> A = make_args<double>(m, points, Q, sign, mean, grad, var, var_f, grad_var, argmin, q_status);
     A.ps = m->ps64;
     A.sv = m->sv64;
     A.L = m->L64;
     timer_mark(m, KSDF_TIMER_QUERY, 0, s);
-    hipLaunchKernelGGL(query_plain_kernel<double>, dim3(grid), dim3(QT), 0, s, A);
+    if (m->k_fuse <= 8) hipLaunchKernelGGL((query_plain_kernel<double, 8>), dim3(grid), dim3(64), 0, s, A);
+    else hipLaunchKernelGGL((query_plain_kernel<double, 16>), dim3(grid), dim3(64), 0, s, A);
     timer_mark(m, KSDF_TIMER_QUERY, 1, s);
   } else {
     return launch_query_fast(m, points, Q, sign, mean, grad, var, var_f, grad_var, argmin, q_status, ws,

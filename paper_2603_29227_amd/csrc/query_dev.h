@@ -110,6 +110,12 @@ void launch_query_split_256_wave(const ksdf_model* m, const FastArgs& A, P1Rec* 
                                int* count, int* cursor, int* tsum, void* pws, hipStream_t s);
 void launch_query_split_256_lane(const ksdf_model* m, const FastArgs& A, P1Rec* rec, P1Rec* rec2,
                                int* count, int* cursor, int* tsum, void* pws, hipStream_t s);
+// one-kernel query launch (query_fast.hip)
+void launch_query_one(const ksdf_model* m, const FastArgs& A, hipStream_t s);
+// counting sort of the queries by (index box, sub-box) in a query workspace; sets A.perm
+int launch_bucketing(const ksdf_model* m, FastArgs& A, void* ws, hipStream_t s);
+// eight lanes per query (query_group.hip); A.perm null: the queries in the caller's order
+void launch_query_group(const ksdf_model* m, const FastArgs& A, hipStream_t s);
 // pair form of pass 1 (query_pairs.hip): usable for Q queries, its workspace, launch
 bool query_pairs_usable(const ksdf_model* m, long Q);
 size_t query_pairs_workspace_bytes(const ksdf_model* m, long Q);
@@ -553,6 +559,46 @@ __device__ __forceinline__ void cell_u2_wave(const FastArgs& A, int b, int m, fl
   }
 }
 
+// The per-lane (vector-load) form of cell_u2_wave, for sparse queries: the same
+// operations in the same order.
+__device__ __forceinline__ void cell_u2_lane(const FastArgs& A, int b, int m, float lx, float ly,
+                                             float lz, float& d2ref, float& u2, float& del) {
+  const float c2 = A.c2;
+  float f = 0.f, R = 0.f, RZ = 0.f;
+  u2 = INFINITY;
+  del = 0.f;
+  for (int pass = 0; pass < 2; ++pass) {
+    const float c2d = c2 * d2ref;
+    float emax = 0.f;
+    f = 0.f;
+    R = 0.f;
+    RZ = 0.f;
+    for (int i = 0; i < m; ++i) {
+      const float4 P = A.ps[b + i];
+      const float dx = lx - P.x, dy = ly - P.y, dz = lz - P.z;
+      const float z2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+      const float e = __builtin_amdgcn_exp2f(fmaf(z2, -c2, c2d));
+      const float ae = fabsf(P.w) * e;
+      f = fmaf(P.w, e, f);
+      R += ae;
+      RZ = fmaf(ae, z2, RZ);
+      emax = fmaxf(emax, e);
+    }
+    if (emax >= 0x1p-24f) break;
+    float d2 = INFINITY;
+    for (int i = 0; i < m; ++i) {
+      const float4 p = A.ps[b + i];
+      const float dx = lx - p.x, dy = ly - p.y, dz = lz - p.z;
+      d2 = fminf(d2, fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+    }
+    d2ref = d2;
+  }
+  if (f > 0.f) {
+    u2 = d2ref - A.two_l2 * LN2 * __log2f(f);
+    del = A.two_l2 * EPS32 * (6.f * R + 3.5f * c2 * RZ) / f;
+  }
+}
+
 // Matern 3/2 pass-1 sums over one chunk: f = sum a g, R = sum |a| g, RZ = sum |a| g z
 // with g_i = (1 + c z_i) 2^(c log2(e) (dref - z_i)) and emax the largest exponential
 // factor; dref <= every z_i (the sample box's lower bound), so no factor exceeds 1.
@@ -679,8 +725,9 @@ __device__ __forceinline__ float cell_lower_bound(const FastArgs& A, float d2box
 // While a condition fails, the cell with the larger error of the failing pair is
 // re-evaluated (its error then counts as zero) and the conditions are checked again,
 // so near-tied cells of small error are not redone.  Returns the argmin cell (-1:
-// none valid); best = its u^2.
-template <int KM>
+// none valid); best = its u^2.  GROUP: that many consecutive lanes hold one query, all
+// with the same values.
+template <int KM, int GROUP = 1>
 __device__ __forceinline__ int resolve_min(const FastArgs& A, bool active, float qx, float qy,
                                            float qz, const int (&cid)[KM], int n, float (&cu2)[KM],
                                            float (&cdl)[KM], float& best) {
@@ -740,7 +787,7 @@ __device__ __forceinline__ int resolve_min(const FastArgs& A, bool active, float
     const float sz = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, qz), src));
     const float u2 = A.matern ? cell_u_matern_ff_wave(A, c, sx, sy, sz)
                               : cell_u2_ff_wave(A, c, sx, sy, sz);
-    if ((int)(threadIdx.x & 63) == src) {
+    if ((int)(threadIdx.x & 63) / GROUP == src / GROUP) {
 #pragma unroll
       for (int r = 0; r < KM; ++r)
         if (r == rs) {
@@ -849,37 +896,7 @@ __device__ __forceinline__ Pass1 query_pass1(const FastArgs& A, long sq) {
         if constexpr (MAT) {
           if (!(lb > best + 2.f * best_del + 1e-6f)) cell_u_matern_lane(A, b, m, lx, ly, lz, d2ref, u2, del);
         } else if (!(lb > best + 2.f * best_del + 1e-6f)) {
-          float f = 0.f, R = 0.f, RZ = 0.f;
-          for (int pass = 0; pass < 2; ++pass) {
-            const float c2d = c2 * d2ref;
-            float emax = 0.f;
-            f = 0.f;
-            R = 0.f;
-            RZ = 0.f;
-            for (int i = 0; i < m; ++i) {
-              const float4 P = A.ps[b + i];
-              const float dx = lx - P.x, dy = ly - P.y, dz = lz - P.z;
-              const float z2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-              const float e = __builtin_amdgcn_exp2f(fmaf(z2, -c2, c2d));
-              const float ae = fabsf(P.w) * e;
-              f = fmaf(P.w, e, f);
-              R += ae;
-              RZ = fmaf(ae, z2, RZ);
-              emax = fmaxf(emax, e);
-            }
-            if (emax >= 0x1p-24f) break;
-            float d2 = INFINITY;
-            for (int i = 0; i < m; ++i) {
-              const float4 p = A.ps[b + i];
-              const float dx = lx - p.x, dy = ly - p.y, dz = lz - p.z;
-              d2 = fminf(d2, fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
-            }
-            d2ref = d2;
-          }
-          if (f > 0.f) {
-            u2 = d2ref - A.two_l2 * LN2 * __log2f(f);
-            del = A.two_l2 * EPS32 * (6.f * R + 3.5f * c2 * RZ) / f;
-          }
+          cell_u2_lane(A, b, m, lx, ly, lz, d2ref, u2, del);
         }
         cu2[r] = u2;
         cdl[r] = del;
@@ -999,6 +1016,59 @@ __device__ __forceinline__ float mfma_vv(const float* __restrict__ Li, const flo
     else res1 = s;
   }
   return hi ? res1 : res0;
+}
+
+// Every output of query qi from its argmin cell's sums.
+template <bool MAT>
+__device__ __forceinline__ void write_outputs(const FastArgs& A, bool active, bool outside, int flags,
+                                              long qi, int bc, float best, float w0, float w1,
+                                              float w2, float vv, float var, float gv0, float gv1,
+                                              float gv2) {
+  if (!active) return;
+  const float sgn = A.sign ? (float)A.sign[qi] : 1.f;
+  uint8_t st = outside ? KSDF_Q_OUTSIDE_INDEX : 0;
+  if (flags & PASS1_FIT_TIMEOUT) st |= KSDF_Q_FIT_TIMEOUT;
+  if (bc < 0) {
+    if (A.grad_var) {
+      A.grad_var[3 * qi] = INFINITY;
+      A.grad_var[3 * qi + 1] = INFINITY;
+      A.grad_var[3 * qi + 2] = INFINITY;
+    }
+    A.mean[qi] = INFINITY;
+    A.grad[3 * qi] = 0.f;
+    A.grad[3 * qi + 1] = 0.f;
+    A.grad[3 * qi + 2] = 0.f;
+    A.var[qi] = INFINITY;
+    if (A.var_f) A.var_f[qi] = 1.f;
+    if (A.argmin) A.argmin[qi] = -1;
+    if (A.qst) A.qst[qi] = st | KSDF_Q_NO_VALID_CELL;
+    return;
+  }
+  float u = 0.f;
+  if (best < 0.f) st |= KSDF_Q_CLAMPED;
+  else u = MAT ? best : sqrtf(best);   // Matern records carry u, RBF u^2
+  const float wn = sqrtf(w0 * w0 + w1 * w1 + w2 * w2);
+  float gx = 0.f, gy = 0.f, gz = 0.f;
+  if (wn > 0.f) {
+    gx = w0 / wn;
+    gy = w1 / wn;
+    gz = w2 / wn;
+  } else {
+    st |= KSDF_Q_GRAD_ZERO;
+  }
+  A.mean[qi] = sgn * u;
+  A.grad[3 * qi] = sgn * gx;
+  A.grad[3 * qi + 1] = sgn * gy;
+  A.grad[3 * qi + 2] = sgn * gz;
+  A.var[qi] = var;
+  if (A.var_f) A.var_f[qi] = fmaxf(1.f - vv, 0.f);
+  if (A.grad_var) {
+    A.grad_var[3 * qi] = gv0;
+    A.grad_var[3 * qi + 1] = gv1;
+    A.grad_var[3 * qi + 2] = gv2;
+  }
+  if (A.argmin) A.argmin[qi] = bc;
+  if (A.qst) A.qst[qi] = st;
 }
 
 // The argmin cell's outputs (gradient, GP variance, softmin variance) and every
@@ -1131,51 +1201,7 @@ __device__ __forceinline__ void query_finish_t(const FastArgs& A, const Pass1& p
     }
   }
 
-  if (!active) return;
-  const float sgn = A.sign ? (float)A.sign[qi] : 1.f;
-  uint8_t st = outside ? KSDF_Q_OUTSIDE_INDEX : 0;
-  if (p1.flags & PASS1_FIT_TIMEOUT) st |= KSDF_Q_FIT_TIMEOUT;
-  if (bc < 0) {
-    if (A.grad_var) {
-      A.grad_var[3 * qi] = INFINITY;
-      A.grad_var[3 * qi + 1] = INFINITY;
-      A.grad_var[3 * qi + 2] = INFINITY;
-    }
-    A.mean[qi] = INFINITY;
-    A.grad[3 * qi] = 0.f;
-    A.grad[3 * qi + 1] = 0.f;
-    A.grad[3 * qi + 2] = 0.f;
-    A.var[qi] = INFINITY;
-    if (A.var_f) A.var_f[qi] = 1.f;
-    if (A.argmin) A.argmin[qi] = -1;
-    if (A.qst) A.qst[qi] = st | KSDF_Q_NO_VALID_CELL;
-    return;
-  }
-  float u = 0.f;
-  if (best < 0.f) st |= KSDF_Q_CLAMPED;
-  else u = MAT ? best : sqrtf(best);   // Matern records carry u, RBF u^2
-  const float wn = sqrtf(w0 * w0 + w1 * w1 + w2 * w2);
-  float gx = 0.f, gy = 0.f, gz = 0.f;
-  if (wn > 0.f) {
-    gx = w0 / wn;
-    gy = w1 / wn;
-    gz = w2 / wn;
-  } else {
-    st |= KSDF_Q_GRAD_ZERO;
-  }
-  A.mean[qi] = sgn * u;
-  A.grad[3 * qi] = sgn * gx;
-  A.grad[3 * qi + 1] = sgn * gy;
-  A.grad[3 * qi + 2] = sgn * gz;
-  A.var[qi] = var;
-  if (A.var_f) A.var_f[qi] = fmaxf(1.f - vv, 0.f);
-  if (A.grad_var) {
-    A.grad_var[3 * qi] = gv0;
-    A.grad_var[3 * qi + 1] = gv1;
-    A.grad_var[3 * qi + 2] = gv2;
-  }
-  if (A.argmin) A.argmin[qi] = bc;
-  if (A.qst) A.qst[qi] = st;
+  write_outputs<MAT>(A, active, outside, p1.flags, qi, bc, best, w0, w1, w2, vv, var, gv0, gv1, gv2);
 }
 
 // The whole query for one wave of sorted queries (MAT: a Matern model).
@@ -1185,26 +1211,11 @@ __device__ __forceinline__ void query_tile(const FastArgs& A, long sq) {
 }
 
 // ---------------------------------------------------------------------------
-// bucketing: histogram, scan, scatter
+// counting sorts: fill, scan (the queries' own sort is in query_launch.hip)
 // ---------------------------------------------------------------------------
 __global__ void fill_kernel(int* p, long n, int v) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
-}
-
-// The counting sort's count and scatter take one atomic per distinct key of a wave
-// (wave_count, wave_slot): consecutive queries mostly share their bins.
-__global__ void bin_kernel(FastArgs A, int* keys, int* counts, long n_bins) {
-  const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool valid = q < A.Q;
-  int key = 0;
-  if (valid) {
-    int sub;
-    const long b = box_key(A, A.pts[3 * q], A.pts[3 * q + 1], A.pts[3 * q + 2], &sub);
-    key = b < 0 ? (int)(n_bins - 1) : (int)((long)A.box_rank[b] * A.sub * A.sub * A.sub + sub);
-    keys[q] = key;
-  }
-  wave_count(counts, key, valid);
 }
 
 constexpr int SCAN_T = 256;
@@ -1277,13 +1288,6 @@ __global__ void __launch_bounds__(SCAN_T) scan_apply_kernel(const int* in, long 
     if (base + j < n) out[base + j] = run;
     run += v[j];
   }
-}
-
-__global__ void scatter_kernel(long Q, const int* keys, int* cursor, int* perm) {
-  const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool valid = q < Q;
-  const int pos = wave_slot(cursor, valid ? keys[q] : 0, valid);
-  if (valid) perm[pos] = (int)q;
 }
 
 // bucketing granularity (sub-boxes per box edge): the tuned value, else the finest
@@ -1360,43 +1364,6 @@ inline FastArgs make_fast_args(const ksdf_model* m, const void* points, long Q, 
   A.inv_mc_ff[0] = (float)(1.0 / mc);
   A.inv_mc_ff[1] = (float)(1.0 / mc - (double)(float)(1.0 / mc));
   return A;
-}
-
-// The permutation written by launch_bucketing (the workspace's second array).
-inline int* bucketed_perm(void* ws, long Q) {
-  return reinterpret_cast<int*>(static_cast<char*>(ws) + align256(Q * sizeof(int)));
-}
-
-// Counting sort of the queries by (index box, sub-box); sets A.perm.
-inline int launch_bucketing(const ksdf_model* m, FastArgs& A, void* ws, hipStream_t s) {
-  const long Q = A.Q;
-  // workspace carve-up
-  const long nb = n_bins_of(m);
-  const long tiles = (nb + SCAN_TILE - 1) / SCAN_TILE;
-  char* w = static_cast<char*>(ws);
-  int* keys = reinterpret_cast<int*>(w);
-  w += align256(Q * sizeof(int));
-  int* perm = reinterpret_cast<int*>(w);
-  w += align256(Q * sizeof(int));
-  int* counts = reinterpret_cast<int*>(w);
-  w += align256(nb * sizeof(int));
-  int* cursor = reinterpret_cast<int*>(w);
-  w += align256(nb * sizeof(int));
-  int* tsum = reinterpret_cast<int*>(w);
-  if (tiles > (long)SCAN_TILE) {
-    set_error("query bucketing: too many bins");
-    return KSDF_ERR_UNSUPPORTED;
-  }
-
-  const unsigned g1 = (unsigned)((Q + 255) / 256);
-  hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, counts, nb, 0);
-  hipLaunchKernelGGL(bin_kernel, dim3(g1), dim3(256), 0, s, A, keys, counts, nb);
-  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)tiles), dim3(SCAN_T), 0, s, counts, nb, tsum);
-  hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(SCAN_T), 0, s, tsum, (int)tiles);
-  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)tiles), dim3(SCAN_T), 0, s, counts, nb, tsum, cursor);
-  hipLaunchKernelGGL(scatter_kernel, dim3(g1), dim3(256), 0, s, Q, keys, cursor, perm);
-  A.perm = perm;
-  return KSDF_OK;
 }
 
 }  // namespace

@@ -51,77 +51,11 @@ void launch_query_nt(const ksdf_model* m, const FastArgs& A, hipStream_t s) {
   else launch_query_nt_k<NT, false>(m, A, s);
 }
 
-size_t bucketing_bytes(const ksdf_model* m, long Q) {
-  const long nb = n_bins_of(m);
-  const long tiles = (nb + SCAN_TILE - 1) / SCAN_TILE;
-  return align256(Q * sizeof(int)) * 2 + align256(nb * sizeof(int)) * 2 +
-         align256(tiles * sizeof(int));
-}
-
 }  // namespace
 
-size_t query_fast_workspace_bytes(const ksdf_model* m, long Q) {
-  const long nc = (long)m->n_cells + 1;
-  const long tiles = (nc + SCAN_TILE - 1) / SCAN_TILE;
-  const bool pairs = m->tuning.query_split && m->tuning.query_pairs && query_pairs_usable(m, Q);
-  return bucketing_bytes(m, Q) + 2 * align256(Q * sizeof(P1Rec)) + 2 * align256(nc * sizeof(int)) +
-         align256(tiles * sizeof(int)) + (pairs ? query_pairs_workspace_bytes(m, Q) : 0);
-}
-
-int launch_query_bucketing(const ksdf_model* m, const void* points, long Q, void* ws, hipStream_t s) {
-  if (Q == 0) return KSDF_OK;
-  FastArgs A = make_fast_args(m, points, Q, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                              nullptr, nullptr);
-  return launch_bucketing(m, A, ws, s);
-}
-
-int launch_query_fast(const ksdf_model* m, const void* points, long Q, const int8_t* sign,
-                      void* mean, void* grad, void* var, void* var_f, void* grad_var, int* argmin,
-                      uint8_t* q_status, void* ws, size_t ws_bytes, hipStream_t s, bool prebucketed) {
-  (void)ws_bytes;   // checked by the caller against query_workspace_bytes
-  if (Q == 0) return KSDF_OK;
-  FastArgs A = make_fast_args(m, points, Q, sign, mean, grad, var, var_f, grad_var, argmin, q_status);
-  if (prebucketed) {
-    A.perm = bucketed_perm(ws, Q);
-  } else {
-    int r = launch_bucketing(m, A, ws, s);
-    if (r != KSDF_OK) return r;
-  }
-  timer_mark(m, KSDF_TIMER_QUERY, 0, s);
-  if (m->tuning.query_split) {
-    char* w = static_cast<char*>(ws) + bucketing_bytes(m, Q);
-    const long nc = (long)m->n_cells + 1;
-    P1Rec* rec = reinterpret_cast<P1Rec*>(w);
-    w += align256(Q * sizeof(P1Rec));
-    P1Rec* rec2 = reinterpret_cast<P1Rec*>(w);
-    w += align256(Q * sizeof(P1Rec));
-    int* count = reinterpret_cast<int*>(w);
-    w += align256(nc * sizeof(int));
-    int* cursor = reinterpret_cast<int*>(w);
-    w += align256(nc * sizeof(int));
-    int* tsum = reinterpret_cast<int*>(w);
-    w += align256(((nc + SCAN_TILE - 1) / SCAN_TILE) * sizeof(int));
-    void* pws = (m->tuning.query_pairs && query_pairs_usable(m, Q)) ? w : nullptr;
-    if ((nc + SCAN_TILE - 1) / SCAN_TILE > (long)SCAN_TILE) {
-      set_error("query: too many cells for the argmin regrouping");
-      return KSDF_ERR_UNSUPPORTED;
-    }
-    const bool lane = m->tuning.query_lanes != 0;
-    if (m->tuning.query_block == 64) {
-      if (lane) launch_query_split_64_lane(m, A, rec, rec2, count, cursor, tsum, pws, s);
-      else launch_query_split_64_wave(m, A, rec, rec2, count, cursor, tsum, pws, s);
-    } else {
-      if (lane) launch_query_split_256_lane(m, A, rec, rec2, count, cursor, tsum, pws, s);
-      else launch_query_split_256_wave(m, A, rec, rec2, count, cursor, tsum, pws, s);
-    }
-  } else if (m->tuning.query_block == 64) {
-    launch_query_nt<64>(m, A, s);
-  } else {
-    launch_query_nt<256>(m, A, s);
-  }
-  timer_mark(m, KSDF_TIMER_QUERY, 1, s);
-  KSDF_HIP_TRY(hipGetLastError());
-  return KSDF_OK;
+void launch_query_one(const ksdf_model* m, const FastArgs& A, hipStream_t s) {
+  if (m->tuning.query_block == 64) launch_query_nt<64>(m, A, s);
+  else launch_query_nt<256>(m, A, s);
 }
 
 }  // namespace ksdf

@@ -1,0 +1,187 @@
+// Host side of the FP32 query: the counting sort of the queries, the choice of the
+// launch, and its workspace.
+#include "query_dev.h"
+
+namespace ksdf {
+namespace {
+
+// The counting sort's count and scatter take one atomic per distinct key of a wave
+// (wave_count, wave_slot): consecutive queries mostly share their bins.
+__global__ void bin_kernel(FastArgs A, int* keys, int* counts, long n_bins) {
+  const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const bool valid = q < A.Q;
+  int key = 0;
+  if (valid) {
+    int sub;
+    const long b = box_key(A, A.pts[3 * q], A.pts[3 * q + 1], A.pts[3 * q + 2], &sub);
+    key = b < 0 ? (int)(n_bins - 1) : (int)((long)A.box_rank[b] * A.sub * A.sub * A.sub + sub);
+    keys[q] = key;
+  }
+  wave_count(counts, key, valid);
+}
+
+__global__ void scatter_kernel(long Q, const int* keys, int* cursor, int* perm) {
+  const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const bool valid = q < Q;
+  const int pos = wave_slot(cursor, valid ? keys[q] : 0, valid);
+  if (valid) perm[pos] = (int)q;
+}
+
+// The permutation written by launch_bucketing (the workspace's second array).
+inline int* bucketed_perm(void* ws, long Q) {
+  return reinterpret_cast<int*>(static_cast<char*>(ws) + align256(Q * sizeof(int)));
+}
+
+// Which kernels answer a query of Q points (the outputs are the same bit for bit).  On the
+// room (5.9k cells of 64 samples, K = 8; us):
+//   points               eight lanes each   per-lane cells   wave-shared cells
+//   4,000 at random             41                242               860
+//   65,536 trajectories        131                291              1179
+//   262,144 trajectories       477                453              1170
+//   493,039 grid               829                640               812
+//   2,097,152 grid            3352               1844              1686
+// Eight lanes per query fill the chip with few queries but take 1.7 ns a query at best; the
+// per-lane and the wave-shared kernels start at about 240 us, and the wave-shared ones win
+// once a wave's queries share their cells, at about 100 queries a cell and more.
+constexpr long GROUP_MAX_Q = 196608;
+constexpr long WAVE_MIN_PER_CELL = 96;
+// The eight-lane kernel takes the queries in the caller's order up to this count: the sort
+// costs 50 us, and saves 200 us of 740 for 262,144 points at random but nothing for points
+// that arrive in order (trajectories, grids).
+constexpr long GROUP_UNSORTED_MAX_Q = 131072;
+
+bool pairs_used(const ksdf_model* m, long Q) {
+  return m->tuning.query_split && m->tuning.query_pairs && query_pairs_usable(m, Q);
+}
+// the matrix-core pass 2 (wave-shared cells only)
+bool mfma_used(const ksdf_model* m) {
+  return m->tuning.query_split && m->tuning.query_mfma && !m->tuning.query_lanes && m->Linv32 &&
+         m->max_m <= 64;
+}
+bool group_used(const ksdf_model* m, long Q) {
+  return m->tuning.query_split && Q <= GROUP_MAX_Q && !mfma_used(m) && !pairs_used(m, Q);
+}
+bool lanes_used(const ksdf_model* m, long Q) {
+  return m->tuning.query_lanes ||
+         (!mfma_used(m) && !pairs_used(m, Q) && Q < WAVE_MIN_PER_CELL * m->n_cells);
+}
+bool sort_used(const ksdf_model* m, long Q) {
+  return !group_used(m, Q) || Q > GROUP_UNSORTED_MAX_Q;
+}
+// limits of the sorts, checked for every launch so that a model beyond them is refused
+// whatever the query count
+int check_sorts(const ksdf_model* m) {
+  if ((n_bins_of(m) + SCAN_TILE - 1) / SCAN_TILE > (long)SCAN_TILE) {
+    set_error("query bucketing: too many bins");
+    return KSDF_ERR_UNSUPPORTED;
+  }
+  if (m->tuning.query_split &&
+      ((long)m->n_cells + 1 + SCAN_TILE - 1) / SCAN_TILE > (long)SCAN_TILE) {
+    set_error("query: too many cells for the argmin regrouping");
+    return KSDF_ERR_UNSUPPORTED;
+  }
+  return KSDF_OK;
+}
+
+size_t bucketing_bytes(const ksdf_model* m, long Q) {
+  const long nb = n_bins_of(m);
+  const long tiles = (nb + SCAN_TILE - 1) / SCAN_TILE;
+  return align256(Q * sizeof(int)) * 2 + align256(nb * sizeof(int)) * 2 +
+         align256(tiles * sizeof(int));
+}
+
+}  // namespace
+
+// Counting sort of the queries by (index box, sub-box); sets A.perm.
+int launch_bucketing(const ksdf_model* m, FastArgs& A, void* ws, hipStream_t s) {
+  const long Q = A.Q;
+  // workspace carve-up
+  const long nb = n_bins_of(m);
+  const long tiles = (nb + SCAN_TILE - 1) / SCAN_TILE;
+  char* w = static_cast<char*>(ws);
+  int* keys = reinterpret_cast<int*>(w);
+  w += align256(Q * sizeof(int));
+  int* perm = reinterpret_cast<int*>(w);
+  w += align256(Q * sizeof(int));
+  int* counts = reinterpret_cast<int*>(w);
+  w += align256(nb * sizeof(int));
+  int* cursor = reinterpret_cast<int*>(w);
+  w += align256(nb * sizeof(int));
+  int* tsum = reinterpret_cast<int*>(w);
+  if (int r = check_sorts(m)) return r;
+  const unsigned g1 = (unsigned)((Q + 255) / 256);
+  hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, counts, nb, 0);
+  hipLaunchKernelGGL(bin_kernel, dim3(g1), dim3(256), 0, s, A, keys, counts, nb);
+  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)tiles), dim3(SCAN_T), 0, s, counts, nb, tsum);
+  hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(SCAN_T), 0, s, tsum, (int)tiles);
+  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)tiles), dim3(SCAN_T), 0, s, counts, nb, tsum, cursor);
+  hipLaunchKernelGGL(scatter_kernel, dim3(g1), dim3(256), 0, s, Q, keys, cursor, perm);
+  A.perm = perm;
+  return KSDF_OK;
+}
+
+size_t query_fast_workspace_bytes(const ksdf_model* m, long Q) {
+  const long nc = (long)m->n_cells + 1;
+  const long tiles = (nc + SCAN_TILE - 1) / SCAN_TILE;
+  const bool pairs = pairs_used(m, Q);
+  return bucketing_bytes(m, Q) + 2 * align256(Q * sizeof(P1Rec)) + 2 * align256(nc * sizeof(int)) +
+         align256(tiles * sizeof(int)) + (pairs ? query_pairs_workspace_bytes(m, Q) : 0);
+}
+
+int launch_query_bucketing(const ksdf_model* m, const void* points, long Q, void* ws, hipStream_t s) {
+  if (Q == 0) return KSDF_OK;
+  if (!sort_used(m, Q)) return check_sorts(m);
+  FastArgs A = make_fast_args(m, points, Q, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                              nullptr, nullptr);
+  return launch_bucketing(m, A, ws, s);
+}
+
+int launch_query_fast(const ksdf_model* m, const void* points, long Q, const int8_t* sign,
+                      void* mean, void* grad, void* var, void* var_f, void* grad_var, int* argmin,
+                      uint8_t* q_status, void* ws, size_t ws_bytes, hipStream_t s, bool prebucketed) {
+  (void)ws_bytes;   // checked by the caller against query_workspace_bytes
+  if (Q == 0) return KSDF_OK;
+  FastArgs A = make_fast_args(m, points, Q, sign, mean, grad, var, var_f, grad_var, argmin, q_status);
+  if (int r = check_sorts(m)) return r;
+  if (!sort_used(m, Q)) {
+    A.perm = nullptr;
+  } else if (prebucketed) {
+    A.perm = bucketed_perm(ws, Q);
+  } else {
+    int r = launch_bucketing(m, A, ws, s);
+    if (r != KSDF_OK) return r;
+  }
+  timer_mark(m, KSDF_TIMER_QUERY, 0, s);
+  if (group_used(m, Q)) {
+    launch_query_group(m, A, s);
+  } else if (m->tuning.query_split) {
+    char* w = static_cast<char*>(ws) + bucketing_bytes(m, Q);
+    const long nc = (long)m->n_cells + 1;
+    P1Rec* rec = reinterpret_cast<P1Rec*>(w);
+    w += align256(Q * sizeof(P1Rec));
+    P1Rec* rec2 = reinterpret_cast<P1Rec*>(w);
+    w += align256(Q * sizeof(P1Rec));
+    int* count = reinterpret_cast<int*>(w);
+    w += align256(nc * sizeof(int));
+    int* cursor = reinterpret_cast<int*>(w);
+    w += align256(nc * sizeof(int));
+    int* tsum = reinterpret_cast<int*>(w);
+    w += align256(((nc + SCAN_TILE - 1) / SCAN_TILE) * sizeof(int));
+    void* pws = pairs_used(m, Q) ? w : nullptr;
+    const bool lane = lanes_used(m, Q);
+    if (m->tuning.query_block == 64) {
+      if (lane) launch_query_split_64_lane(m, A, rec, rec2, count, cursor, tsum, pws, s);
+      else launch_query_split_64_wave(m, A, rec, rec2, count, cursor, tsum, pws, s);
+    } else {
+      if (lane) launch_query_split_256_lane(m, A, rec, rec2, count, cursor, tsum, pws, s);
+      else launch_query_split_256_wave(m, A, rec, rec2, count, cursor, tsum, pws, s);
+    }
+  } else {
+    launch_query_one(m, A, s);
+  }
+  timer_mark(m, KSDF_TIMER_QUERY, 1, s);
+  KSDF_HIP_TRY(hipGetLastError());
+  return KSDF_OK;
+}
+
+}  // namespace ksdf

@@ -1,0 +1,71 @@
+"""Eight lanes per query: the query kernel that answers small and medium calls,
+at the sizes where their blocks of eight and their dispatch turn.
+
+The FP32 query kernel keeps the order of every operation of the one-kernel form
+(query_split=0), so all outputs agree bit for bit; it is used up to 196,608 points and sorts
+them above 131,072.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_29227_amd import ksdf, scenes
+
+pytestmark = pytest.mark.gpu
+
+OUT = ("mean", "grad", "var", "var_f", "grad_var", "argmin", "status")
+
+
+def _sphere(m_max, n_samples=9000, n_queries=1000, dtype=np.float32):
+    wl = scenes.sphere_workload(n_samples=n_samples, n_queries=n_queries)
+    return dataclasses.replace(wl, points=wl.points.astype(dtype), queries=wl.queries.astype(dtype),
+                               m_max=m_max)
+
+
+def _fitted(wl, **kw):
+    cells = ksdf.build_cells(wl.points, wl.origin, wl.h, wl.margin, wl.m_max, 1)
+    model = ksdf.Model(cells, len(wl.points), wl.origin, wl.h, ell=wl.ell, noise_var=wl.noise_var, **kw)
+    model.fit(torch.from_numpy(wl.points).cuda())
+    return model, cells
+
+
+@pytest.mark.parametrize("kernel", ["rbf", "matern32"])
+@pytest.mark.parametrize("m_max", [1, 7, 8, 9, 63, 64, 65, 128])
+@pytest.mark.parametrize("k_fuse", [1, 8, 9, 16])
+def test_query_equals_the_one_kernel_form(kernel, m_max, k_fuse):
+    print(f"[gpu-case] group query {kernel} m<={m_max} k={k_fuse}", flush=True)
+    wl = _sphere(m_max)
+    model, cells = _fitted(wl, kernel=kernel, k_fuse=k_fuse)
+    assert cells.m.max() == m_max
+    q = torch.from_numpy(wl.queries).cuda()
+    q[::5] *= 40   # outside the candidate index: every cell is scanned
+    sg = torch.from_numpy(wl.sign).cuda()
+    for n in (1, 7, 8, 9, 65, 1000):
+        model.set_tuning(query_split=0)
+        want = model.query(q[:n], sg[:n], grad_var=True)
+        model.set_tuning(query_split=1)
+        got = model.query(q[:n], sg[:n], grad_var=True)
+        few = model.query(q[:n], sg[:n], var_f=False, argmin=False, status=False)
+        for k in OUT:
+            assert torch.equal(got[k], want[k]), (k, n)
+        for k in few:
+            assert torch.equal(few[k], want[k]), (k, n)
+
+
+@pytest.mark.parametrize("n", [131072, 131073, 196608, 196609])
+def test_query_and_bucketed_query_at_the_dispatch_edges(n):
+    print(f"[gpu-case] group query, {n} points", flush=True)
+    wl = scenes.small_room_workload(n_queries=n, cfg_id=47, uneven=True)
+    model, _ = _fitted(wl)
+    q, sg = torch.from_numpy(wl.queries).cuda(), torch.from_numpy(wl.sign).cuda()
+    model.set_tuning(query_split=0)
+    want = model.query(q, sg, grad_var=True)
+    model.set_tuning(query_split=1)
+    got = model.query(q, sg, grad_var=True)
+    ws = model.new_workspace(n)
+    model.bucket(q, workspace=ws)
+    two = model.query(q, sg, grad_var=True, workspace=ws, bucketed=True)
+    for k in OUT:
+        assert torch.equal(got[k], want[k]) and torch.equal(two[k], want[k]), k
