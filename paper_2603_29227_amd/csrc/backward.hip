@@ -22,87 +22,17 @@
 // differentiated through when tied.  k* is recomputed, never stored.
 #include <cmath>
 
-#include "ff.h"
-#include "ksdf_internal.h"
-#include "wave_ops.h"
+#include "backward_dev.h"
 
 namespace ksdf {
 namespace {
 
 constexpr int BT = 256;
 
+// One query's VJP on its argmin cell without a var_f cotangent (those run eight lanes per
+// query, backward_group.hip), per-thread loops: FP64 RBF models with many queries.
 template <class T>
-struct BwdArgs {
-  const T* __restrict__ pts;
-  long Q;
-  const int8_t* sign;
-  const int* argmin;
-  const T* d_mean;
-  const T* d_grad;
-  const T* d_var;
-  const T* d_var_f;
-  T* d_points;
-  double* part;            // [Q,2] per-query (dL/dl, dL/dsigma^2)
-  int n_cells;
-  const int* offsets;
-  const long* loff;
-  const T* ps;             // [nnz,4] (px,py,pz,a) cell-local
-  const float* plo;        // FP32 store: float-float low parts of ps
-  const T* sv;
-  const T* L;              // packed rows, reciprocal diagonal
-  const T* xi;             // [nnz,2] (FP64) or [nnz+pad,4] float-float (FP32)
-  const T* D;              // packed dA/dl or null
-  const double* centre64;
-  const float* box;        // [n,8] sample AABB (cell-local)
-  T ell, two_l2, alpha;
-  float c2_ff[2];          // log2(e) / (2 l^2) as a float pair (FP32 models)
-  float mc_ff[2];          // Matern c = sqrt(3) / l and c log2(e) as float pairs
-  float mcl_ff[2];
-  double ell_d, alpha_d;   // the same in FP64
-  int alpha_tied;
-  int uniform_noise;
-  // the softplus margin cost (ksdf_cost_backward): when c_mean is set, the mean and
-  // var cotangents are formed from the forward outputs instead of read
-  const T* c_mean;
-  const T* c_var;
-  T c_margin, c_kvar;
-  T* c_cost;               // per-query cost, or null
-};
-
-// Cotangents of mean and var for query q: the given ones, or those of the cost
-// softplus(t), t = margin - mean + kvar sqrt(var): d/dmean = -sigmoid(t) and
-// d/dvar = kvar sigmoid(t) / (2 sqrt(var)), with the stable forms of sigmoid and
-// softplus (max(t, 0) + log1p(e^-|t|)); var is clamped below at 1e-30.
-template <class T>
-__device__ __forceinline__ void mean_var_cotangents(const BwdArgs<T>& A, long q, T& gm, T& gv) {
-  gm = A.d_mean ? A.d_mean[q] : T(0);
-  gv = A.d_var ? A.d_var[q] : T(0);
-  if (A.c_mean) {
-    const T sd = sqrt(fmax(A.c_var[q], T(1e-30)));
-    const T t = A.c_margin - A.c_mean[q] + A.c_kvar * sd;
-    const T e = exp(-fabs(t));
-    const T sg = t >= T(0) ? T(1) / (T(1) + e) : e / (T(1) + e);
-    gm = -sg;
-    gv = A.c_kvar * sg / (T(2) * sd);
-    if (A.c_cost) A.c_cost[q] = fmax(t, T(0)) + log1p(e);
-  }
-}
-
-template <class T>
-__device__ __forceinline__ T aabb_d2(const float* bx, T x, T y, T z) {
-  const T ex = fmax(fmax((T)bx[0] - x, T(0)), x - (T)bx[4]);
-  const T ey = fmax(fmax((T)bx[1] - y, T(0)), y - (T)bx[5]);
-  const T ez = fmax(fmax((T)bx[2] - z, T(0)), z - (T)bx[6]);
-  return ex * ex + ey * ey + ez * ez;
-}
-
-// One query's VJP on its argmin cell, per-thread loops (the plain path; also the
-// FP32 path, where the wave calls it with a wave-uniform cell so the per-cell data
-// arrive through scalar loads).  With VARF (a var_f cotangent is given), v is
-// per-thread storage for k, then L^{-1} k, then beta = A^{-1} k; without it the two
-// triangular solves and v are not needed.
-template <class T, bool VARF>
-__device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T* v, T out_dx[3],
+__device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T out_dx[3],
                                           double out_th[2]) {
   const T lt = A.ell;
   const T x0 = A.pts[3 * q], x1 = A.pts[3 * q + 1], x2 = A.pts[3 * q + 2];
@@ -112,11 +42,9 @@ __device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T*
   T gg[3] = {T(0), T(0), T(0)};
   if (A.d_grad)
     for (int d = 0; d < 3; ++d) gg[d] = A.d_grad[3 * q + d];
-  const T gf = VARF && A.d_var_f ? A.d_var_f[q] : T(0);
   const int b = A.offsets[c], m = A.offsets[c + 1] - b;
   const T* p = A.ps + 4L * b;
   const T* sv = A.sv + b;
-  const T* Lc = A.L + A.loff[c];
   constexpr int XS = sizeof(T) == 4 ? 4 : 2;   // FP32 store: float-float pairs, hi first
   const T* xi = A.xi + XS * (long)b;
   const double* cc = A.centre64 + 3L * c;
@@ -128,7 +56,6 @@ __device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T*
     const T dx = l0 - p[4 * i], dy = l1 - p[4 * i + 1], dz = l2 - p[4 * i + 2];
     d2 = fmin(d2, dx * dx + dy * dy + dz * dz);
   }
-  const T ginv = exp(-d2 * inv2l2);
   const T zmin = sqrt(d2);
   // pass A: f', w', Z, softmin moments, k
   T f = 0, w[3] = {0, 0, 0}, Za = 0, S = 0, M1 = 0, M2 = 0;
@@ -147,24 +74,6 @@ __device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T*
     S += sm;
     M1 += sm * t;
     M2 += sm * t * t;
-    if constexpr (VARF) v[i] = e * ginv;
-  }
-  T vv = 0;
-  if constexpr (VARF) {
-    // forward substitution: v <- L^{-1} k
-    for (int i = 0; i < m; ++i) {
-      const T* row = Lc + (long)i * (i + 1) / 2;
-      T t = v[i];
-      for (int j = 0; j < i; ++j) t -= row[j] * v[j];
-      v[i] = t * row[i];
-      vv += v[i] * v[i];
-    }
-    // backward substitution: v <- L^{-T} v = A^{-1} k (row-oriented, last row first)
-    for (int i = m - 1; i >= 0; --i) {
-      const T* row = Lc + (long)i * (i + 1) / 2;
-      v[i] *= row[i];
-      for (int j = 0; j < i; ++j) v[j] -= row[j] * v[i];
-    }
   }
   const T u2 = f > T(0) ? d2 - A.two_l2 * log(f) : T(-1);
   const bool mean_live = u2 > T(0);
@@ -175,7 +84,6 @@ __device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T*
     const T gw = (gg[0] * w[0] + gg[1] * w[1] + gg[2] * w[2]) / wn;
     for (int d = 0; d < 3; ++d) y[d] = (gg[d] - gw * w[d] / wn) / wn;
   }
-  const bool varf_live = VARF && (T(1) - vv) > T(0);
   const T m1 = M1 / S;
   const T h = zmin + m1;
   const T Vz = M2 / S - m1 * m1;
@@ -193,8 +101,8 @@ __device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T*
     dVa += T(2) * sv[i] * ci * (si * (h - z) * (Bi + T(1)) - A.alpha * si * Vz);
   }
   // pass C: per-sample accumulations
-  T dxv[3] = {0, 0, 0}, Hy[3] = {0, 0, 0}, Wz[3] = {0, 0, 0}, bk[3] = {0, 0, 0};
-  T bkz = 0, bb = 0, El = 0, Es = 0, Eld[3] = {0, 0, 0}, Esd[3] = {0, 0, 0};
+  T dxv[3] = {0, 0, 0}, Hy[3] = {0, 0, 0}, Wz[3] = {0, 0, 0};
+  T El = 0, Es = 0, Eld[3] = {0, 0, 0}, Esd[3] = {0, 0, 0};
   for (int i = 0; i < m; ++i) {
     const T di[3] = {l0 - p[4 * i], l1 - p[4 * i + 1], l2 - p[4 * i + 2]};
     const T z2 = di[0] * di[0] + di[1] * di[1] + di[2] * di[2];
@@ -205,39 +113,21 @@ __device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T*
     const T ci = si * (A.alpha * (h - z) + T(1));
     const T dvdz = T(2) * A.alpha * (-sv[i] * ci * (ci + si) + si * V + ci * P);
     const T dy = di[0] * y[0] + di[1] * y[1] + di[2] * y[2];
-    T kb = 0;
-    if constexpr (VARF) kb = v[i] * e * ginv;
     for (int d = 0; d < 3; ++d) {
       if (z > T(0)) dxv[d] += dvdz * di[d] / z;
       Hy[d] += ae * dy * di[d];
       Wz[d] += ae * z2 * di[d];
-      if constexpr (VARF) bk[d] += kb * di[d];
       Eld[d] += e * xi[XS * i] * di[d];
       Esd[d] += e * xi[XS * i + 1] * di[d];
     }
-    if constexpr (VARF) {
-      bkz += kb * z2;
-      bb += v[i] * v[i];
-    }
     El += e * xi[XS * i];
     Es += e * xi[XS * i + 1];
-  }
-  T bDb = 0;
-  if (VARF && A.D && gf != T(0) && varf_live) {
-    const T* Dc = A.D + A.loff[c];
-    for (int i = 1; i < m; ++i) {
-      const T* row = Dc + (long)i * (i + 1) / 2;
-      T t = 0;
-      for (int j = 0; j < i; ++j) t += row[j] * v[j];
-      bDb += T(2) * v[i] * t;
-    }
   }
   const T l3 = lt * lt * lt;
   // d_points
   for (int d = 0; d < 3; ++d) {
     T r = s * (f * y[d] - Hy[d] / (lt * lt)) + gv * dxv[d];
     if (mean_live) r += s * gm * w[d] / (f * u);
-    if (varf_live) r += gf * T(2) * bk[d] / (lt * lt);
     out_dx[d] = r;
   }
   // weight cotangent . xi (through the fit)
@@ -252,30 +142,16 @@ __device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T*
   if (mean_live) dl += s * gm * (u2 - Za / f) / (lt * u);
   dl += s * (y[0] * Wz[0] + y[1] * Wz[1] + y[2] * Wz[2]) / l3;
   if (A.alpha_tied) dl += gv * dVa * (-T(2) * A.alpha / lt);
-  if (varf_live) dl += gf * (-T(2) * bkz / l3 + bDb);
   dl -= aXl;
   if (A.uniform_noise) {
     ds += gv * C2;
-    if (varf_live) ds += gf * bb;
     ds -= aXs;
   }
   out_th[0] = (double)dl;
   out_th[1] = (double)ds;
 }
 
-// the per-query hyperparameter terms: FP64 models keep doubles; FP32 models keep
-// float pairs (dl, ds), summed afterwards in float-float
 template <class T>
-__device__ __forceinline__ void store_theta(const BwdArgs<T>& A, long q, const double th[2]) {
-  if constexpr (sizeof(T) == 8) {
-    A.part[2 * q] = th[0];
-    A.part[2 * q + 1] = th[1];
-  } else {
-    reinterpret_cast<float2*>(A.part)[q] = make_float2((float)th[0], (float)th[1]);
-  }
-}
-
-template <class T, bool VARF>
 __global__ void __launch_bounds__(BT) bwd_plain_kernel(BwdArgs<T> A) {
   const long q = (long)blockIdx.x * BT + threadIdx.x;
   if (q >= A.Q) return;
@@ -287,14 +163,7 @@ __global__ void __launch_bounds__(BT) bwd_plain_kernel(BwdArgs<T> A) {
     T gm, gv;
     mean_var_cotangents(A, q, gm, gv);   // the cost alone
   }
-  if (c >= 0) {
-    if constexpr (VARF) {
-      T v[KSDF_MAX_M];
-      query_vjp<T, true>(A, q, c, v, dx, th);
-    } else {
-      query_vjp<T, false>(A, q, c, nullptr, dx, th);
-    }
-  }
+  if (c >= 0) query_vjp<T>(A, q, c, dx, th);
   for (int d = 0; d < 3; ++d) A.d_points[3 * q + d] = dx[d];
   store_theta(A, q, th);
 }
@@ -311,50 +180,32 @@ __global__ void __launch_bounds__(BT) bwd_plain_kernel(BwdArgs<T> A) {
 //                              d/dl|_A = -2 c^2 sum beta_i z_i^2 e^{-c z_i} / l
 // and the softmin variance as for the RBF.  The fit enters through the adjoint
 // vectors xi_l = A^{-1} (dA/dl) a and xi_s = A^{-1} a as in query_vjp.
-template <class T, bool VARF>
-__device__ void vjp_matern(const BwdArgs<T>& A, long q, int c, double* v, double out_dx[3],
+template <bool VARF>
+__device__ void vjp_matern(const BwdArgs<double>& A, long q, int c, double* v, double out_dx[3],
                            double out_th[2]) {
-  constexpr bool F64 = sizeof(T) == 8;
-  const double lt = F64 ? (double)A.ell : A.ell_d;
-  const double al = F64 ? (double)A.alpha : A.alpha_d;
+  const double lt = A.ell, al = A.alpha;
   const double mc = sqrt(3.0) / lt;
   const double x0 = A.pts[3 * q], x1 = A.pts[3 * q + 1], x2 = A.pts[3 * q + 2];
   const double s = A.sign ? (double)A.sign[q] : 1.0;
-  T gmt, gvt;
-  mean_var_cotangents(A, q, gmt, gvt);
-  const double gm = gmt, gv = gvt;
+  double gm, gv;
+  mean_var_cotangents(A, q, gm, gv);
   double gg[3] = {0, 0, 0};
   if (A.d_grad)
     for (int d = 0; d < 3; ++d) gg[d] = A.d_grad[3 * q + d];
-  const double gf = VARF && A.d_var_f ? (double)A.d_var_f[q] : 0.0;
+  const double gf = VARF && A.d_var_f ? A.d_var_f[q] : 0.0;
   const int b = A.offsets[c], m = A.offsets[c + 1] - b;
-  const T* Lc = A.L + A.loff[c];
+  const double* Lc = A.L + A.loff[c];
   const double l0 = x0 - A.centre64[3L * c], l1 = x1 - A.centre64[3L * c + 1],
                l2 = x2 - A.centre64[3L * c + 2];
   auto load = [&](int i, double di[3], double& pa) {
-    if constexpr (F64) {
-      const T* p = A.ps + 4L * (b + i);
-      di[0] = l0 - p[0];
-      di[1] = l1 - p[1];
-      di[2] = l2 - p[2];
-      pa = p[3];
-    } else {
-      const float* p = A.ps + 4L * (b + i);
-      const float* pl = A.plo + 4L * (b + i);
-      di[0] = l0 - ((double)p[0] + (double)pl[0]);
-      di[1] = l1 - ((double)p[1] + (double)pl[1]);
-      di[2] = l2 - ((double)p[2] + (double)pl[2]);
-      pa = (double)p[3] + (double)pl[3];
-    }
+    const double* p = A.ps + 4L * (b + i);
+    di[0] = l0 - p[0];
+    di[1] = l1 - p[1];
+    di[2] = l2 - p[2];
+    pa = p[3];
   };
-  auto xi_l = [&](int i) -> double {
-    if constexpr (F64) return A.xi[2L * (b + i)];
-    else return (double)A.xi[4L * (b + i)] + (double)A.xi[4L * (b + i) + 2];
-  };
-  auto xi_s = [&](int i) -> double {
-    if constexpr (F64) return A.xi[2L * (b + i) + 1];
-    else return (double)A.xi[4L * (b + i) + 1] + (double)A.xi[4L * (b + i) + 3];
-  };
+  auto xi_l = [&](int i) { return A.xi[2L * (b + i)]; };
+  auto xi_s = [&](int i) { return A.xi[2L * (b + i) + 1]; };
   double d2 = INFINITY;
   for (int i = 0; i < m; ++i) {
     double di[3], pa;
@@ -384,16 +235,16 @@ __device__ void vjp_matern(const BwdArgs<T>& A, long q, int c, double* v, double
   double vv = 0;
   if constexpr (VARF) {
     for (int i = 0; i < m; ++i) {
-      const T* row = Lc + (long)i * (i + 1) / 2;
+      const double* row = Lc + (long)i * (i + 1) / 2;
       double t = v[i];
-      for (int j = 0; j < i; ++j) t -= (double)row[j] * v[j];
-      v[i] = t * (double)row[i];
+      for (int j = 0; j < i; ++j) t -= row[j] * v[j];
+      v[i] = t * row[i];
       vv += v[i] * v[i];
     }
     for (int i = m - 1; i >= 0; --i) {
-      const T* row = Lc + (long)i * (i + 1) / 2;
-      v[i] *= (double)row[i];
-      for (int j = 0; j < i; ++j) v[j] -= (double)row[j] * v[i];
+      const double* row = Lc + (long)i * (i + 1) / 2;
+      v[i] *= row[i];
+      for (int j = 0; j < i; ++j) v[j] -= row[j] * v[i];
     }
   }
   const double u = f > 0.0 ? zmin - log(f) / mc : -1.0;
@@ -459,11 +310,11 @@ __device__ void vjp_matern(const BwdArgs<T>& A, long q, int c, double* v, double
   }
   double bDb = 0;
   if (VARF && A.D && gf != 0.0 && varf_live) {
-    const T* Dc = A.D + A.loff[c];
+    const double* Dc = A.D + A.loff[c];
     for (int i = 1; i < m; ++i) {
-      const T* row = Dc + (long)i * (i + 1) / 2;
+      const double* row = Dc + (long)i * (i + 1) / 2;
       double t = 0;
-      for (int j = 0; j < i; ++j) t += (double)row[j] * v[j];
+      for (int j = 0; j < i; ++j) t += row[j] * v[j];
       bDb += 2.0 * v[i] * t;
     }
   }
@@ -495,28 +346,13 @@ __device__ void vjp_matern(const BwdArgs<T>& A, long q, int c, double* v, double
   out_th[1] = ds;
 }
 
-// Compensated FP32 sum (TwoSum, Knuth): the running sum and the sum of its rounding
-// errors, so that m terms carry about one rounding of the result instead of m.
-struct CAcc {
-  float s = 0.f, c = 0.f;
-  __device__ __forceinline__ void add(float x) {
-#pragma clang fp contract(off)
-    const float t = s + x;
-    const float bb = t - s;
-    c += (s - (t - bb)) + (x - bb);
-    s = t;
-  }
-  __device__ __forceinline__ float val() const { return s + c; }
-};
-
 // The Matern 3/2 VJP of one query for an FP32 model, in FP32: the same sums as
 // vjp_matern, with the differences to the samples exact as float pairs, z_i and
 // z_i - d as float pairs (the square root by one Newton step), the exponentials from
 // float-pair arguments (the hardware 2^x on the fraction, the low part to first
-// order), and the sums whose terms cancel accumulated with compensation.  With VARF
-// the triangular solves for A^{-1} k run in FP32 on the factor (as query_vjp).
-template <bool VARF>
-__device__ void vjp_matern_f32(const BwdArgs<float>& A, long q, int c, float* v, float out_dx[3],
+// order), and the sums whose terms cancel accumulated with compensation.  A var_f cotangent
+// runs eight lanes per query (backward_group.hip).
+__device__ void vjp_matern_f32(const BwdArgs<float>& A, long q, int c, float out_dx[3],
                                double out_th[2]) {
   const float lt = A.ell, al = A.alpha;
   const float mc = A.mc_ff[0];
@@ -528,9 +364,7 @@ __device__ void vjp_matern_f32(const BwdArgs<float>& A, long q, int c, float* v,
   float gg[3] = {0.f, 0.f, 0.f};
   if (A.d_grad)
     for (int d = 0; d < 3; ++d) gg[d] = A.d_grad[3 * q + d];
-  const float gf = VARF && A.d_var_f ? A.d_var_f[q] : 0.f;
   const int b = A.offsets[c], m = A.offsets[c + 1] - b;
-  const float* Lc = A.L + A.loff[c];
   const float4* P4 = reinterpret_cast<const float4*>(A.ps);
   const float4* PL = reinterpret_cast<const float4*>(A.plo);
   const float4* X4 = reinterpret_cast<const float4*>(A.xi);
@@ -587,22 +421,6 @@ __device__ void vjp_matern_f32(const BwdArgs<float>& A, long q, int c, float* v,
     S += sm;
     M1 += sm * t;
     M2 += sm * t * t;
-    if constexpr (VARF) v[i] = fmaf(mc, z, 1.f) * expc(zf);
-  }
-  float vv = 0.f;
-  if constexpr (VARF) {
-    for (int i = 0; i < m; ++i) {
-      const float* row = Lc + (long)i * (i + 1) / 2;
-      float t = v[i];
-      for (int j = 0; j < i; ++j) t -= row[j] * v[j];
-      v[i] = t * row[i];
-      vv += v[i] * v[i];
-    }
-    for (int i = m - 1; i >= 0; --i) {
-      const float* row = Lc + (long)i * (i + 1) / 2;
-      v[i] *= row[i];
-      for (int j = 0; j < i; ++j) v[j] -= row[j] * v[i];
-    }
   }
   const float fv = f.val(), fev = fe.val();
   const float wv[3] = {w[0].val(), w[1].val(), w[2].val()};
@@ -614,7 +432,6 @@ __device__ void vjp_matern_f32(const BwdArgs<float>& A, long q, int c, float* v,
     const float gw = (gg[0] * wv[0] + gg[1] * wv[1] + gg[2] * wv[2]) / wn;
     for (int d = 0; d < 3; ++d) y[d] = (gg[d] - gw * wv[d] / wn) / wn;
   }
-  const bool varf_live = VARF && (1.f - vv) > 0.f;
   const float iS = 1.f / S;
   const float m1 = M1 * iS;
   const float h = zmin + m1;
@@ -636,9 +453,8 @@ __device__ void vjp_matern_f32(const BwdArgs<float>& A, long q, int c, float* v,
     C2 += ci * ci;
     dVa += 2.f * svi * ci * (si * (h - z) * (Bi + 1.f) - al * si * Vz);
   }
-  float dxv[3] = {0.f, 0.f, 0.f}, bk[3] = {0.f, 0.f, 0.f};
+  float dxv[3] = {0.f, 0.f, 0.f};
   CAcc Hy[3], Wz[3], El, Es, Eld[3], Esd[3];
-  float bkz = 0.f, bb = 0.f;
   for (int i = 0; i < m; ++i) {
     float di[3], pa;
     ff z2f;
@@ -654,8 +470,6 @@ __device__ void vjp_matern_f32(const BwdArgs<float>& A, long q, int c, float* v,
     const float svi = A.sv[b + i];
     const float dvdz = 2.f * al * (-svi * ci * (ci + si) + si * V + ci * Pp);
     const float dy = di[0] * y[0] + di[1] * y[1] + di[2] * y[2];
-    float kb = 0.f;
-    if constexpr (VARF) kb = v[i] * expc(zf);
     const float4 xq = X4[b + i];
     const float xl = xq.x + xq.z, xs = xq.y + xq.w;
     const float rz = z > 0.f ? 1.f / z : 0.f;
@@ -664,31 +478,15 @@ __device__ void vjp_matern_f32(const BwdArgs<float>& A, long q, int c, float* v,
       dxv[d] += dvdz * di[d] * rz;
       Hy[d].add(ae * dy * di[d] * rz);
       Wz[d].add(ae * z * di[d]);
-      if constexpr (VARF) bk[d] += kb * di[d];
       Eld[d].add(e * xl * di[d]);
       Esd[d].add(e * xs * di[d]);
-    }
-    if constexpr (VARF) {
-      bkz += kb * z2;
-      bb += v[i] * v[i];
     }
     El.add(kp * xl);
     Es.add(kp * xs);
   }
-  float bDb = 0.f;
-  if (VARF && A.D && gf != 0.f && varf_live) {
-    const float* Dc = A.D + A.loff[c];
-    for (int i = 1; i < m; ++i) {
-      const float* row = Dc + (long)i * (i + 1) / 2;
-      float t = 0.f;
-      for (int j = 0; j < i; ++j) t += row[j] * v[j];
-      bDb += 2.f * v[i] * t;
-    }
-  }
   for (int d = 0; d < 3; ++d) {
     float r = s * (fev * y[d] - mc * Hy[d].val()) + gv * dxv[d];
     if (mean_live) r += s * gm * mc * wv[d] / fv;
-    if (varf_live) r += gf * 2.f * mc * mc * bk[d];
     out_dx[d] = r;
   }
   float aXl = s * (y[0] * Eld[0].val() + y[1] * Eld[1].val() + y[2] * Eld[2].val());
@@ -702,46 +500,54 @@ __device__ void vjp_matern_f32(const BwdArgs<float>& A, long q, int c, float* v,
   if (mean_live) dl += s * gm * (u - mc * Za.val() / fv) / lt;
   dl += s * (mc / lt) * (y[0] * Wz[0].val() + y[1] * Wz[1].val() + y[2] * Wz[2].val());
   if (A.alpha_tied) dl += gv * dVa * (-2.f * al / lt);
-  if (varf_live) dl += gf * (-2.f * mc * mc * bkz / lt + bDb);
   dl -= aXl;
   if (A.uniform_noise) {
     ds += gv * C2;
-    if (varf_live) ds += gf * bb;
     ds -= aXs;
   }
   out_th[0] = (double)dl;
   out_th[1] = (double)ds;
 }
 
-template <class T, bool VARF>
-__global__ void __launch_bounds__(BT) bwd_matern_kernel(BwdArgs<T> A) {
+// FP32 models: the points in argmin-cell order (perm), so that a wave's lanes read few
+// cells (1e6 points at random 5.1 ms in the caller's order)
+__global__ void __launch_bounds__(BT) bwd_matern32_kernel(BwdArgs<float> A, const int* perm) {
+  const long sq = (long)blockIdx.x * BT + threadIdx.x;
+  if (sq >= A.Q) return;
+  const long q = perm[sq];
+  int c = A.argmin[q];
+  if (c >= A.n_cells) c = -1;
+  float dx[3] = {0.f, 0.f, 0.f};
+  double th[2] = {0.0, 0.0};
+  if (c < 0 && A.c_mean) {
+    float gm, gv;
+    mean_var_cotangents(A, q, gm, gv);   // the cost alone
+  }
+  if (c >= 0) vjp_matern_f32(A, q, c, dx, th);
+  for (int d = 0; d < 3; ++d) A.d_points[3 * q + d] = dx[d];
+  store_theta(A, q, th);
+}
+
+template <bool VARF>
+__global__ void __launch_bounds__(BT) bwd_matern64_kernel(BwdArgs<double> A) {
   const long q = (long)blockIdx.x * BT + threadIdx.x;
   if (q >= A.Q) return;
   int c = A.argmin[q];
   if (c >= A.n_cells) c = -1;
   double dx[3] = {0, 0, 0}, th[2] = {0, 0};
   if (c < 0 && A.c_mean) {
-    T gm, gv;
+    double gm, gv;
     mean_var_cotangents(A, q, gm, gv);   // the cost alone
   }
   if (c >= 0) {
-    if constexpr (sizeof(T) == 4) {
-      float fdx[3];
-      if constexpr (VARF) {
-        float v[KSDF_MAX_M];
-        vjp_matern_f32<true>(A, q, c, v, fdx, th);
-      } else {
-        vjp_matern_f32<false>(A, q, c, nullptr, fdx, th);
-      }
-      for (int d = 0; d < 3; ++d) dx[d] = fdx[d];
-    } else if constexpr (VARF) {
+    if constexpr (VARF) {
       double v[KSDF_MAX_M];
-      vjp_matern<T, true>(A, q, c, v, dx, th);
+      vjp_matern<VARF>(A, q, c, v, dx, th);
     } else {
-      vjp_matern<T, false>(A, q, c, nullptr, dx, th);
+      vjp_matern<VARF>(A, q, c, nullptr, dx, th);
     }
   }
-  for (int d = 0; d < 3; ++d) A.d_points[3 * q + d] = (T)dx[d];
+  for (int d = 0; d < 3; ++d) A.d_points[3 * q + d] = dx[d];
   store_theta(A, q, th);
 }
 
@@ -753,10 +559,9 @@ __global__ void __launch_bounds__(BT) bwd_matern_kernel(BwdArgs<T> A) {
 // sums sum e_i xi_i -- are accumulated with compensation, so that their error is a
 // few roundings of the terms rather than of the sum; the softmin sums (positive
 // terms) are plain.  The per-query hyperparameter terms leave in FP64 for the
-// fixed-order reduction.  UNI: the cell is wave-uniform (scalar loads).
+// fixed-order reduction.
 constexpr int BCH = 2;
 
-template <bool UNI>
 __device__ __forceinline__ void vjp_f32(const BwdArgs<float>& A, float x0, float x1, float x2,
                                         float s, float gm, const float gg[3], float gv, int c,
                                         float out_dx[3], double out_th[2]) {
@@ -764,8 +569,8 @@ __device__ __forceinline__ void vjp_f32(const BwdArgs<float>& A, float x0, float
   const float4* __restrict__ PL = reinterpret_cast<const float4*>(A.plo);
   const float4* __restrict__ X4 = reinterpret_cast<const float4*>(A.xi);
   const float* __restrict__ SV = A.sv;
-  const int b = UNI ? __builtin_amdgcn_readfirstlane(A.offsets[c]) : A.offsets[c];
-  const int m = (UNI ? __builtin_amdgcn_readfirstlane(A.offsets[c + 1]) : A.offsets[c + 1]) - b;
+  const int b = A.offsets[c];
+  const int m = A.offsets[c + 1] - b;
   const float lt = A.ell, two_l2 = A.two_l2, al = A.alpha;
   const float ca = 1.4426950408889634f * al;
   // the query in the cell's frame, exact as a float pair (the store's coordinates are
@@ -881,7 +686,7 @@ __device__ __forceinline__ void vjp_f32(const BwdArgs<float>& A, float x0, float
       C2 += ci * ci;
       dVa += 2.f * svj * ci * (si * (h - z) * (Bi + 1.f) - al * si * Vz);
       const float rz = z > 0.f ? 1.f / z : 0.f;
-      const float q1 = -svj * ci * (ci + si) * rz, q2 = si * rz, q3 = ci * rz;
+      const float q1 = var_part1_f32(svj, ci, si, rz), q2 = si * rz, q3 = ci * rz;
       const float dy = di[0] * y[0] + di[1] * y[1] + di[2] * y[2];
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
@@ -898,12 +703,9 @@ __device__ __forceinline__ void vjp_f32(const BwdArgs<float>& A, float x0, float
     }
   }
   const float l3 = lt * lt * lt;
-  for (int d = 0; d < 3; ++d) {
-    const float dxv = 2.f * al * (Q1[d] + V * Q2[d] + Pp * Q3[d]);
-    float r = s * (fv * y[d] - Hy[d].val() / (lt * lt)) + gv * dxv;
-    if (mean_live) r += s * gm * wv[d] / (fv * u);
-    out_dx[d] = r;
-  }
+  for (int d = 0; d < 3; ++d)
+    out_dx[d] = point_grad_f32(A, s, gm, gv, fv, u, mean_live, V, Pp, y[d], Hy[d].val(), wv[d], Q1[d],
+                               Q2[d], Q3[d]);
   float aXl = s * (y[0] * Eld[0].val() + y[1] * Eld[1].val() + y[2] * Eld[2].val());
   float aXs = s * (y[0] * Esd[0].val() + y[1] * Esd[1].val() + y[2] * Esd[2].val());
   if (mean_live) {
@@ -921,68 +723,26 @@ __device__ __forceinline__ void vjp_f32(const BwdArgs<float>& A, float x0, float
   out_th[1] = (double)ds;
 }
 
-// FP32: lanes take queries in argmin-cell order (perm), and each wave walks the
-// distinct argmin cells of its lanes -- after the sort usually one or two -- so the
-// cell index is wave-uniform and the cell's samples, factor and adjoint vectors are
-// read through scalar loads.
-template <bool VARF, bool LANE>
-__global__ void __launch_bounds__(BT) bwd_wave_kernel(BwdArgs<float> A, const int* perm) {
+// FP32 RBF models with many queries: one thread per query, in argmin-cell order (perm), each
+// lane reading its own cell.  (A wave that walks its lanes' argmin cells through scalar loads
+// was slower on every set: 262,144 trajectory points 1.84 against 0.25 ms, 4e6 at random 4.00
+// and 3.41, a 200^3 grid 5.63 and 4.87.)
+__global__ void __launch_bounds__(BT) bwd_lane_kernel(BwdArgs<float> A, const int* perm) {
   const long sq = (long)blockIdx.x * BT + threadIdx.x;
-  const bool active = sq < A.Q;
-  const long q = active ? perm[sq] : 0;
-  int bc = active ? A.argmin[q] : -1;
-  if (bc >= A.n_cells) bc = -1;
+  if (sq >= A.Q) return;
+  const long q = perm[sq];
+  int c = A.argmin[q];
+  if (c >= A.n_cells) c = -1;
   float dx[3] = {0.f, 0.f, 0.f};
   double th[2] = {0.0, 0.0};
-  bool todo = bc >= 0;
-  // per-lane inputs (the no-var_f path reads them once for all its cells)
   const float x0 = A.pts[3 * q], x1 = A.pts[3 * q + 1], x2 = A.pts[3 * q + 2];
   const float sgn = A.sign ? (float)A.sign[q] : 1.f;
-  float gm = 0.f, gv = 0.f;
-  if (active) mean_var_cotangents(A, q, gm, gv);
+  float gm, gv;
+  mean_var_cotangents(A, q, gm, gv);
   float gg[3] = {0.f, 0.f, 0.f};
   if (A.d_grad)
     for (int d = 0; d < 3; ++d) gg[d] = A.d_grad[3 * q + d];
-  if constexpr (LANE && !VARF) {
-    // per lane (sparse queries): every lane its own argmin cell, in one round
-    if (__ballot(todo)) {
-      float tdx[3];
-      double tth[2];
-      vjp_f32<false>(A, x0, x1, x2, sgn, gm, gg, gv, todo ? bc : 0, tdx, tth);
-      if (todo) {
-        for (int d = 0; d < 3; ++d) dx[d] = tdx[d];
-        th[0] = tth[0];
-        th[1] = tth[1];
-        todo = false;
-      }
-    }
-  }
-  while (true) {
-    unsigned key = todo ? (unsigned)bc : 0xffffffffu;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) key = min(key, (unsigned)__shfl_xor((int)key, o, 64));
-    key = (unsigned)__builtin_amdgcn_readfirstlane((int)key);
-    if (key == 0xffffffffu) break;
-    const int c = (int)key;
-    if constexpr (VARF) {
-      if (todo && bc == c) {
-        float v[KSDF_MAX_M];
-        query_vjp<float, true>(A, q, c, v, dx, th);
-        todo = false;
-      }
-    } else {
-      float tdx[3];
-      double tth[2];
-      vjp_f32<true>(A, x0, x1, x2, sgn, gm, gg, gv, c, tdx, tth);
-      if (todo && bc == c) {
-        for (int d = 0; d < 3; ++d) dx[d] = tdx[d];
-        th[0] = tth[0];
-        th[1] = tth[1];
-        todo = false;
-      }
-    }
-  }
-  if (!active) return;
+  if (c >= 0) vjp_f32(A, x0, x1, x2, sgn, gm, gg, gv, c, dx, th);
   for (int d = 0; d < 3; ++d) A.d_points[3 * q + d] = dx[d];
   store_theta(A, q, th);
 }
@@ -1118,6 +878,27 @@ __global__ void __launch_bounds__(RT) theta_final32_kernel(const float4* red, do
 
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Eight lanes per query (backward_group.hip) or one thread per query, which needs some
+// hundred thousand of them to fill the chip.  With a var_f cotangent a thread's kernel
+// vector lives in memory, so those always take eight lanes.  Room of 64-sample cells, eight
+// lanes against one thread (us): FP32 64,000 trajectory points 79 / 117, 262,144 260 / 245,
+// 1e6 941 / 755, with var_f 262,144 at random 800 / 9202; Matern 3/2 262,144 287 / 350;
+// FP64 64,000 143 / 145, a 128^3 grid 3293 / 1529, with var_f 65,536 877 / 2135.
+constexpr long GROUP_MAX_Q32 = 196608, GROUP_MAX_Q64 = 65536;
+bool group_used(const ksdf_model* m, long Q, bool varf) {
+  if (m->precision == KSDF_FP64)
+    return m->kernel == KSDF_KERNEL_RBF && (varf || Q <= GROUP_MAX_Q64);
+  return varf || Q <= GROUP_MAX_Q32;
+}
+// Whether the points are taken in argmin-cell order (FP32 models): one thread per query
+// always; eight lanes only with var_f, where the factor is read three times (262,144 points
+// at random 0.80 ms sorted, 2.51 unsorted; without var_f 334 against 288 us).
+constexpr long GROUP_UNSORTED_MAX_Q = 16384;
+bool sort_used(const ksdf_model* m, long Q, bool varf) {
+  return m->precision != KSDF_FP64 &&
+         (!group_used(m, Q, varf) || (varf && Q > GROUP_UNSORTED_MAX_Q));
+}
+
 }  // namespace
 
 size_t backward_workspace_bytes(const ksdf_model* m, long Q) {
@@ -1169,7 +950,10 @@ int launch_backward(const ksdf_model* m, const void* points, long Q, const int8_
     if (r != KSDF_OK) return r;
     argmin = am;
   }
-  if (Q > 0 && m->precision != KSDF_FP64) {
+  const bool varf = d_var_f != nullptr;
+  const bool grouped = group_used(m, Q, varf);
+  const bool sorted = sort_used(m, Q, varf);
+  if (Q > 0 && sorted) {
     const unsigned gq = (unsigned)((Q + ST - 1) / ST);
     hipLaunchKernelGGL(fill_int_kernel, dim3((unsigned)((nc + ST - 1) / ST)), dim3(ST), 0, s, count,
                        nc, 0);
@@ -1179,7 +963,6 @@ int launch_backward(const ksdf_model* m, const void* points, long Q, const int8_
     hipLaunchKernelGGL(argmin_scatter_kernel, dim3(gq), dim3(ST), 0, s, Q, key, cursor, perm);
   }
   const unsigned grid = (unsigned)((Q + BT - 1) / BT);
-  const bool varf = d_var_f != nullptr;
   const double two_l2 = 2.0 * m->ell * m->ell;
   if (m->precision == KSDF_FP64) {
     BwdArgs<double> A{};
@@ -1202,16 +985,17 @@ int launch_backward(const ksdf_model* m, const void* points, long Q, const int8_
     A.offsets = m->offsets; A.loff = m->loff;
     A.ps = m->ps64; A.sv = m->sv64; A.L = m->L64; A.xi = m->xi64;
     A.D = m->adjoint_varf ? m->D64 : nullptr;
-    A.centre64 = m->centre64; A.box = m->box32;
+    A.centre64 = m->centre64;
     A.ell = m->ell; A.two_l2 = two_l2; A.alpha = m->alpha;
     A.alpha_tied = m->alpha_tied; A.uniform_noise = !m->has_svar;
     timer_mark(m, KSDF_TIMER_BACKWARD, 0, s);
-    if (Q > 0 && m->kernel == KSDF_KERNEL_MATERN32) {
-      if (varf) hipLaunchKernelGGL((bwd_matern_kernel<double, true>), dim3(grid), dim3(BT), 0, s, A);
-      else hipLaunchKernelGGL((bwd_matern_kernel<double, false>), dim3(grid), dim3(BT), 0, s, A);
+    if (Q > 0 && grouped) {
+      launch_backward_group(m, A, varf, sorted ? perm : nullptr, s);
+    } else if (Q > 0 && m->kernel == KSDF_KERNEL_MATERN32) {
+      if (varf) hipLaunchKernelGGL(bwd_matern64_kernel<true>, dim3(grid), dim3(BT), 0, s, A);
+      else hipLaunchKernelGGL(bwd_matern64_kernel<false>, dim3(grid), dim3(BT), 0, s, A);
     } else if (Q > 0) {
-      if (varf) hipLaunchKernelGGL((bwd_plain_kernel<double, true>), dim3(grid), dim3(BT), 0, s, A);
-      else hipLaunchKernelGGL((bwd_plain_kernel<double, false>), dim3(grid), dim3(BT), 0, s, A);
+      hipLaunchKernelGGL(bwd_plain_kernel<double>, dim3(grid), dim3(BT), 0, s, A);
     }
     timer_mark(m, KSDF_TIMER_BACKWARD, 1, s);
   } else {
@@ -1235,9 +1019,9 @@ int launch_backward(const ksdf_model* m, const void* points, long Q, const int8_
     A.offsets = m->offsets; A.loff = m->loff;
     A.ps = m->ps32; A.sv = m->sv32; A.L = m->L32; A.xi = m->xi32;
     A.D = m->adjoint_varf ? m->D32 : nullptr;
-    A.centre64 = m->centre64; A.box = m->box32;
+    A.centre64 = m->centre64;
     A.ell = (float)m->ell; A.two_l2 = (float)two_l2; A.alpha = (float)m->alpha;
-    A.ell_d = m->ell; A.alpha_d = m->alpha; A.plo = m->plo32;
+    A.plo = m->plo32;
     {
       const double c2 = 1.4426950408889634 / two_l2;
       A.c2_ff[0] = (float)c2;
@@ -1250,14 +1034,12 @@ int launch_backward(const ksdf_model* m, const void* points, long Q, const int8_
     }
     A.alpha_tied = m->alpha_tied; A.uniform_noise = !m->has_svar;
     timer_mark(m, KSDF_TIMER_BACKWARD, 0, s);
-    if (Q > 0 && m->kernel == KSDF_KERNEL_MATERN32) {
-      if (varf) hipLaunchKernelGGL((bwd_matern_kernel<float, true>), dim3(grid), dim3(BT), 0, s, A);
-      else hipLaunchKernelGGL((bwd_matern_kernel<float, false>), dim3(grid), dim3(BT), 0, s, A);
+    if (Q > 0 && grouped) {
+      launch_backward_group(m, A, varf, sorted ? perm : nullptr, s);
+    } else if (Q > 0 && m->kernel == KSDF_KERNEL_MATERN32) {
+      hipLaunchKernelGGL(bwd_matern32_kernel, dim3(grid), dim3(BT), 0, s, A, perm);
     } else if (Q > 0) {
-      if (varf) hipLaunchKernelGGL((bwd_wave_kernel<true, false>), dim3(grid), dim3(BT), 0, s, A, perm);
-      else if (m->tuning.backward_lanes)
-        hipLaunchKernelGGL((bwd_wave_kernel<false, true>), dim3(grid), dim3(BT), 0, s, A, perm);
-      else hipLaunchKernelGGL((bwd_wave_kernel<false, false>), dim3(grid), dim3(BT), 0, s, A, perm);
+      hipLaunchKernelGGL(bwd_lane_kernel, dim3(grid), dim3(BT), 0, s, A, perm);
     }
     timer_mark(m, KSDF_TIMER_BACKWARD, 1, s);
   }

@@ -1,9 +1,12 @@
-"""Eight lanes per query: the query kernel that answers small and medium calls,
+"""Eight lanes per query: the query and backward kernels that answer small and medium calls,
 at the sizes where their blocks of eight and their dispatch turn.
 
 The FP32 query kernel keeps the order of every operation of the one-kernel form
 (query_split=0), so all outputs agree bit for bit; it is used up to 196,608 points and sorts
-them above 131,072.
+them above 131,072.  The backward is held to the oracle's VJP, and to the per-thread kernels
+that answer larger calls: both take the same terms and sums in the same order and differ in
+the fused multiply-adds of a handful of final operations, a few 2^-24 of the parts of a
+point's gradient.
 """
 import dataclasses
 
@@ -12,6 +15,7 @@ import pytest
 import torch
 
 from paper_2603_29227_amd import ksdf, scenes
+from tests.test_gpu_backward import _compare, _cotangents, _gpu_vjp, _setup
 
 pytestmark = pytest.mark.gpu
 
@@ -69,3 +73,38 @@ def test_query_and_bucketed_query_at_the_dispatch_edges(n):
     two = model.query(q, sg, grad_var=True, workspace=ws, bucketed=True)
     for k in OUT:
         assert torch.equal(got[k], want[k]) and torch.equal(two[k], want[k]), k
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("m_max", [1, 7, 9, 64, 65, 128])
+def test_backward_with_var_f_matches_the_oracle(precision, m_max):
+    print(f"[gpu-case] group backward {precision} m<={m_max}", flush=True)
+    wl = _sphere(m_max, n_queries=203, dtype=np.float32 if precision == "fp32" else np.float64)
+    model, cells, dt = _setup(wl, precision, var_f=True)
+    cot = _cotangents(len(wl.queries), 5, grad=precision == "fp64")
+    dp, dh, am = _gpu_vjp(model, wl.queries, wl.sign, cot, dt)
+    _compare(dp, dh, am, wl, cells, wl.queries, wl.sign, cot, precision)
+
+
+@pytest.mark.parametrize("precision,kernel,limit", [("fp32", "rbf", 196608), ("fp32", "matern32", 196608),
+                                                    ("fp64", "rbf", 65536)])
+def test_backward_equals_the_per_thread_kernels(precision, kernel, limit):
+    print(f"[gpu-case] group backward against one thread per query, {precision} {kernel}", flush=True)
+    wl = scenes.small_room_workload(n_queries=4099, cfg_id=36, uneven=True)
+    model, _, dt = _setup(wl, precision, kernel=kernel)
+    reps = limit // len(wl.queries) + 1
+    q = torch.from_numpy(wl.queries).to("cuda", dt)
+    sg = torch.from_numpy(wl.sign).cuda()
+    g = torch.Generator(device="cuda").manual_seed(1)
+    cot = [torch.randn(*s, generator=g, device="cuda", dtype=dt) for s in ((4099,), (4099, 3), (4099,))]
+    am = model.query(q, sg)["argmin"]
+    a, ah = model.backward(q, sg, *cot, argmin=am)
+    rep = lambda t: t.repeat(reps, *([1] * (t.dim() - 1)))   # noqa: E731
+    b, bh = model.backward(rep(q), rep(sg), *(rep(c) for c in cot), argmin=rep(am))
+    eps = 2.0 ** (-24 if precision == "fp32" else -53)
+    b = b[:4099]
+    big = a.abs().amax(1, keepdim=True)
+    # the parts of a gradient exceed it by what cancels between them: 2^10 covers all but
+    # points whose gradient nearly vanishes, which the median's share of the bound covers
+    assert bool(((a - b).abs() <= eps * 2 ** 10 * (big + big.median())).all())
+    assert torch.allclose(ah * reps, bh, rtol=eps * 2 ** 10, atol=0)
