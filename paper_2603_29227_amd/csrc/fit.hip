@@ -91,12 +91,6 @@ void launch_bucket(const FitArgs& A, const int* list, const int* count, int n, h
 
 __global__ void set_int_kernel(int* p, int v) { *p = v; }
 
-__global__ void __launch_bounds__(FIT_THREADS) fit64_kernel(FitArgs A) {
-  __shared__ double smem[FIT64_SMEM_DOUBLES];
-  const int count = A.list ? *A.list_count : A.n_cells;
-  for (int t = blockIdx.x; t < count; t += gridDim.x) fit64_cell(A, A.list ? A.list[t] : t, smem);
-}
-
 // ---- streaming refit (Sec. IV-C, App. G) ----
 
 // Training-queue score of App. G, s = c2 (1 + eta c0), in FP32 with every rounding
@@ -325,7 +319,7 @@ int launch_refit(ksdf_model* m, const void* pts, int dtype, const void* svar, fl
     A.list = sel;
     A.list_count = n_sel;
     A.emit32 = 0;
-    hipLaunchKernelGGL(fit64_kernel, dim3((unsigned)budget), dim3(FIT_THREADS), 0, s, A);
+    launch_fit64(m, A, budget, s);
   } else {
     const int minb = m->tuning.fit_min_bucket;
     hipLaunchKernelGGL(refit_bucket_kernel, dim3(gb), dim3(256), 0, s, sel, n_sel, m->offsets, minb,
@@ -345,8 +339,7 @@ int launch_refit(ksdf_model* m, const void* pts, int dtype, const void* svar, fl
     A.list = m->fb_list;
     A.list_count = m->fb_count;
     A.emit32 = 1;
-    hipLaunchKernelGGL(fit64_kernel, dim3((unsigned)std::min(budget, 2048)), dim3(FIT_THREADS), 0, s,
-                       A);
+    launch_fit64(m, A, std::min(budget, 1024), s);
   }
   if (m->precision != KSDF_FP64) launch_linv(m, s);
   timer_mark(m, KSDF_TIMER_FIT, 1, s);
@@ -384,10 +377,9 @@ int launch_fit(ksdf_model* m, const void* pts, int dtype, const void* svar, uint
   FitArgs A = make_fit_args(m, pts, dtype, svar, user_status);
   if (m->n_cells == 0) return KSDF_OK;
   if (m->precision == KSDF_FP64) {
-    A.list = nullptr;
     A.emit32 = 0;
     timer_mark(m, KSDF_TIMER_FIT, 0, s);
-    hipLaunchKernelGGL(fit64_kernel, dim3(m->n_cells), dim3(FIT_THREADS), 0, s, A);
+    launch_fit64_all(m, A, s);
     timer_mark(m, KSDF_TIMER_FIT, 1, s);
   } else {
     hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(1), 0, s, m->fb_count, 0);
@@ -405,8 +397,7 @@ int launch_fit(ksdf_model* m, const void* pts, int dtype, const void* svar, uint
     A.list = m->fb_list;
     A.list_count = m->fb_count;
     A.emit32 = 1;
-    const int grid = m->n_cells < 2048 ? m->n_cells : 2048;
-    hipLaunchKernelGGL(fit64_kernel, dim3(grid), dim3(FIT_THREADS), 0, s, A);
+    launch_fit64(m, A, std::min(m->n_cells, 1024), s);
     launch_linv(m, s);
     timer_mark(m, KSDF_TIMER_FIT, 1, s);
   }

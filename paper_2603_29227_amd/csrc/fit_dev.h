@@ -6,6 +6,51 @@
 #include "ksdf_internal.h"
 
 namespace ksdf {
+
+// (shared by the translation units that launch them, hence outside the file-local namespace)
+struct FitArgs {
+  const void* pts;
+  int pts_f64;
+  const void* svar;         // per-sample variance (same dtype as pts) or null
+  const int* offsets;
+  const int* samples;
+  const long* loff;
+  const double* centre64;
+  double ell, noise, cond_thr;
+  float noise_ff[2];     // sigma^2, 1/(2 l^2) and 1/l^3 as float-float pairs
+  float inv2l2_ff[2];
+  float inv_l3_ff[2];
+  int kernel;            // KSDF_KERNEL_* (Table I)
+  float mc_ff[2];        // Matern 3/2 rate c = sqrt(3) / l, float-float
+  float mc2_ff[2];       // c^2 and 1 / l, float-float (Matern adjoint)
+  float inv_l_ff[2];
+  int adjoint;           // also prepare the adjoint vectors xi (and D when non-null)
+  float* xi32;           // [nnz+pad,4] (xi_l, xi_s) as float-float: hi_l, hi_s, lo_l, lo_s
+  float* D32;            // packed dA/dl or null
+  double* xi64;
+  double* D64;
+  // FP32 store
+  float* ps32;
+  float* plo32;
+  float* sv32;
+  float* L32;
+  float* box32;
+  float* cond32;
+  int* fb_list;
+  int* fb_count;
+  // FP64 store
+  double* ps64;
+  double* sv64;
+  double* L64;
+  uint8_t* cstatus;
+  uint8_t* user_status;
+  // FP64 kernel: cells to process (null = all cells) and whether to emit the FP32 store
+  const int* list;
+  const int* list_count;
+  int n_cells;
+  int emit32;
+};
+
 namespace {
 
 
@@ -179,48 +224,6 @@ __device__ __forceinline__ double load_coord(const void* pts, int pts_f64, long 
                  : (double)static_cast<const float*>(pts)[3 * s + d];
 }
 
-struct FitArgs {
-  const void* pts;
-  int pts_f64;
-  const void* svar;         // per-sample variance (same dtype as pts) or null
-  const int* offsets;
-  const int* samples;
-  const long* loff;
-  const double* centre64;
-  double ell, noise, cond_thr;
-  float noise_ff[2];     // sigma^2, 1/(2 l^2) and 1/l^3 as float-float pairs
-  float inv2l2_ff[2];
-  float inv_l3_ff[2];
-  int kernel;            // KSDF_KERNEL_* (Table I)
-  float mc_ff[2];        // Matern 3/2 rate c = sqrt(3) / l, float-float
-  float mc2_ff[2];       // c^2 and 1 / l, float-float (Matern adjoint)
-  float inv_l_ff[2];
-  int adjoint;           // also prepare the adjoint vectors xi (and D when non-null)
-  float* xi32;           // [nnz+pad,4] (xi_l, xi_s) as float-float: hi_l, hi_s, lo_l, lo_s
-  float* D32;            // packed dA/dl or null
-  double* xi64;
-  double* D64;
-  // FP32 store
-  float* ps32;
-  float* plo32;
-  float* sv32;
-  float* L32;
-  float* box32;
-  float* cond32;
-  int* fb_list;
-  int* fb_count;
-  // FP64 store
-  double* ps64;
-  double* sv64;
-  double* L64;
-  uint8_t* cstatus;
-  uint8_t* user_status;
-  // FP64 kernel: cells to process (null = all cells) and whether to emit the FP32 store
-  const int* list;
-  const int* list_count;
-  int n_cells;
-  int emit32;
-};
 
 // Block-parallel right-looking Cholesky of packed lower Ap (in place); returns
 // false (uniformly across the block) on a non-positive pivot.
@@ -633,134 +636,14 @@ __device__ bool fit32_cell(const FitArgs& A, int c, float* smem) {
   return need64;
 }
 
-constexpr int FIT64_SMEM_DOUBLES = 6 * MAXM;
+}  // namespace
 
-// Fit one cell in FP64 with the whole block (factor in place in global memory);
-// smem holds FIT64_SMEM_DOUBLES doubles.  emit32 writes the FP32 store.
-__device__ void fit64_cell(const FitArgs& A, int c, double* smem) {
-  double* xs = smem;
-  double* sv = xs + 3 * MAXM;
-  double* a_s = sv + MAXM;
-  double* g_s = a_s + MAXM;
-  {
-    const int b = A.offsets[c], m = A.offsets[c + 1] - b;
-    __syncthreads();
-    for (int i = threadIdx.x; i < m; i += blockDim.x) {
-      const long s = A.samples[b + i];
-      for (int d = 0; d < 3; ++d)
-        xs[3 * i + d] = load_coord<double>(A.pts, A.pts_f64, s, d) - A.centre64[3 * c + d];
-      sv[i] = A.svar ? (A.pts_f64 ? static_cast<const double*>(A.svar)[s]
-                                  : (double)static_cast<const float*>(A.svar)[s])
-                     : A.noise;
-    }
-    __syncthreads();
-    double* Ap = A.L64 + A.loff[c];   // the factor is computed in place in global memory
-    assemble<double>(Ap, xs, sv, m, 1.0 / (2.0 * A.ell * A.ell), A.kernel, std::sqrt(3.0) / A.ell);
-    __threadfence_block();
-    const bool ok = block_cholesky<double>(Ap, m);
-    __threadfence_block();
-    __syncthreads();
-    WVec<double> a;
-    if (threadIdx.x < 64 && ok) {
-      WVec<double> ones, y;
-#pragma unroll
-      for (int s2 = 0; s2 < SLOTS; ++s2) ones.s[s2] = 1.0;
-      wave_forward<double>(Ap, m, ones, y);
-      wave_backward<double>(Ap, m, y, a);
-    }
-    __syncthreads();
-    if (A.adjoint && ok) {
-      // adjoint vectors of the fit in FP64: xi_l = A^{-1} (dA/dl) a, xi_s = A^{-1} a
-      const int lane = threadIdx.x & 63;
-      if (threadIdx.x < 64) {
-#pragma unroll
-        for (int t2 = 0; t2 < SLOTS; ++t2) {
-          const int i = t2 * 64 + lane;
-          if (i < m) a_s[i] = a.s[t2];
-        }
-      }
-      __syncthreads();
-      const double inv2l2 = 1.0 / (2.0 * A.ell * A.ell), il3 = 1.0 / (A.ell * A.ell * A.ell);
-      const bool matern = A.kernel == KSDF_KERNEL_MATERN32;
-      const double mcd = std::sqrt(3.0) / A.ell;
-      // dA_ij/dl without the 1/l^3 (RBF) or 1/l (Matern 3/2) factor
-      auto dkl = [&](double r2) {
-        return matern ? mcd * mcd * r2 * exp(-mcd * sqrt(r2)) : exp(-r2 * inv2l2) * r2;
-      };
-      const double lfac = matern ? 1.0 / A.ell : il3;
-      for (int i = threadIdx.x; i < m; i += blockDim.x) {
-        double acc = 0.0;
-        for (int k = 0; k < m; ++k) {
-          if (k == i) continue;
-          const double dx = xs[3 * i] - xs[3 * k], dy = xs[3 * i + 1] - xs[3 * k + 1],
-                       dz = xs[3 * i + 2] - xs[3 * k + 2];
-          const double r2 = dx * dx + dy * dy + dz * dz;
-          acc += dkl(r2) * a_s[k];
-        }
-        g_s[i] = acc * lfac;
-      }
-      __syncthreads();
-      if (threadIdx.x < 64) {
-        WVec<double> gv, av, y, xl_, xs_;
-#pragma unroll
-        for (int t2 = 0; t2 < SLOTS; ++t2) {
-          const int i = t2 * 64 + lane;
-          gv.s[t2] = i < m ? g_s[i] : 0.0;
-          av.s[t2] = i < m ? a_s[i] : 0.0;
-        }
-        wave_forward<double>(Ap, m, gv, y);
-        wave_backward<double>(Ap, m, y, xl_);
-        wave_forward<double>(Ap, m, av, y);
-        wave_backward<double>(Ap, m, y, xs_);
-#pragma unroll
-        for (int t2 = 0; t2 < SLOTS; ++t2) {
-          const int i = t2 * 64 + lane;
-          if (i < m) {
-            const double xsv = A.svar ? 0.0 : xs_.s[t2];
-            if (A.emit32) {
-              const float hl = (float)xl_.s[t2], hs = (float)xsv;
-              A.xi32[4L * (b + i)] = hl;
-              A.xi32[4L * (b + i) + 1] = hs;
-              A.xi32[4L * (b + i) + 2] = (float)(xl_.s[t2] - (double)hl);
-              A.xi32[4L * (b + i) + 3] = (float)(xsv - (double)hs);
-            } else {
-              A.xi64[2L * (b + i)] = xl_.s[t2];
-              A.xi64[2L * (b + i) + 1] = xsv;
-            }
-          }
-        }
-      }
-      if (A.D32 || A.D64) {
-        for (int e = threadIdx.x; e < m * (m + 1) / 2; e += blockDim.x) {
-          int i = (int)((sqrt(8.0 * (double)e + 1.0) - 1.0) * 0.5);
-          while (i * (i + 1) / 2 > e) --i;
-          while ((i + 1) * (i + 2) / 2 <= e) ++i;
-          const int k = e - i * (i + 1) / 2;
-          const double dx = xs[3 * i] - xs[3 * k], dy = xs[3 * i + 1] - xs[3 * k + 1],
-                       dz = xs[3 * i + 2] - xs[3 * k + 2];
-          const double r2 = dx * dx + dy * dy + dz * dz;
-          const double dv = (i == k) ? 0.0 : dkl(r2) * lfac;
-          if (A.emit32) A.D32[A.loff[c] + e] = (float)dv;
-          else A.D64[A.loff[c] + e] = dv;
-        }
-      }
-      __syncthreads();
-    }
-    if (A.emit32) {
-      write_cell<double, float>(Ap, xs, sv, a, m, ok, A.ps32 + 4L * b, A.sv32 + b,
-                                A.L32 + A.loff[c], A.box32 + 8L * c, A.plo32 + 4L * b);
-    } else {
-      write_cell<double, double>(Ap, xs, sv, a, m, ok, A.ps64 + 4L * b, A.sv64 + b, Ap,
-                                 A.box32 ? A.box32 + 8L * c : nullptr);
-    }
-    if (threadIdx.x == 0) {
-      const uint8_t st = (A.emit32 ? KSDF_C_FP64 : 0) | (ok ? 0 : KSDF_C_FAILED);
-      A.cstatus[c] = st;
-      if (A.user_status) A.user_status[c] = st;
-    }
-  }
-}
+// FP64 fits (fit64.hip): the cells of A.list (A.list_count of them, at most as known to the
+// device; grid: workgroups), or every cell of the model
+void launch_fit64(const ksdf_model* m, const FitArgs& A, int grid, hipStream_t s);
+void launch_fit64_all(const ksdf_model* m, FitArgs A, hipStream_t s);
 
+namespace {
 
 // Arguments of a fit of model m (the FP64 refit list fields are set by the launch).
 inline FitArgs make_fit_args(ksdf_model* m, const void* pts, int dtype, const void* svar,

@@ -12,7 +12,7 @@
 // limit, settable for tests); on expiry the workgroup stops waiting, every query it
 // then answers carries KSDF_Q_FIT_TIMEOUT, and the model's flag in its store records
 // the expiry for ksdf_model_check.
-#include "fit_dev.h"
+#include "fit64_dev.h"
 #include "query_dev.h"
 
 namespace ksdf {
@@ -111,7 +111,7 @@ __global__ void fused_reset_kernel(int* ctl) {
 template <int KM, int MB, int MF>
 int launch_fused_t(ksdf_model* m, FitArgs& F, FastArgs& A, FusedCtl& C, hipStream_t s) {
   const size_t smem = std::max(fit32_smem_floats<MF>() * sizeof(float),
-                               FIT64_SMEM_DOUBLES * sizeof(double));
+                               fit64_smem_doubles(MF) * sizeof(double));
   auto kern = fused_kernel<KM, MB, MF>;
   // attribute and occupancy are taken once per kernel, so that a launch made under
   // stream capture issues no device-attribute calls
