@@ -4,14 +4,12 @@
 namespace ksdf {
 namespace {
 
-constexpr int FIT64_THREADS = 256;
-
 // MB: the largest m of the launch, which sizes the factor in LDS
 template <int MB>
 __global__ void __launch_bounds__(FIT64_THREADS) fit64_kernel(FitArgs A, int n) {
   __shared__ double smem[fit64_smem_doubles(MB)];
   const int count = A.list_count ? *A.list_count : n;
-  for (int t = blockIdx.x; t < count; t += gridDim.x) fit64_cell(A, A.list[t], smem);
+  for (int t = blockIdx.x; t < count; t += gridDim.x) fit64_cell<MB>(A, A.list[t], smem);
 }
 
 }  // namespace

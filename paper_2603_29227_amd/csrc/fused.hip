@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(FT) fused_kernel(FitArgs F, FastArgs Q, FusedC
       if constexpr (MF >= 128) need64 = fit32_task<128>(F, c, smem);
       else need64 = true;
     }
-    if (need64) fit64_cell(F, c, reinterpret_cast<double*>(smem));
+    if (need64) fit64_cell<MF>(F, c, reinterpret_cast<double*>(smem));
     __threadfence();
     __syncthreads();
     if (threadIdx.x == 0)
