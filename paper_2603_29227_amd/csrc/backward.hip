@@ -754,13 +754,16 @@ __global__ void fill_int_kernel(int* p, long n, int v) {
   if (i < n) p[i] = v;
 }
 __global__ void __launch_bounds__(ST) argmin_count_kernel(const int* argmin, long Q, int n_cells,
-                                                          int* key, int* count) {
+                                                          int* key, int* rank, int* count) {
   const long q = (long)blockIdx.x * ST + threadIdx.x;
   const bool valid = q < Q;
   int c = valid ? argmin[q] : n_cells;
   if (c < 0 || c >= n_cells) c = n_cells;
-  if (valid) key[q] = c;
-  wave_count(count, c, valid);   // consecutive queries mostly share their cell
+  const int r = wave_slot(count, c, valid);   // consecutive queries mostly share their cell
+  if (valid) {
+    key[q] = c;
+    rank[q] = r;
+  }
 }
 // exclusive scan of count[0..n) into start (one block; n is a cell count)
 __global__ void __launch_bounds__(1024) scan_counts_kernel(const int* count, int n, int* start) {
@@ -784,12 +787,10 @@ __global__ void __launch_bounds__(1024) scan_counts_kernel(const int* count, int
     run += count[i];
   }
 }
-__global__ void __launch_bounds__(ST) argmin_scatter_kernel(long Q, const int* key, int* cursor,
-                                                            int* perm) {
+__global__ void __launch_bounds__(ST) argmin_scatter_kernel(long Q, const int* key, const int* rank,
+                                                            const int* start, int* perm) {
   const long q = (long)blockIdx.x * ST + threadIdx.x;
-  const bool valid = q < Q;
-  const int pos = wave_slot(cursor, valid ? key[q] : 0, valid);
-  if (valid) perm[pos] = (int)q;
+  if (q < Q) perm[start[key[q]] + rank[q]] = (int)q;
 }
 
 // Deterministic FP64 reduction of the per-query hyperparameter partials: RB blocks each
@@ -955,12 +956,13 @@ int launch_backward(const ksdf_model* m, const void* points, long Q, const int8_
   const bool sorted = sort_used(m, Q, varf);
   if (Q > 0 && sorted) {
     const unsigned gq = (unsigned)((Q + ST - 1) / ST);
+    int* rank = reinterpret_cast<int*>(part);   // the partials are written after the sort
     hipLaunchKernelGGL(fill_int_kernel, dim3((unsigned)((nc + ST - 1) / ST)), dim3(ST), 0, s, count,
                        nc, 0);
     hipLaunchKernelGGL(argmin_count_kernel, dim3(gq), dim3(ST), 0, s, argmin, Q, m->n_cells, key,
-                       count);
+                       rank, count);
     hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, s, count, (int)nc, cursor);
-    hipLaunchKernelGGL(argmin_scatter_kernel, dim3(gq), dim3(ST), 0, s, Q, key, cursor, perm);
+    hipLaunchKernelGGL(argmin_scatter_kernel, dim3(gq), dim3(ST), 0, s, Q, key, rank, cursor, perm);
   }
   const unsigned grid = (unsigned)((Q + BT - 1) / BT);
   const double two_l2 = 2.0 * m->ell * m->ell;

@@ -2,6 +2,7 @@
 // persistent fused fit+query kernel.  See query_fast.hip for the method.
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 
 #include "ff.h"
@@ -24,6 +25,7 @@ struct FastArgs {
   int* argmin;
   uint8_t* qst;
   const int* perm;
+  int* rank;   // split query: each record's place among those of its argmin bin
   // models with cells of more than 64 samples: the split query groups its records by
   // this rank (cells of up to 64 samples first) so that its second kernel runs in two
   // launches sized for 64 and 128 samples; null otherwise (records grouped by cell id)
@@ -1290,16 +1292,60 @@ __global__ void __launch_bounds__(SCAN_T) scan_apply_kernel(const int* in, long 
   }
 }
 
-// bucketing granularity (sub-boxes per box edge): the tuned value, else the finest
-// that keeps the bin count near 8M
-int sub_of(const ksdf_model* m) {
+// exclusive scan of up to SCAN_SMALL counts in one block
+constexpr int SCAN_SMALL = 1024 * SCAN_PER;
+__global__ void __launch_bounds__(1024) scan_small_kernel(const int* in, int n, int* out) {
+  __shared__ int wsum[16];
+  const int base = threadIdx.x * SCAN_PER, lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+  int v[SCAN_PER];
+  int s = 0;
+#pragma unroll
+  for (int j = 0; j < SCAN_PER; ++j) {
+    v[j] = base + j < n ? in[base + j] : 0;
+    s += v[j];
+  }
+  int t = s;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(t, o, 64);
+    if (lane >= o) t += u;
+  }
+  if (lane == 63) wsum[wave] = t;
+  __syncthreads();
+  int run = t - s;
+  for (int w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll
+  for (int j = 0; j < SCAN_PER; ++j) {
+    if (base + j < n) out[base + j] = run;
+    run += v[j];
+  }
+}
+
+// start <- exclusive scan of count (n <= SCAN_TILE^2; tsum: scratch of one int per tile)
+inline void launch_scan(const int* count, long n, int* tsum, int* start, hipStream_t s) {
+  if (n <= SCAN_SMALL) {
+    hipLaunchKernelGGL(scan_small_kernel, dim3(1), dim3(1024), 0, s, count, (int)n, start);
+    return;
+  }
+  const long tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
+  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)tiles), dim3(SCAN_T), 0, s, count, n, tsum);
+  hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(SCAN_T), 0, s, tsum, (int)tiles);
+  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)tiles), dim3(SCAN_T), 0, s, count, n, tsum, start);
+}
+
+// bucketing granularity (sub-boxes per box edge): the tuned value, else the finest that
+// keeps the bin count near 8M and, for Q points, at one bin a point (finer bins order the
+// points no better and cost their clearing and scan: 30 us for the room's 1.8M)
+int sub_of(const ksdf_model* m, long Q = 8L << 20) {
   const long nb = m->index.n_boxes;
   const int t = m->tuning.query_sub;
   if ((t == 1 || t == 2 || t == 4) && nb * t * t * t <= (16L << 20)) return t;
-  return nb * 64 <= (8L << 20) ? 4 : (nb * 8 <= (8L << 20) ? 2 : 1);
+  const long most = std::min(Q, 8L << 20);
+  return nb * 64 <= most ? 4 : (nb * 8 <= most ? 2 : 1);
 }
-long n_bins_of(const ksdf_model* m) {
-  const long s = sub_of(m);
+// bins of a query of Q points; without Q, the most of any (which sizes the workspace)
+long n_bins_of(const ksdf_model* m, long Q = 8L << 20) {
+  const long s = sub_of(m, Q);
   return m->index.n_boxes * s * s * s + 1;
 }
 
@@ -1339,7 +1385,7 @@ inline FastArgs make_fast_args(const ksdf_model* m, const void* points, long Q, 
     A.dims[d] = m->index.dims[d];
   }
   A.inv_h = (float)(1.0 / m->h);
-  A.sub = sub_of(m);
+  A.sub = sub_of(m, Q);
   A.n_boxes = m->index.n_boxes;
   A.box_off = m->index.box_off;
   A.box_rank = m->index.box_rank;

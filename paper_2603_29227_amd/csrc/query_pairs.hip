@@ -135,8 +135,11 @@ __global__ void __launch_bounds__(PT) pair_fuse_kernel(FastArgs A, const int* ca
   o.bc = bc;
   o.bref = bref;
   o.flags = (outside ? 1 : 0) | (active ? 2 : 0);
-  if (active) rec[sq] = pack_p1(o);
-  wave_count(count, bc < 0 ? A.n_cells : (A.p2rank ? A.p2rank[bc] : bc), active);
+  const int slot = wave_slot(count, bc < 0 ? A.n_cells : (A.p2rank ? A.p2rank[bc] : bc), active);
+  if (active) {
+    rec[sq] = pack_p1(o);
+    A.rank[sq] = slot;
+  }
 }
 
 int km_of(const ksdf_model* m) { return m->k_fuse <= 8 ? 8 : 16; }
@@ -180,10 +183,7 @@ void launch_pass1_pairs(const ksdf_model* m, const FastArgs& A, P1Rec* rec, int*
   hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, pcount, nc, 0);
   if (KM == 8) hipLaunchKernelGGL((pair_cand_kernel<8>), dim3(gq), dim3(PT), 0, s, A, cand, pcount);
   else hipLaunchKernelGGL((pair_cand_kernel<16>), dim3(gq), dim3(PT), 0, s, A, cand, pcount);
-  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)tiles), dim3(SCAN_T), 0, s, pcount, nc, ptsum);
-  hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(SCAN_T), 0, s, ptsum, (int)tiles);
-  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)tiles), dim3(SCAN_T), 0, s, pcount, nc, ptsum,
-                     pcursor);
+  launch_scan(pcount, nc, ptsum, pcursor, s);
   // the scan's entry n_cells (no pair has that key) stays the total through the scatter
   const int* ptotal = pcursor + m->n_cells;
   if (KM == 8) {

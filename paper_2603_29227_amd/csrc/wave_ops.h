@@ -37,7 +37,7 @@ __device__ __forceinline__ long xcd_block(long n) {
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + k;
 }
 
-// Wave-aggregated counting-sort steps over small integer keys: the lanes that share
+// Wave-aggregated counting-sort steps over integer keys: the lanes that share
 // a key take one atomic between them (the lowest lane issues it).
 __device__ __forceinline__ void wave_count(int* count, int key, bool valid) {
   unsigned long long pending = __ballot(valid);
@@ -50,22 +50,29 @@ __device__ __forceinline__ void wave_count(int* count, int key, bool valid) {
     pending &= ~mask;
   }
 }
-// position of each valid lane in its key's range (cursor: running start per key)
-__device__ __forceinline__ int wave_slot(int* cursor, int key, bool valid) {
+// The same count, and each valid lane's place among the entries of its key (in no set order).
+// The lanes that share a key are found first, without memory, and the lowest of each then
+// issues its atomic in one instruction, so that a wave of unlike keys waits once (30 us a
+// kernel for 64 of them one after the other).
+__device__ __forceinline__ int wave_slot(int* count, int key, bool valid) {
   unsigned long long pending = __ballot(valid);
   const int lane = threadIdx.x & 63;
-  int pos = -1;
+  int leader = lane, before = 0, n = 0;
   while (pending) {
-    const int leader = __ffsll((long long)pending) - 1;
-    const int k = __builtin_amdgcn_readlane(key, leader);
+    const int l = __ffsll((long long)pending) - 1;
+    const int k = __builtin_amdgcn_readlane(key, l);
     const unsigned long long mask = __ballot(valid && key == k);
-    int base = 0;
-    if (lane == leader) base = atomicAdd(cursor + k, (int)__popcll(mask));
-    base = __builtin_amdgcn_readlane(base, leader);
-    if (valid && key == k) pos = base + (int)__popcll(mask & ((1ull << lane) - 1ull));
+    if (valid && key == k) {
+      leader = l;
+      before = (int)__popcll(mask & ((1ull << lane) - 1ull));
+      n = (int)__popcll(mask);
+    }
     pending &= ~mask;
   }
-  return pos;
+  int base = 0;
+  if (valid && leader == lane) base = atomicAdd(count + key, n);
+  base = __shfl(base, leader, 64);
+  return valid ? base + before : -1;
 }
 
 }  // namespace
