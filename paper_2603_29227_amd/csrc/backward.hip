@@ -877,6 +877,32 @@ __global__ void __launch_bounds__(RT) theta_final32_kernel(const float4* red, do
   }
 }
 
+// Both steps in one block, for few points
+constexpr long THETA_ONE_BLOCK_Q = 4096;
+__global__ void __launch_bounds__(RT) theta_small32_kernel(const float2* part, int Q, double* out) {
+  ff a{0.f, 0.f}, b{0.f, 0.f};
+  for (int i = threadIdx.x; i < Q; i += RT) {
+    const float2 v = part[i];
+    a = ff_add(a, ff{v.x, 0.f});
+    b = ff_add(b, ff{v.y, 0.f});
+  }
+  __shared__ float4 r;
+  block_sum2_ff(a, b, &r);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    out[0] = (double)r.x + (double)r.y;
+    out[1] = (double)r.z + (double)r.w;
+  }
+}
+__global__ void __launch_bounds__(RT) theta_small_kernel(const double* part, int Q, double* out) {
+  double a = 0.0, b = 0.0;
+  for (int i = threadIdx.x; i < Q; i += RT) {
+    a += part[2 * i];
+    b += part[2 * i + 1];
+  }
+  block_sum2(a, b, out);
+}
+
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Eight lanes per query (backward_group.hip) or one thread per query, which needs some
@@ -1045,7 +1071,13 @@ int launch_backward(const ksdf_model* m, const void* points, long Q, const int8_
     }
     timer_mark(m, KSDF_TIMER_BACKWARD, 1, s);
   }
-  if (m->precision == KSDF_FP64) {
+  if (Q <= THETA_ONE_BLOCK_Q) {
+    if (m->precision == KSDF_FP64)
+      hipLaunchKernelGGL(theta_small_kernel, dim3(1), dim3(RT), 0, s, part, (int)Q, d_hyper);
+    else
+      hipLaunchKernelGGL(theta_small32_kernel, dim3(1), dim3(RT), 0, s,
+                         reinterpret_cast<const float2*>(part), (int)Q, d_hyper);
+  } else if (m->precision == KSDF_FP64) {
     hipLaunchKernelGGL(theta_partial_kernel, dim3(RB), dim3(RT), 0, s, part, Q, red);
     hipLaunchKernelGGL(theta_final_kernel, dim3(1), dim3(RT), 0, s, red, d_hyper);
   } else {

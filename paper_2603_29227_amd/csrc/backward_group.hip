@@ -15,10 +15,10 @@
 namespace ksdf {
 namespace {
 
-template <class T, int ROWS>
+template <class T, int ROWS, bool VARF>
 struct BwdGroupLds {
-  alignas(16) T t[ROWS * GT_STRIDE];    // terms of 8 samples x 8 queries, by kind
-  alignas(16) T k[GQ * GK_STRIDE];      // k, then L^{-1} k, then A^{-1} k
+  alignas(16) T t[ROWS * GT_STRIDE];            // terms of 8 samples x 8 queries, by kind
+  alignas(16) T k[VARF ? GQ * GK_STRIDE : 4];   // k, then L^{-1} k, then A^{-1} k
 };
 
 // v^T D v for the packed strict lower triangle D (twice the lower part), v in LDS
@@ -63,7 +63,7 @@ __device__ __forceinline__ T group_fmin(T d) {
 // query_vjp (RBF; FP64 models, and FP32 models with a var_f cotangent)
 template <class T, bool VARF>
 __global__ void __launch_bounds__(64) bwd_group_kernel(BwdArgs<T> A, const int* perm) {
-  __shared__ BwdGroupLds<T, 17> S;
+  __shared__ BwdGroupLds<T, 17, VARF> S;
   const int lane = threadIdx.x & 63, g = lane & (GL - 1);
   const long sq = xcd_block(gridDim.x) * GQ + lane / GL;
   const bool active = sq < A.Q;
@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(64) bwd_group_kernel(BwdArgs<T> A, const int* 
     const T l0 = x0 - (T)cc[0], l1 = x1 - (T)cc[1], l2 = x2 - (T)cc[2];
     const T inv2l2 = T(1) / A.two_l2;
     T* row = S.t + lane;
-    T* k = S.k + lane / GL * GK_STRIDE;
+    T* k = S.k + (VARF ? lane / GL * GK_STRIDE : 0);
     auto put = [&](int r, T v) { row[r * GT_STRIDE] = v; };
     // scaling reference: the exact nearest sample
     T d2 = (T)INFINITY;
@@ -294,7 +294,7 @@ template <bool MAT, bool VARF>
 __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, const int* perm) {
   static_assert(MAT || !VARF, "the RBF's var_f cotangent runs in bwd_group_kernel");
   // rows 0..15 compensated sums, 16.. the factors of the plain ones
-  __shared__ BwdGroupLds<float, 28> S;
+  __shared__ BwdGroupLds<float, 28, VARF> S;
   const int lane = threadIdx.x & 63, g = lane & (GL - 1);
   const long sq = xcd_block(gridDim.x) * GQ + lane / GL;
   const bool active = sq < A.Q;
@@ -324,10 +324,9 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
     const ff ly = ff_two_sum(A.pts[3 * q + 1], -(float)A.centre64[3L * c + 1]);
     const ff lz = ff_two_sum(A.pts[3 * q + 2], -(float)A.centre64[3L * c + 2]);
     float* row = S.t + lane;
-    float* k = S.k + lane / GL * GK_STRIDE;
+    float* k = S.k + (VARF ? lane / GL * GK_STRIDE : 0);
     auto put = [&](int r, float v) { row[r * GT_STRIDE] = v; };
-    auto load = [&](int i, float di[3], ff& z2, float& pa) {
-      const float4 h = P4[b + i], lo = PL[b + i];
+    auto unpack = [&](float4 h, float4 lo, float di[3], ff& z2, float& pa) {
       const ff dx = ff_sub_lean(lx.hi, lx.lo, h.x, lo.x);
       const ff dy = ff_sub_lean(ly.hi, ly.lo, h.y, lo.y);
       const ff dz = ff_sub_lean(lz.hi, lz.lo, h.z, lo.z);
@@ -337,6 +336,18 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
       z2 = ff_norm2_lean(dx, dy, dz);
       pa = h.w + lo.w;
     };
+    // f(i, sample's high and low parts) for the lane's sample i of each eight, the next
+    // ones' loads in flight (i past the last repeats it)
+    auto each = [&](auto&& f) {
+      float4 h = P4[b + min(g, m - 1)], lo = PL[b + min(g, m - 1)];
+      for (int i0 = 0; i0 < m; i0 += GL) {
+        const float4 ch = h, cl = lo;
+        const int j = b + min(i0 + GL + g, m - 1);
+        h = P4[j];
+        lo = PL[j];
+        f(i0 + g, ch, cl);
+      }
+    };
     // 2^-t for a float-pair t >= 0
     auto exp2n = [&](ff t) {
       const float n = floorf(t.hi);
@@ -344,12 +355,12 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
       return ldexpf(e, -(int)n);
     };
     ff d2f{INFINITY, 0.f};
-    for (int i = g; i < m; i += GL) {
+    each([&](int, float4 h, float4 lo) {
       float di[3], pa;
       ff z2;
-      load(i, di, z2, pa);
+      unpack(h, lo, di, z2, pa);
       if (z2.hi < d2f.hi || (z2.hi == d2f.hi && z2.lo < d2f.lo)) d2f = z2;
-    }
+    });
     auto fmin2 = [&](float oh, float ol) {
       if (oh < d2f.hi || (oh == d2f.hi && ol < d2f.lo)) d2f = ff{oh, ol};
     };
@@ -361,10 +372,10 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
     const float zmin = MAT ? zminf.hi + zminf.lo : sqrtf(d2);
     // the terms of one sample: e (scaled kernel factor), z, t = z - zmin, and for the
     // Matern kernel z as a float pair
-    auto sample = [&](int i, bool in, float di[3], float& pa, float& z2, float& z, float& t, float& e,
-                      ff& zf) {
+    auto sample = [&](float4 h, float4 lo, bool in, float di[3], float& pa, float& z2, float& z,
+                      float& t, float& e, ff& zf) {
       ff z2f;
-      load(in ? i : 0, di, z2f, pa);
+      unpack(h, lo, di, z2f, pa);
       z2 = z2f.hi + z2f.lo;
       if constexpr (MAT) {
         zf = ff_sqrt(z2f);
@@ -385,12 +396,11 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
     put(5, 0.f);
     put(6, 0.f);
     put(7, 0.f);
-    for (int i0 = 0; i0 < m; i0 += GL) {
-      const int i = i0 + g;
+    each([&](int i, float4 ph, float4 pl) {
       const bool in = i < m;
       float di[3], pa, z2, z, t, e;
       ff zf;
-      sample(i, in, di, pa, z2, z, t, e, zf);
+      sample(ph, pl, in, di, pa, z2, z, t, e, zf);
       const float ae = pa * e;
       put(0, MAT ? ae * fmaf(mc, z, 1.f) : ae);
       put(1, ae * di[0]);
@@ -409,7 +419,7 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
       group_fma(S.t, lane_entry(lanes8(16, 17, 19, 16, 16, 16, 16, 16)),
                 lane_entry(lanes8(17, 18, 18, 17, 17, 17, 17, 17)), acc);
       wave_lds_sync();
-    }
+    });
     const float sum0 = ca0.val();
     const float fv = group_lane<0>(sum0);
     const float wv[3] = {group_lane<1>(sum0), group_lane<2>(sum0), group_lane<3>(sum0)};
@@ -449,12 +459,11 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
     put(14, 0.f);
     put(15, 0.f);
     put(27, 0.f);
-    for (int i0 = 0; i0 < m; i0 += GL) {
-      const int i = i0 + g;
+    each([&](int i, float4 ph, float4 pl) {
       const bool in = i < m;
       float di[3], pa, z2, z, t, e;
       ff zf;
-      sample(i, in, di, pa, z2, z, t, e, zf);
+      sample(ph, pl, in, di, pa, z2, z, t, e, zf);
       const int j = in ? i : 0;
       const float4 xq = X4[b + j];
       const float svj = A.sv[b + j];
@@ -493,7 +502,7 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
       group_fma(S.t, lane_entry(lanes8(22, 22, 23, 23, 23, 27, 27, 27)),
                 lane_entry(lanes8(25, 26, 24, 25, 26, 27, 27, 27)), a1);
       wave_lds_sync();
-    }
+    });
     const float s0 = cb0.val(), s1 = cb1.val();
     const float Hy[3] = {group_lane<0>(s0), group_lane<1>(s0), group_lane<2>(s0)};
     const float Wz[3] = {group_lane<3>(s0), group_lane<4>(s0), group_lane<5>(s0)};
@@ -509,12 +518,11 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
     float bk[3] = {0.f, 0.f, 0.f}, bkz = 0.f, bb = 0.f, bDb = 0.f;
     if constexpr (VARF) {
       acc = 0.f;
-      for (int i0 = 0; i0 < m; i0 += GL) {
-        const int i = i0 + g;
+      each([&](int i, float4 ph, float4 pl) {
         const bool in = i < m;
         float di[3], pa, z2, z, t, e;
         ff zf;
-        sample(i, in, di, pa, z2, z, t, e, zf);
+        sample(ph, pl, in, di, pa, z2, z, t, e, zf);
         const float vi = in ? k[i] : 0.f;
         put(0, vi * exp2n(ff_mul(zf, mclf)));
         put(1, di[0]);
@@ -526,7 +534,7 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
         group_fma(S.t, lane_entry(lanes8(0, 0, 0, 0, 5, 27, 27, 27)),
                   lane_entry(lanes8(1, 2, 3, 4, 5, 27, 27, 27)), acc);
         wave_lds_sync();
-      }
+      });
       bk[0] = group_lane<0>(acc);
       bk[1] = group_lane<1>(acc);
       bk[2] = group_lane<2>(acc);

@@ -51,6 +51,16 @@ __device__ __forceinline__ double dpp(double v) {
 }
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141;
 
+// group_lane without LDS, for broadcasts on a chain (two moves and a select against the LDS
+// pipe's latency)
+template <int S, class T>
+__device__ __forceinline__ T group_lane_quick(T v) {
+  constexpr int s = S & 3;
+  const T x = dpp<s | s << 2 | s << 4 | s << 6>(v);   // each four lanes' own lane s
+  const T y = dpp<DPP_MIRROR8>(x);
+  return ((threadIdx.x & 4) == 0) == (S < 4) ? x : y;
+}
+
 // the smallest (distance, id) pair of each group
 template <class T>
 __device__ __forceinline__ void group_min(T& d, int& id) {
@@ -117,41 +127,53 @@ __device__ __forceinline__ void load_row8(const double* p, double (&l)[GL]) {
 // place in the group's vector k in LDS; returns |L^{-1} k|^2.  Blocks of eight rows, one per
 // lane: the columns before the block from LDS, then the block's own triangle through the
 // group.  Every entry subtracts its columns in order, as a sequential substitution does.
+// The loads of the next eight columns, and those of the next block's start, are in flight
+// during the current ones' steps.
 template <class T>
 __device__ __forceinline__ T group_forward_subst(T* k, const T* __restrict__ Lc, int m) {
   const int g = threadIdx.x & (GL - 1);
   T vv = T(0);
-  for (int b0 = 0; b0 < m; b0 += GL) {
-    const int i = b0 + g;
-    const bool row = i < m;
-    // lanes past the last row read it too (their results are not used)
-    const int ir = row ? i : m - 1;
+  T ld[GL], l[GL];   // the row's entries in the block (its diagonal the reciprocal); columns
+  // lanes past the last row read it too (their results are not used)
+  auto row_of_block = [&](int b0) { return min(b0 + g, m - 1); };
+  auto load_block = [&](int b0) {
+    const int ir = row_of_block(b0);
     const T* Li = Lc + ir * (ir + 1) / 2;
-    T t = k[ir];
-    T ld[GL];   // the row's entries in the block (its diagonal the reciprocal)
 #pragma unroll
     for (int e = 0; e < GL; ++e) ld[e] = Li[min(b0 + e, ir)];
+    if (b0 > 0) load_row8(Li, l);
+  };
+  if (m > 0) load_block(0);
+  for (int b0 = 0; b0 < m; b0 += GL) {
+    const int i = b0 + g, ir = row_of_block(b0);
+    const T* Li = Lc + ir * (ir + 1) / 2;
+    T t = k[ir];
     for (int j = 0; j < b0; j += GL) {
       const T* kj = static_cast<const T*>(__builtin_assume_aligned(k + j, 16));
-      T l[GL], v[GL];
-      load_row8(Li + j, l);   // j + 7 < b0 <= ir
+      T lc[GL], v[GL];
+#pragma unroll
+      for (int e = 0; e < GL; ++e) lc[e] = l[e];
+      load_row8(Li + min(j + GL, b0 - GL), l);   // b0 - 1 < ir: within the row
 #pragma unroll
       for (int e = 0; e < GL; ++e) v[e] = kj[e];
 #pragma unroll
-      for (int e = 0; e < GL; ++e) t = fma(-l[e], v[e], t);
+      for (int e = 0; e < GL; ++e) t = fma(-lc[e], v[e], t);
     }
-    T rd = T(0), x = T(0);
+    T rd = T(0), x = T(0), lb[GL];
 #pragma unroll
-    for (int e = 0; e < GL; ++e)
+    for (int e = 0; e < GL; ++e) {
+      lb[e] = ld[e];
       if (e == g) rd = ld[e];
+    }
+    if (b0 + GL < m) load_block(b0 + GL);
     static_for<0, GL>([&](auto E) {
       constexpr int e = E;
-      const T xe = group_lane<e>(t * rd);   // row b0 + e is final at this step
+      const T xe = group_lane_quick<e>(t * rd);   // row b0 + e is final at this step
       if (g == e) x = xe;
-      if (g > e) t = fma(-ld[e], xe, t);
+      if (g > e) t = fma(-lb[e], xe, t);
       if (b0 + e < m) vv = fma(xe, xe, vv);
     });
-    if (row) k[i] = x;
+    if (i < m) k[i] = x;
     wave_lds_sync();
   }
   return vv;
@@ -188,7 +210,7 @@ __device__ __forceinline__ void group_backward_subst(T* k, const T* __restrict__
       if (e == g) rd = ld[e];
     static_for<0, GL>([&](auto E) {
       constexpr int e = GL - 1 - E;
-      const T xe = group_lane<e>(t * rd);
+      const T xe = group_lane_quick<e>(t * rd);
       if (g == e) x = xe;
       if (g < e && b0 + e < m) t = fma(-ld[e], xe, t);
     });

@@ -106,11 +106,11 @@ __device__ __forceinline__ void group_candidates(const FastArgs& A, bool active,
   }
 }
 
-// cell_u2_lane with the next four samples' loads in flight during the current four's terms
+// cell_u2_lane with the next eight samples' loads in flight during the current eight's terms
 // (entries past m contribute nothing)
 __device__ __forceinline__ void cell_u2_group(const FastArgs& A, int b, int m, float lx, float ly,
                                               float lz, float& d2ref, float& u2, float& del) {
-  constexpr int C = 4;
+  constexpr int C = 8;
   const float c2 = A.c2;
   float f = 0.f, R = 0.f, RZ = 0.f;
   u2 = INFINITY;
@@ -159,6 +159,59 @@ __device__ __forceinline__ void cell_u2_group(const FastArgs& A, int b, int m, f
   }
 }
 
+// cell_u_matern_lane, the same way
+__device__ __forceinline__ void cell_u_matern_group(const FastArgs& A, int b, int m, float lx, float ly,
+                                                    float lz, float& d2ref, float& u, float& del) {
+  constexpr int C = 8;
+  const float mc = A.mc, mcl = A.mc_l2e;
+  float f = 0.f, R = 0.f, RZ = 0.f;
+  u = INFINITY;
+  del = 0.f;
+  const float4* __restrict__ ps = A.ps + b;
+  for (int pass = 0; pass < 2; ++pass) {
+    const float dref = __builtin_amdgcn_sqrtf(d2ref);
+    float emax = 0.f;
+    f = 0.f;
+    R = 0.f;
+    RZ = 0.f;
+    float4 N[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) N[j] = ps[min(j, m - 1)];
+    for (int i0 = 0; i0 < m; i0 += C) {
+      float4 P[C];
+#pragma unroll
+      for (int j = 0; j < C; ++j) P[j] = N[j];
+#pragma unroll
+      for (int j = 0; j < C; ++j) N[j] = ps[min(i0 + C + j, m - 1)];
+#pragma unroll
+      for (int j = 0; j < C; ++j) {
+        const bool in = i0 + j < m;
+        const float dx = lx - P[j].x, dy = ly - P[j].y, dz = lz - P[j].z;
+        const float z = __builtin_amdgcn_sqrtf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+        const float ex = in ? __builtin_amdgcn_exp2f(mcl * (dref - z)) : 0.f;
+        const float g = fmaf(mc, z, 1.f) * ex;
+        const float ag = fabsf(P[j].w) * g;
+        f = fmaf(P[j].w, g, f);
+        R += ag;
+        RZ = fmaf(ag, z, RZ);
+        emax = fmaxf(emax, ex);
+      }
+    }
+    if (emax >= 0x1p-24f) break;
+    float d2 = INFINITY;
+    for (int i = 0; i < m; ++i) {
+      const float4 p = ps[i];
+      const float dx = lx - p.x, dy = ly - p.y, dz = lz - p.z;
+      d2 = fminf(d2, fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+    }
+    d2ref = d2;
+  }
+  if (f > 0.f) {
+    u = __builtin_amdgcn_sqrtf(d2ref) - LN2 * __log2f(f) / mc;
+    del = EPS32 * (8.f * R + 4.f * mc * RZ) / (mc * f);
+  }
+}
+
 template <int KM, bool MAT>
 __global__ void __launch_bounds__(64) query_group_kernel(FastArgs A) {
   __shared__ GroupLds S;
@@ -193,7 +246,7 @@ __global__ void __launch_bounds__(64) query_group_kernel(FastArgs A) {
       const float lx = qx - ctr.x, ly = qy - ctr.y, lz = qz - ctr.z;
       float d2ref = aabb_d2(bx, lx, ly, lz);
       mlb[s] = cell_lower_bound(A, d2ref, bx[3]);
-      if constexpr (MAT) cell_u_matern_lane(A, b, m, lx, ly, lz, d2ref, mu[s], mdel[s]);
+      if constexpr (MAT) cell_u_matern_group(A, b, m, lx, ly, lz, d2ref, mu[s], mdel[s]);
       else cell_u2_group(A, b, m, lx, ly, lz, d2ref, mu[s], mdel[s]);
       mref[s] = d2ref;
     }
@@ -254,12 +307,16 @@ __global__ void __launch_bounds__(64) query_group_kernel(FastArgs A) {
     const int xr = lane_entry(lanes8(0, 0, 0, 8, 4, 9, 6, 7));
     const int yr = lane_entry(lanes8(1, 2, 3, 4, 5, 10, 5, 5));
     float acc = 0.f;
+    const int last = max(m - 1, 0);
+    float4 Pn = A.ps[b + min(g, last)];
+    float SVn = A.sv[b + min(g, last)];
     for (int i0 = 0; __ballot(i0 < m); i0 += GL) {
       const int i = i0 + g;
       const bool in = i < m;
-      const int j = in ? i : 0;
-      const float4 P = A.ps[b + j];
-      const float SV = A.sv[b + j];
+      const float4 P = Pn;
+      const float SV = SVn;
+      Pn = A.ps[b + min(i + GL, last)];
+      SVn = A.sv[b + min(i + GL, last)];
       const float dx = lx - P.x, dy = ly - P.y, dz = lz - P.z;
       const float z2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
       const float pp = fmaf(P.z, P.z, fmaf(P.y, P.y, P.x * P.x));

@@ -108,3 +108,26 @@ def test_backward_equals_the_per_thread_kernels(precision, kernel, limit):
     # points whose gradient nearly vanishes, which the median's share of the bound covers
     assert bool(((a - b).abs() <= eps * 2 ** 10 * (big + big.median())).all())
     assert torch.allclose(ah * reps, bh, rtol=eps * 2 ** 10, atol=0)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_hyperparameter_sums_where_one_block_ends(precision):
+    """d_hyper of up to 4,096 points is summed by one block, beyond by 256: the same as the sum
+    over two halves, to the FP64 rounding of the few additions that are ordered otherwise (FP32
+    partials are added in float-float, 2^-44 a step)."""
+    print(f"[gpu-case] hyperparameter sums {precision}", flush=True)
+    wl = scenes.small_room_workload(n_queries=4097, cfg_id=36)
+    model, _, dt = _setup(wl, precision)
+    q, sg = torch.from_numpy(wl.queries).to("cuda", dt), torch.from_numpy(wl.sign).cuda()
+    g = torch.Generator(device="cuda").manual_seed(1)
+    cot = [torch.rand(*s, generator=g, device="cuda", dtype=dt) for s in ((4097,), (4097, 3), (4097,))]
+    am = model.query(q, sg)["argmin"]
+
+    def sums(a, b):
+        s = slice(a, b)
+        return model.backward(q[s], sg[s], *(c[s].contiguous() for c in cot), argmin=am[s])[1].clone()
+
+    each = torch.stack([sums(i, i + 1) for i in range(0, 4097, 64)]).abs().sum(0) * 64   # their size
+    eps = 2.0 ** (-40 if precision == "fp32" else -46)
+    for n in (1, 255, 256, 257, 4096, 4097):
+        assert bool(((sums(0, n) - sums(0, n // 2) - sums(n // 2, n)).abs() <= eps * each).all()), n
