@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libksdf.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["api.hip", "fit.hip", "fit64.hip", "index.hip", "query.hip", "query_launch.hip", "query_fast.hip", "query_split64_wave.hip",
+SOURCES = ["api.hip", "fit.hip", "fit64.hip", "fit_rbf.hip", "fit_matern.hip", "index.hip", "query.hip", "query_launch.hip", "query_fast.hip", "query_split64_wave.hip",
            "query_split64_lane.hip", "query_split256_wave.hip", "query_split256_lane.hip",
            "query_pairs.hip", "query_group.hip", "fused.hip", "backward.hip", "backward_group.hip", "bhm.hip", "noalloc.hip"]
 HOST_SOURCES = ["cells_host.cpp"]

@@ -2,91 +2,69 @@
 //
 // Cells with m <= 64 are fitted by one wave each (fit_wave.h: rows in registers, four
 // cells per workgroup, no workgroup barriers); larger cells by one workgroup each
-// (256 threads, 4 waves of 64), which gathers the cell's samples into cell-local
-// coordinates, assembles A = K + Sigma, factors it A = L L^T in place (right-looking,
-// packed lower triangle), solves a = A^{-1} 1 with wave-0 triangular solves whose dot
-// products reduce by cross-lane shuffles.  Both write the per-cell store: (p_i, a_i),
-// sigma_i^2, the packed factor with the reciprocal diagonal, the sample bounding box
-// and A+ = sum of positive a_i.
+// (fit_quad.h: four waves, 64 x 64 blocks in registers); fit_launch.h has their kernels.
+// Both write the per-cell store: (p_i, a_i), sigma_i^2, the packed factor with the
+// reciprocal diagonal, the sample bounding box and A+ = sum of positive a_i.
 //
-// The workgroup fit keeps A in LDS (float-float entries plus the FP32 factor, 99 KB
-// at m = 128).  Both estimate cond_2(A) by power and inverse iteration; a cell above
-// the threshold or with a non-positive pivot is queued for the FP64 kernel, which
-// factors in global memory (the plain FP64 path uses that kernel for every cell).
+// Both bound cond_2(A) by A's row sums and, where that does not decide, estimate it by
+// power and inverse iteration; a cell above the threshold or with a non-positive pivot is
+// queued for the FP64 kernel (the plain FP64 path uses that kernel for every cell).
 #include <algorithm>
 
 #include "fit_dev.h"
-#include "fit_wave.h"
-#include "fit_quad.h"
 
 namespace ksdf {
 namespace {
 
-constexpr int FIT_THREADS = 256;
-
-// list: the cells to fit; count (device, or null for the grid size): how many of them
-template <int MB>
-__global__ void __launch_bounds__(FIT_THREADS) fit32_kernel(FitArgs A, const int* list,
-                                                            const int* count) {
-  __shared__ float smem[fit32_smem_floats<MB>()];
-  if (count && (int)blockIdx.x >= *count) return;
-  const int c = list[blockIdx.x];
-  const bool need64 = fit32_cell<MB>(A, c, smem);
-  if (threadIdx.x == 0 && need64) {
-    const int slot = atomicAdd(A.fb_count, 1);
-    A.fb_list[slot] = c;
+// dA/dl of the FP32-fitted cells, packed as the factor (adjoint_var_f models), from the stored
+// coordinates: dA_ik/dl = A_ik r_ik^2 / l^3 (RBF) or c^2 r_ik^2 exp(-c r_ik) / l (Matern 3/2).
+// Its own kernel, one thread an entry: inside the fit its rows were 4-byte stores 64 rows
+// apart, and their branches split the adjoint's sum and spilled its terms.  43 us for the
+// room's 5516 cells of 64 samples.
+__global__ void __launch_bounds__(FIT_THREADS) fit_dA_kernel(FitArgs A, FitList l) {
+  if (l.count && (int)blockIdx.x >= *l.count) return;
+  const int c = l.cells[blockIdx.x];
+  const int b = A.offsets[c], m = A.offsets[c + 1] - b;
+  __shared__ float4 xh[MAXM], xl[MAXM];
+  for (int i = threadIdx.x; i < m; i += FIT_THREADS) {
+    xh[i] = reinterpret_cast<const float4*>(A.ps32)[b + i];
+    xl[i] = reinterpret_cast<const float4*>(A.plo32)[b + i];
   }
-}
-
-// One wave per cell for m <= MB <= 64 (fit_wave.h), four cells per workgroup; n: the
-// list's length when count is null
-template <int MB, bool MATERN>
-__global__ void __launch_bounds__(FIT_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
-fit32w_kernel(FitArgs A, const int* list,
-                                                             const int* count, int n) {
-  __shared__ WaveFitLds<MB> lds[FIT_THREADS / 64];
-  const int w = threadIdx.x / 64;
-  const int t = blockIdx.x * (FIT_THREADS / 64) + w;
-  if (t >= (count ? *count : n)) return;
-  const int c = list[t];
-  const bool need64 = fit32_wave<MB, MATERN>(A, c, lds[w]);
-  if ((threadIdx.x & 63) == 0 && need64) {
-    const int slot = atomicAdd(A.fb_count, 1);
-    A.fb_list[slot] = c;
-  }
-}
-
-// One workgroup (four waves) per cell for 64 < m <= 128 (fit_quad.h)
-template <bool MATERN>
-__global__ void __launch_bounds__(FIT_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
-fit32q_kernel(FitArgs A, const int* list, const int* count) {
-  __shared__ QuadFitLds lds;
-  if (count && (int)blockIdx.x >= *count) return;
-  const int c = list[blockIdx.x];
-  const bool need64 = fit32_quad<MATERN>(A, c, lds);
-  if (threadIdx.x == 0 && need64) {
-    const int slot = atomicAdd(A.fb_count, 1);
-    A.fb_list[slot] = c;
-  }
-}
-
-// launch a bucket: the one-wave fit up to m = 64, the four-wave fit above
-template <int MB>
-void launch_bucket(const FitArgs& A, const int* list, const int* count, int n, hipStream_t s) {
-  if (n <= 0) return;
-  if constexpr (MB <= 64) {
-    const int per = FIT_THREADS / 64;
-    const dim3 grid((unsigned)((n + per - 1) / per));
+  __syncthreads();
+  const ff inv2l2{A.inv2l2_ff[0], A.inv2l2_ff[1]};
+  float* D = A.D32 + A.loff[c];
+  for (int e = threadIdx.x; e < m * (m + 1) / 2; e += FIT_THREADS) {
+    int i = (int)((sqrtf(8.f * (float)e + 1.f) - 1.f) * 0.5f);
+    while (i * (i + 1) / 2 > e) --i;
+    while ((i + 1) * (i + 2) / 2 <= e) ++i;
+    const int k = e - i * (i + 1) / 2;
+    const float4 h = xh[i], l = xl[i], g = xh[k], f = xl[k];
+    const ff r2 = ff_norm2_lean(ff_sub_lean(h.x, l.x, g.x, f.x), ff_sub_lean(h.y, l.y, g.y, f.y),
+                                ff_sub_lean(h.z, l.z, g.z, f.z));
+    float d;
     if (A.kernel == KSDF_KERNEL_MATERN32)
-      hipLaunchKernelGGL((fit32w_kernel<MB, true>), grid, dim3(FIT_THREADS), 0, s, A, list, count, n);
+      d = A.mc2_ff[0] * r2.hi * expf(-A.mc_ff[0] * sqrtf(r2.hi)) * A.inv_l_ff[0];
     else
-      hipLaunchKernelGGL((fit32w_kernel<MB, false>), grid, dim3(FIT_THREADS), 0, s, A, list, count, n);
+      d = ff_exp_neg_lean(ff_mul(r2, inv2l2)).hi * r2.hi * A.inv_l3_ff[0];
+    D[e] = i == k ? 0.f : d;
+  }
+}
+
+// The FP32 fits of the cells of up to 16, 32, 64 and 128 samples, and their packed dA/dl where
+// the model keeps it
+void launch_fit32(const FitArgs& A, const FitList (&l)[4], hipStream_t s) {
+  if (A.kernel == KSDF_KERNEL_MATERN32) {
+    launch_fit_large_matern(A, l[3], l[2], s);
+    launch_fit_small_matern(A, 32, l[1], s);
+    launch_fit_small_matern(A, 16, l[0], s);
   } else {
-    if (A.kernel == KSDF_KERNEL_MATERN32)
-      hipLaunchKernelGGL((fit32q_kernel<true>), dim3((unsigned)n), dim3(FIT_THREADS), 0, s, A, list, count);
-    else
-      hipLaunchKernelGGL((fit32q_kernel<false>), dim3((unsigned)n), dim3(FIT_THREADS), 0, s, A, list, count);
+    launch_fit_large_rbf(A, l[3], l[2], s);
+    launch_fit_small_rbf(A, 32, l[1], s);
+    launch_fit_small_rbf(A, 16, l[0], s);
   }
+  if (!A.adjoint || !A.D32) return;
+  for (const FitList& k : l)
+    if (k.n > 0) hipLaunchKernelGGL(fit_dA_kernel, dim3((unsigned)k.n), dim3(FIT_THREADS), 0, s, A, k);
 }
 
 __global__ void set_int_kernel(int* p, int v) { *p = v; }
@@ -329,13 +307,12 @@ int launch_refit(ksdf_model* m, const void* pts, int dtype, const void* svar, fl
     const int* bs = m->bucket_start;
     const int lo32 = minb >= 32 ? bs[0] : bs[1];
     const int lo64 = minb >= 64 ? bs[0] : bs[2];
-    const int n16 = minb < 32 ? bs[1] - bs[0] : 0;
-    const int n32 = minb < 64 ? bs[2] - lo32 : 0;
-    const int n64 = bs[3] - lo64, n128 = bs[4] - bs[3];
-    launch_bucket<16>(A, blist, bcount, std::min(n16, budget), s);
-    launch_bucket<32>(A, blist + budget, bcount + 1, std::min(n32, budget), s);
-    launch_bucket<64>(A, blist + 2L * budget, bcount + 2, std::min(n64, budget), s);
-    launch_bucket<128>(A, blist + 3L * budget, bcount + 3, std::min(n128, budget), s);
+    const int n[4] = {minb < 32 ? bs[1] - bs[0] : 0, minb < 64 ? bs[2] - lo32 : 0, bs[3] - lo64,
+                      bs[4] - bs[3]};
+    FitList l[4];
+    for (int bk = 0; bk < 4; ++bk)
+      l[bk] = FitList{blist + (long)bk * budget, bcount + bk, std::min(n[bk], budget)};
+    launch_fit32(A, l, s);
     A.list = m->fb_list;
     A.list_count = m->fb_count;
     A.emit32 = 1;
@@ -390,10 +367,11 @@ int launch_fit(ksdf_model* m, const void* pts, int dtype, const void* svar, uint
     const int minb = m->tuning.fit_min_bucket;
     const int lo32 = minb >= 32 ? bs[0] : bs[1];
     const int lo64 = minb >= 64 ? bs[0] : bs[2];
-    if (minb < 32) launch_bucket<16>(A, lists + bs[0], nullptr, bs[1] - bs[0], s);
-    if (minb < 64) launch_bucket<32>(A, lists + lo32, nullptr, bs[2] - lo32, s);
-    launch_bucket<64>(A, lists + lo64, nullptr, bs[3] - lo64, s);
-    launch_bucket<128>(A, lists + bs[3], nullptr, bs[4] - bs[3], s);
+    const FitList l[4] = {{lists + bs[0], nullptr, minb < 32 ? bs[1] - bs[0] : 0},
+                          {lists + lo32, nullptr, minb < 64 ? bs[2] - lo32 : 0},
+                          {lists + lo64, nullptr, bs[3] - lo64},
+                          {lists + bs[3], nullptr, bs[4] - bs[3]}};
+    launch_fit32(A, l, s);
     A.list = m->fb_list;
     A.list_count = m->fb_count;
     A.emit32 = 1;

@@ -160,6 +160,16 @@ __device__ void wave_matvec(const T* Ap, int m, const WVec<T>& x, WVec<T>& y) {
   }
 }
 
+// cond_2(A) <= (largest row sum) / (smallest sample variance) for A = K + Sigma: the entries
+// are positive (Perron) and K is positive semidefinite.  Where that lies a factor 1.25 below
+// the refit threshold the estimate below, which approaches cond_2 from below but for the
+// rounding of the FP32 solves (about cond 2^-24, 0.06 at the threshold of 1e6), cannot reach the threshold either, and its
+// four products and four solves are left out (a tenth of the fit of 64 samples).
+__device__ __forceinline__ float cond_upper_bound(float rowsum, float var) { return rowsum / var; }
+__device__ __forceinline__ bool cond_surely_below(float bound, double thr) {
+  return bound > 0.f && 1.25f * bound <= (float)thr;   // false for variances not above zero
+}
+
 // 2-norm condition estimate of SPD A: lambda_max by power iteration with Rayleigh
 // quotients on the packed A (entries all positive, so the start vector of ones is
 // close to the Perron vector), lambda_min by inverse iteration through the factor
@@ -637,6 +647,21 @@ __device__ bool fit32_cell(const FitArgs& A, int c, float* smem) {
 }
 
 }  // namespace
+
+constexpr int FIT_THREADS = 256;
+
+// Cells to fit: their ids, and how many: n, or at most n where the device knows (count)
+struct FitList {
+  const int* cells;
+  const int* count;
+  int n;
+};
+// FP32 fits (fit_rbf.hip, fit_matern.hip): of up to mb = 16 or 32 samples; of 65 to 128 (q) and
+// of up to 64 (w)
+void launch_fit_small_rbf(const FitArgs& A, int mb, const FitList& l, hipStream_t s);
+void launch_fit_small_matern(const FitArgs& A, int mb, const FitList& l, hipStream_t s);
+void launch_fit_large_rbf(const FitArgs& A, const FitList& q, const FitList& w, hipStream_t s);
+void launch_fit_large_matern(const FitArgs& A, const FitList& q, const FitList& w, hipStream_t s);
 
 // FP64 fits (fit64.hip): the cells of A.list (A.list_count of them, at most as known to the
 // device; grid: workgroups), or every cell of the model

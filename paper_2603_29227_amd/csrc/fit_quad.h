@@ -35,7 +35,7 @@ struct QuadFitLds {
   alignas(16) float wh[128];
   alignas(16) float wl[128];
   alignas(16) float y[128];       // hand-offs of the triangular solves
-  alignas(16) float col[64];      // the column of a register factorisation step
+  alignas(16) float col[2][64];   // the column of a register factorisation step
   float ps[2][128];               // partial sums of the second column block: [rhs][row]
   float pc[2][128];
   float red[2];                   // cross-wave reductions
@@ -117,35 +117,67 @@ struct QuadFit {
     return fmaxf(S.red[0], S.red[1]);
   }
 
-  // The triangular solves index no register array, so they run as loops (j uniform,
-  // v_readlane with a scalar lane index) rather than unrolled: that keeps the
-  // registers for the rows of A.
+  // The triangular solves index no register array, so they run as loops over 16 columns
+  // (j uniform, v_readlane with a scalar lane index) rather than unrolled over all 64: that
+  // keeps the registers for the rows of A.  The next 16 entries of L are read ahead: a chain
+  // of 64 steps that waited for its entries took 3 us.  n: columns before the identity.
+  static constexpr int TRI = 16;
+  // y = L^-1 r for one 64 x 64 block, the lane's row of L at `row`
+  __device__ __forceinline__ float tri_forward(const float* row, float r, int n) const {
+    float y = 0.f, p[TRI], q[TRI];
+    static_for<0, TRI>([&](auto K) { p[K] = row[K]; });
+    for (int j0 = 0; j0 < n; j0 += TRI) {
+      const float* next = row + (j0 + TRI < 64 ? j0 + TRI : j0);
+      static_for<0, TRI>([&](auto K) { q[K] = next[K]; });
+      static_for<0, TRI>([&](auto K) {
+        const float t = r * rd, yj = readlane(t, j0 + K);
+        y = lane == j0 + K ? t : y;
+        r = fmaf(-p[K], yj, r);
+      });
+      static_for<0, TRI>([&](auto K) { p[K] = q[K]; });
+    }
+    return y;
+  }
+  // x = L^-T r for the block of rows first.. (and columns first..), last rows first
+  __device__ __forceinline__ float tri_backward(int first, float r, int n) const {
+    float x = 0.f, p[TRI], q[TRI];
+    int i0 = (n - 1) & ~(TRI - 1);
+    auto entry = [&](int i) { return S.L[pkq(first + i, first) + lane]; };
+    static_for<0, TRI>([&](auto K) { p[K] = entry(i0 + TRI - 1 - K); });
+    for (; i0 >= 0; i0 -= TRI) {
+      const int n0 = i0 >= TRI ? i0 - TRI : 0;
+      static_for<0, TRI>([&](auto K) { q[K] = entry(n0 + TRI - 1 - K); });
+      static_for<0, TRI>([&](auto K) {
+        const int i = i0 + TRI - 1 - K;
+        const float t = r * rd, xi = readlane(t, i);
+        x = lane == i ? t : x;
+        r = fmaf(-p[K], xi, r);
+      });
+      static_for<0, TRI>([&](auto K) { p[K] = q[K]; });
+    }
+    return x;
+  }
+
   // L y = b (b and y on the lanes of waves 0 and 1, rows R)
   __device__ __forceinline__ float forward(float b) {
     float y = 0.f;
     if (w == 0) {
-      const float* row = S.L + pkq(lane, 0);
-      float r = b;
-#pragma unroll 4
-      for (int j = 0; j < 64; ++j) {
-        const float yj = readlane(r * rd, j);
-        if (lane == j) y = yj;
-        r = fmaf(-row[j], yj, r);
-      }
+      y = tri_forward(S.L + pkq(lane, 0), b, 64);
       S.y[lane] = y;
     }
     __syncthreads();
     if (w == 1) {
       const float* row = S.L + pkq(64 + lane, 0);
       float r = b;
-#pragma unroll 8
-      for (int j = 0; j < 64; ++j) r = fmaf(-row[j], S.y[j], r);
 #pragma unroll 4
-      for (int j = 0; j < m - 64; ++j) {
-        const float yj = readlane(r * rd, j);
-        if (lane == j) y = yj;
-        r = fmaf(-row[64 + j], yj, r);
+      for (int g = 0; g < 16; ++g) {
+        const float4 v = reinterpret_cast<const float4*>(S.y)[g];
+        r = fmaf(-row[4 * g], v.x, r);
+        r = fmaf(-row[4 * g + 1], v.y, r);
+        r = fmaf(-row[4 * g + 2], v.z, r);
+        r = fmaf(-row[4 * g + 3], v.w, r);
       }
+      y = tri_forward(row + 64, r, m - 64);
     }
     return y;
   }
@@ -154,26 +186,21 @@ struct QuadFit {
   __device__ __forceinline__ float backward(float y) {
     float x = 0.f;
     if (w == 1) {
-      float r = y;
-#pragma unroll 4
-      for (int i = m - 65; i >= 0; --i) {
-        const float xi = readlane(r * rd, i);
-        if (lane == i) x = xi;
-        r = fmaf(-S.L[pkq(64 + i, 64) + lane], xi, r);
-      }
+      x = tri_backward(64, y, m - 64);
       S.y[64 + lane] = x;
     }
     __syncthreads();
     if (w == 0) {
       float r = y;
-#pragma unroll 8
-      for (int i = 0; i < 64; ++i) r = fmaf(-S.L[pkq(64 + i, 0) + lane], S.y[64 + i], r);
 #pragma unroll 4
-      for (int i = 63; i >= 0; --i) {
-        const float xi = readlane(r * rd, i);
-        if (lane == i) x = xi;
-        r = fmaf(-S.L[pkq(i, 0) + lane], xi, r);
+      for (int g = 0; g < 16; ++g) {
+        const float4 v = reinterpret_cast<const float4*>(S.y + 64)[g];
+        r = fmaf(-S.L[pkq(64 + 4 * g, 0) + lane], v.x, r);
+        r = fmaf(-S.L[pkq(65 + 4 * g, 0) + lane], v.y, r);
+        r = fmaf(-S.L[pkq(66 + 4 * g, 0) + lane], v.z, r);
+        r = fmaf(-S.L[pkq(67 + 4 * g, 0) + lane], v.w, r);
       }
+      x = tri_backward(0, r, 64);
     }
     __syncthreads();
     return x;
@@ -266,40 +293,6 @@ struct QuadFit {
   }
 };
 
-// Register Cholesky of a 64 x 64 block held one row per lane (Lr), first n columns
-// (the rest identity); leaves 1 / L_ii in rd.  false on a non-positive pivot.
-__device__ __forceinline__ bool block_chol64(float (&Lr)[64], float& rd, float* col, int n) {
-  const int lane = threadIdx.x & 63;
-  bool ok = true;
-  rd = 1.f;
-  static_for<0, 64>([&](auto J) {
-    constexpr int j = J;
-    if (ok && j < n) {
-      const float d = readlane(Lr[j], j);
-      if (!(d > 0.f)) {
-        ok = false;
-      } else {
-        const float ljj = sqrtf(d), inv = 1.f / ljj;
-        const float l = lane > j ? Lr[j] * inv : (lane == j ? ljj : 0.f);
-        Lr[j] = l;
-        if (lane == j) rd = inv;
-        col[lane] = l;
-        wave_lds_sync();
-        static_for<(j + 1) / 4, 16>([&](auto G) {
-          constexpr int g = G;
-          const float4 cv = reinterpret_cast<const float4*>(col)[g];
-          if constexpr (4 * g > j) Lr[4 * g] = fmaf(-l, cv.x, Lr[4 * g]);
-          if constexpr (4 * g + 1 > j) Lr[4 * g + 1] = fmaf(-l, cv.y, Lr[4 * g + 1]);
-          if constexpr (4 * g + 2 > j) Lr[4 * g + 2] = fmaf(-l, cv.z, Lr[4 * g + 2]);
-          if constexpr (4 * g + 3 > j) Lr[4 * g + 3] = fmaf(-l, cv.w, Lr[4 * g + 3]);
-        });
-        wave_lds_sync();
-      }
-    }
-  });
-  return ok;
-}
-
 // Fit cell c (64 < m <= 128) with the whole workgroup; true when it must be refitted
 // in FP64.
 template <bool MATERN>
@@ -356,33 +349,38 @@ __device__ __forceinline__ bool fit32_quad(const FitArgs& A, int c, QuadFitLds& 
   const ff inv2l2{A.inv2l2_ff[0], A.inv2l2_ff[1]};
   const ff mc{A.mc_ff[0], A.mc_ff[1]};
   float Lr[64];
+  float rowsum = 0.f;   // this block's part of row R's sum
   static_for<0, 64>([&](auto K) {
     constexpr int k = K;
     const int C = 64 * cb + k;
-    ff v{R == C ? 1.f : 0.f, 0.f};
-    if (C < m) {   // uniform
-      const ff r2 = Q.dist2(xh, xl, C);
-      ff kv;
-      if constexpr (MATERN) {
-        const ff t = ff_mul(ff_sqrt(r2), mc);
-        kv = ff_mul(ff_add(ff{1.f, 0.f}, t), ff_exp_neg_lean(t));
-      } else {
-        kv = ff_exp_neg_lean(ff_mul(r2, inv2l2));
-      }
-      if (R == C) kv = ff_add(kv, ff{svh, svl});
-      if (mine) v = kv;
+    const ff r2 = Q.dist2(xh, xl, C);
+    ff kv;
+    if constexpr (MATERN) {
+      const ff t = ff_mul(ff_sqrt(r2), mc);
+      kv = ff_mul(ff_add(ff{1.f, 0.f}, t), ff_exp_neg_lean(t));
+    } else {
+      kv = ff_exp_neg_lean(ff_mul(r2, inv2l2));
     }
+    const ff kd = ff_add(kv, ff{svh, svl});
+    const bool inside = mine && C < m;
+    ff v{inside ? kv.hi : 0.f, inside ? kv.lo : 0.f};
+    if (R == C) v = inside ? kd : ff{1.f, 0.f};
     Q.ah[k] = v.hi;
     // the lower triangle, each entry once (entries above it go to a per-lane dummy slot,
     // which keeps the store unconditional)
     S.Alo[C <= R ? pkq(R, 0) + C : QF_NP + threadIdx.x] = v.lo;
     Lr[k] = v.hi;
-    __builtin_amdgcn_sched_barrier(0);   // one entry's temporaries at a time
+    rowsum += v.hi;
+    if constexpr (k % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // two entries' temporaries
   });
+  if (w >= 2) S.ps[0][R] = rowsum;
+  __syncthreads();
+  const float2 lim = Q.rows_max2(w < 2 && mine ? rowsum + S.ps[0][R] : 0.f, w < 2 && mine ? -svh : -INFINITY);
+  const float bound = cond_upper_bound(lim.x, -lim.y);
   // L11 (wave 0)
   if (w == 0) {
     float rd0;
-    const bool ok = block_chol64(Lr, rd0, S.col, 64);
+    const bool ok = reg_cholesky<64>(Lr, rd0, S.col);
     if (ok) {
       static_for<0, 64>([&](auto K) {
         if (K < lane) S.L[pkq(lane, K)] = Lr[K];
@@ -445,7 +443,7 @@ __device__ __forceinline__ bool fit32_quad(const FitArgs& A, int c, QuadFitLds& 
     });
     wave_lds_sync();
     float rd3;
-    const bool ok3 = block_chol64(Lr, rd3, S.col, m - 64);
+    const bool ok3 = reg_cholesky<64>(Lr, rd3, S.col);
     if (ok3) {
       static_for<0, 64>([&](auto K) {
         if (K < lane) S.L[pkq(64 + lane, 64 + K)] = Lr[K];
@@ -458,8 +456,8 @@ __device__ __forceinline__ bool fit32_quad(const FitArgs& A, int c, QuadFitLds& 
   __syncthreads();
   ok = S.flag != 0;
   if (w == 1) Q.rd = S.L[pkq(64 + lane, 64 + lane)];
-  float cond = INFINITY;
-  if (ok) {
+  float cond = ok ? bound : INFINITY;
+  if (ok && !cond_surely_below(bound, A.cond_thr)) {
     // lambda_max by power iteration (ones start), lambda_min by inverse iteration
     // (alternating-sign start), as the one-wave fit
     const bool row = w < 2 && mine;
@@ -497,26 +495,22 @@ __device__ __forceinline__ bool fit32_quad(const FitArgs& A, int c, QuadFitLds& 
       __syncthreads();
       const ff il = MATERN ? ff{A.inv_l_ff[0], A.inv_l_ff[1]} : ff{A.inv_l3_ff[0], A.inv_l3_ff[1]};
       const ff mc2{A.mc2_ff[0], A.mc2_ff[1]};
-      const float il3f = A.inv_l3_ff[0];
       float gs = 0.f, gc = 0.f;
-      float* Drow = (A.D32 && mine) ? A.D32 + A.loff[c] + pkq(R, 0) : nullptr;
+      const float yh[3] = {own(xh[0]), own(xh[1]), own(xh[2])};   // formed again (fit_wave.h)
+      const float yl[3] = {own(xl[0]), own(xl[1]), own(xl[2])};
+      const int Rv = own(R);
       static_for<0, 64>([&](auto K) {
         constexpr int k = K;
         const int C = 64 * cb + k;
-        if (C < m) {   // uniform; the diagonal term is zero (r = 0)
-          const ff r2 = Q.dist2(xh, xl, C);
-          ff dk;
-          if constexpr (MATERN) dk = ff_mul(ff_mul(ff_exp_neg_lean(ff_mul(ff_sqrt(r2), mc)), r2), mc2);
-          else dk = ff_mul(ff{Q.ah[k], Q.alo(k, R)}, r2);
-          if (C == R) dk = ff{0.f, 0.f};
-          dot2_sub(gs, gc, dk.hi, dk.lo, S.vh[C], S.vl[C]);
-          if (Drow && C < R)
-            Drow[C] = MATERN ? A.mc2_ff[0] * r2.hi * expf(-A.mc_ff[0] * sqrtf(r2.hi)) * A.inv_l_ff[0]
-                             : Q.ah[k] * r2.hi * il3f;
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        const ff r2 = Q.dist2(yh, yl, C);
+        ff dk;
+        if constexpr (MATERN) dk = ff_mul(ff_mul(ff_exp_neg_lean(ff_mul(ff_sqrt(r2), mc)), r2), mc2);
+        else dk = ff_mul(ff{Q.ah[k], Q.alo(k, Rv)}, r2);
+        if (C == R) dk = ff{0.f, 0.f};   // r = 0
+        dot2_sub(gs, gc, dk.hi, dk.lo, S.vh[C], S.vl[C]);
+        asm volatile("" : "+v"(gs), "+v"(gc));   // summed here (fit_wave.h)
+        if constexpr (k % 2 == 1) __builtin_amdgcn_sched_barrier(0);
       });
-      if (Drow && w < 2) Drow[R] = 0.f;
       if (w >= 2) {
         S.ps[0][R] = gs;
         S.pc[0][R] = gc;

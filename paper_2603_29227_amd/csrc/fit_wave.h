@@ -5,9 +5,9 @@
 // row i: its row of A (float-float) and of the factor L stay in registers (the loops
 // over a row are unrolled, so every index is a compile-time constant), and the
 // values other lanes need travel through a small per-wave LDS area:
-//   * the factorisation is right-looking by columns: at column j lane i scales its
-//     entry to L_ij, the column goes to LDS, and every lane applies the rank-1 update
-//     a_ik -= L_ij L_kj to its row with the column read back four entries at a time;
+//   * the factorisation (reg_cholesky) is right-looking by columns: at column j lane i
+//     scales its entry to L_ij, the column goes to LDS, and every lane applies the rank-1
+//     update a_ik -= L_ij L_kj to its row, the column read back four entries at a time;
 //   * the solves run on the packed factor in LDS: L y = b with y_j leaving lane j by
 //     v_readlane and each lane reading its own row, L^T x = y with lanes k < i reading
 //     row i (contiguous); both without bank conflicts, and with the factor out of the
@@ -16,9 +16,12 @@
 // The residuals are compensated dot products (Dot2) of the float-float rows with the
 // float-float iterate, the kernel entries come from lean float-float helpers (exact
 // coordinate differences, TwoProduct squares, a table-driven exp), and the kernel
-// function is a template parameter, so the unrolled loops carry no run-time branches
-// beyond the uniform "column inside the cell" tests.  Rows past m are the identity, so
-// a cell is the leading block of an MB x MB factorisation.
+// function is a template parameter.  Rows and columns past m are the identity's, so a cell
+// is the leading block of an MB x MB factorisation, and the unrolled loops run over all MB
+// columns without a branch: the zeros they add change no bit, and a test of each column
+// against m cost more than the columns it left out (64 branches per loop, behind which no
+// load was moved ahead, and spilled registers): a cell of 63 samples took 172 us with the
+// tests and takes 98, and the room's 5516 cells 744 and 410 us.
 #pragma once
 
 #include <type_traits>
@@ -46,7 +49,7 @@ struct WaveFitLds {
   alignas(16) float vl[64];
   alignas(16) float wh[64];
   alignas(16) float wl[64];
-  alignas(16) float col[64];               // the column of the factorisation step
+  alignas(16) float col[2][64];            // the column of the factorisation step
   alignas(16) float L[wave_lds_l_floats<MB>()];   // packed factor rows, reciprocal diagonal
 };
 
@@ -56,6 +59,58 @@ __device__ __forceinline__ bool packed_diag(int e) {
   if ((i + 1) * (i + 2) / 2 <= e) ++i;
   if (i * (i + 1) / 2 > e) --i;
   return e == i * (i + 3) / 2;
+}
+
+// The lane's number as a value of its own for each loop, so that the comparisons with it are
+// made where they are used and not kept for the next loop (64 masks, which spill).
+template <class T>
+__device__ __forceinline__ T own(T v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
+// Cholesky factor of an N x N matrix held one row per lane (Lr), right-looking by columns;
+// leaves 1 / L_ii in rd; false on a non-positive pivot (Lr is then of no use).  The next pivot
+// needs one entry of the column only, which comes by v_readlane, so its square root and
+// reciprocal run while the rest of the rank-1 update reads the column from LDS: a column took
+// 930 cycles one after the other.
+template <int N>
+__device__ __forceinline__ bool reg_cholesky(float (&Lr)[N], float& rd, float (&col)[2][64]) {
+  const int lane = threadIdx.x & 63;
+  float d = readlane(Lr[0], 0);
+  bool ok = d > 0.f;
+  float ljj = sqrtf(d), inv = 1.f / ljj;
+  float l = lane > 0 ? Lr[0] * inv : ljj;
+  rd = lane == 0 ? inv : 1.f;
+  Lr[0] = l;
+  static_for<0, N - 1>([&](auto J) {
+    constexpr int j = J;
+    __builtin_amdgcn_sched_barrier(0);
+    const int me = own(lane);
+    float* cj = col[j & 1];
+    cj[lane] = l;
+    wave_lds_sync();
+    Lr[j + 1] = fmaf(-l, readlane(l, j + 1), Lr[j + 1]);
+    d = readlane(Lr[j + 1], j + 1);
+    ok = ok && d > 0.f;
+    ljj = sqrtf(d);
+    inv = 1.f / ljj;
+    const float lj = Lr[j + 1] * inv;
+    const float next = me > j + 1 ? lj : (me == j + 1 ? ljj : 0.f);
+    rd = me == j + 1 ? inv : rd;
+    Lr[j + 1] = next;
+    static_for<(j + 2) / 4, N / 4>([&](auto G) {
+      constexpr int g = G;
+      const float4 cv = reinterpret_cast<const float4*>(cj)[g];
+      if constexpr (4 * g > j + 1) Lr[4 * g] = fmaf(-l, cv.x, Lr[4 * g]);
+      if constexpr (4 * g + 1 > j + 1) Lr[4 * g + 1] = fmaf(-l, cv.y, Lr[4 * g + 1]);
+      if constexpr (4 * g + 2 > j + 1) Lr[4 * g + 2] = fmaf(-l, cv.z, Lr[4 * g + 2]);
+      if constexpr (4 * g + 3 > j + 1) Lr[4 * g + 3] = fmaf(-l, cv.w, Lr[4 * g + 3]);
+      if constexpr (g % 6 == 5) __builtin_amdgcn_sched_barrier(0);   // registers for the reads
+    });
+    l = next;
+  });
+  return ok;
 }
 
 template <int MB, bool MATERN>
@@ -69,6 +124,9 @@ struct WaveFit {
 
   __device__ __forceinline__ WaveFit(WaveFitLds<MB>& s, int m_)
       : S(s), lane(threadIdx.x & 63), m(m_) {}
+  // The loops are unrolled without branches: the scheduler keeps to one step, as it would
+  // draw the loads of many ahead and spill the rows.
+  static __device__ __forceinline__ void step_end() { __builtin_amdgcn_sched_barrier(0); }
 
   // squared distance of samples `lane` and k, float-float, from the broadcast coordinates
   __device__ __forceinline__ ff dist2(const float xh_[3], const float xl_[3], int k) const {
@@ -84,13 +142,13 @@ struct WaveFit {
   __device__ __forceinline__ float forward(float b) const {
     const float* row = S.L + (lane < MB ? lane * (lane + 1) / 2 : 0);   // lanes past MB: unused
     float r = b, y = 0.f;
+    const int me = own(lane);
     static_for<0, MB>([&](auto J) {
       constexpr int j = J;
-      if (j < m) {   // uniform
-        const float yj = readlane(r * rd, j);
-        if (lane == j) y = yj;
-        r = fmaf(-row[j], yj, r);   // meaningful for lanes > j only
-      }
+      if constexpr (j % 8 == 0) step_end();
+      const float t = r * rd, yj = readlane(t, j);
+      y = me == j ? t : y;
+      r = fmaf(-row[j], yj, r);   // meaningful for lanes > j only
     });
     return y;
   }
@@ -99,20 +157,19 @@ struct WaveFit {
   __device__ __forceinline__ void forward2(float b0, float b1, float& y0, float& y1) const {
     const float* row = S.L + (lane < MB ? lane * (lane + 1) / 2 : 0);   // lanes past MB: unused
     float r0 = b0, r1 = b1;
+    const int me = own(lane);
     y0 = 0.f;
     y1 = 0.f;
     static_for<0, MB>([&](auto J) {
       constexpr int j = J;
-      if (j < m) {
-        const float u0 = readlane(r0 * rd, j), u1 = readlane(r1 * rd, j);
-        if (lane == j) {
-          y0 = u0;
-          y1 = u1;
-        }
-        const float l = row[j];
-        r0 = fmaf(-l, u0, r0);
-        r1 = fmaf(-l, u1, r1);
-      }
+      if constexpr (j % 8 == 0) step_end();
+      const float t0 = r0 * rd, t1 = r1 * rd, u0 = readlane(t0, j), u1 = readlane(t1, j);
+      const bool at = me == j;
+      y0 = at ? t0 : y0;
+      y1 = at ? t1 : y1;
+      const float l = row[j];
+      r0 = fmaf(-l, u0, r0);
+      r1 = fmaf(-l, u1, r1);
     });
   }
 
@@ -120,33 +177,32 @@ struct WaveFit {
   // lanes' updates touch entries they no longer use (the reads stay inside L)
   __device__ __forceinline__ float backward(float y) const {
     float r = y, x = 0.f;
+    const int me = own(lane);
     static_for<0, MB>([&](auto I) {
       constexpr int i = MB - 1 - I;
-      if (i < m) {
-        const float xi = readlane(r * rd, i);
-        if (lane == i) x = xi;
-        r = fmaf(-S.L[i * (i + 1) / 2 + lane], xi, r);
-      }
+      if constexpr (i % 8 == 7) step_end();
+      const float t = r * rd, xi = readlane(t, i);
+      x = me == i ? t : x;
+      r = fmaf(-S.L[i * (i + 1) / 2 + lane], xi, r);
     });
     return x;
   }
 
   __device__ __forceinline__ void backward2(float y0, float y1, float& x0, float& x1) const {
     float r0 = y0, r1 = y1;
+    const int me = own(lane);
     x0 = 0.f;
     x1 = 0.f;
     static_for<0, MB>([&](auto I) {
       constexpr int i = MB - 1 - I;
-      if (i < m) {
-        const float u0 = readlane(r0 * rd, i), u1 = readlane(r1 * rd, i);
-        if (lane == i) {
-          x0 = u0;
-          x1 = u1;
-        }
-        const float l = S.L[i * (i + 1) / 2 + lane];
-        r0 = fmaf(-l, u0, r0);
-        r1 = fmaf(-l, u1, r1);
-      }
+      if constexpr (i % 8 == 7) step_end();
+      const float t0 = r0 * rd, t1 = r1 * rd, u0 = readlane(t0, i), u1 = readlane(t1, i);
+      const bool at = me == i;
+      x0 = at ? t0 : x0;
+      x1 = at ? t1 : x1;
+      const float l = S.L[i * (i + 1) / 2 + lane];
+      r0 = fmaf(-l, u0, r0);
+      r1 = fmaf(-l, u1, r1);
     });
   }
 
@@ -159,6 +215,7 @@ struct WaveFit {
     float y = 0.f;
     static_for<0, MB / 4>([&](auto G) {
       constexpr int g = G;
+      if constexpr (g % 4 == 0) step_end();
       const float4 v = reinterpret_cast<const float4*>(S.vh)[g];
       y = fmaf(ah[4 * g], v.x, y);
       y = fmaf(ah[4 * g + 1], v.y, y);
@@ -174,6 +231,7 @@ struct WaveFit {
     float s = rhs.hi, c = rhs.lo;
     static_for<0, MB / 4>([&](auto G) {
       constexpr int g = G;
+      step_end();
       const float4 h = reinterpret_cast<const float4*>(vh)[g];
       const float4 l = reinterpret_cast<const float4*>(vl)[g];
       dot2_sub(s, c, ah[4 * g], al[4 * g], h.x, l.x);
@@ -293,63 +351,47 @@ __device__ __forceinline__ bool fit32_wave(const FitArgs& A, int c, WaveFitLds<M
   // A = K + Sigma, row `lane`, float-float; the identity past m
   const ff inv2l2{A.inv2l2_ff[0], A.inv2l2_ff[1]};
   const ff mc{A.mc_ff[0], A.mc_ff[1]};
+  const int me0 = own(lane);
+  float rowsum = 0.f;   // row `lane` of A: a bound of its largest eigenvalue
   static_for<0, MB>([&](auto K) {
     constexpr int k = K;
-    ff v{lane == k ? 1.f : 0.f, 0.f};
-    if (k < m) {   // uniform
-      const ff r2 = W.dist2(xh, xl, k);
-      ff kv;
-      if constexpr (MATERN) {
-        const ff t = ff_mul(ff_sqrt(r2), mc);
-        kv = ff_mul(ff_add(ff{1.f, 0.f}, t), ff_exp_neg_lean(t));
-      } else {
-        kv = ff_exp_neg_lean(ff_mul(r2, inv2l2));
-      }
-      if (k == lane) kv = ff_add(kv, ff{svh, svl});
-      if (mine) v = kv;
+    if constexpr (k % 2 == 0) W.step_end();   // two columns at a time hide each other's latencies
+    const ff r2 = W.dist2(xh, xl, k);
+    ff kv;
+    if constexpr (MATERN) {
+      const ff t = ff_mul(ff_sqrt(r2), mc);
+      kv = ff_mul(ff_add(ff{1.f, 0.f}, t), ff_exp_neg_lean(t));
+    } else {
+      kv = ff_exp_neg_lean(ff_mul(r2, inv2l2));
     }
+    const ff kd = ff_add(kv, ff{svh, svl});
+    const bool inside = mine && k < m;
+    ff v{inside ? kv.hi : 0.f, inside ? kv.lo : 0.f};
+    if (k == me0) v = inside ? kd : ff{1.f, 0.f};
+    // formed here: left to its first use after the factorisation, the low part would keep
+    // three values alive per column
+    asm volatile("" : "+v"(v.hi), "+v"(v.lo));
     W.ah[k] = v.hi;
     W.al[k] = v.lo;
     W.Lr[k] = v.hi;
+    rowsum += v.hi;
   });
-  // Cholesky, right-looking by columns
-  bool ok = true;
-  W.rd = 1.f;
-  static_for<0, MB>([&](auto J) {
-    constexpr int j = J;
-    if (ok && j < m) {   // uniform: a failed pivot stops the factorisation
-      const float d = readlane(W.Lr[j], j);
-      if (!(d > 0.f)) {
-        ok = false;
-      } else {
-        const float ljj = sqrtf(d), inv = 1.f / ljj;
-        const float l = lane > j ? W.Lr[j] * inv : (lane == j ? ljj : 0.f);
-        W.Lr[j] = l;
-        if (lane == j) W.rd = inv;
-        S.col[lane] = l;
-        wave_lds_sync();
-        static_for<(j + 1) / 4, MB / 4>([&](auto G) {
-          constexpr int g = G;
-          const float4 cv = reinterpret_cast<const float4*>(S.col)[g];
-          if constexpr (4 * g > j) W.Lr[4 * g] = fmaf(-l, cv.x, W.Lr[4 * g]);
-          if constexpr (4 * g + 1 > j) W.Lr[4 * g + 1] = fmaf(-l, cv.y, W.Lr[4 * g + 1]);
-          if constexpr (4 * g + 2 > j) W.Lr[4 * g + 2] = fmaf(-l, cv.z, W.Lr[4 * g + 2]);
-          if constexpr (4 * g + 3 > j) W.Lr[4 * g + 3] = fmaf(-l, cv.w, W.Lr[4 * g + 3]);
-        });
-        wave_lds_sync();
-      }
-    }
-  });
-  // the packed factor (reciprocal diagonal) for the L^T solves and the store
-  if (ok) {
+  const bool ok = reg_cholesky<MB>(W.Lr, W.rd, S.col);
+  // the packed factor (reciprocal diagonal) for the L^T solves and the store.  Every lane
+  // writes its whole register row, the last column first: what lies past the diagonal falls
+  // on entries of later rows with a smaller column, whose own writes come after.
+  if (ok && lane < MB) {
+    float* row = S.L + lane * (lane + 1) / 2;
     static_for<0, MB>([&](auto K) {
-      if (K < lane && mine) S.L[pk(lane, K)] = W.Lr[K];
+      row[MB - 1 - K] = W.Lr[MB - 1 - K];
+      wave_lds_sync();   // keeps the order
     });
-    if (mine) S.L[pk(lane, lane)] = W.rd;
+    row[lane] = W.rd;
   }
   wave_lds_sync();
-  float cond = INFINITY;
-  if (ok) {
+  float cond = ok ? cond_upper_bound(wave_max(mine ? rowsum : 0.f), wave_min(mine ? svh : INFINITY))
+                  : INFINITY;
+  if (ok && !cond_surely_below(cond, A.cond_thr)) {
     // lambda_max by power iteration (ones start), lambda_min by inverse iteration
     // (alternating-sign start): a lower bound of cond_2(A), as cond2_estimate
     float x = mine ? 1.f : 0.f, lmax = 0.f;
@@ -385,24 +427,24 @@ __device__ __forceinline__ bool fit32_wave(const FitArgs& A, int c, WaveFitLds<M
       wave_lds_sync();
       const ff il = MATERN ? ff{A.inv_l_ff[0], A.inv_l_ff[1]} : ff{A.inv_l3_ff[0], A.inv_l3_ff[1]};
       const ff mc2{A.mc2_ff[0], A.mc2_ff[1]};
-      const float il3f = A.inv_l3_ff[0];
       float gs = 0.f, gc = 0.f;   // minus the row sum, as Dot2 accumulators
-      float* Drow = A.D32 ? A.D32 + A.loff[c] + (mine ? pk(lane, 0) : 0) : nullptr;
+      // (coordinates of their own here, so that the distances are formed again: kept from
+      // the assembly they would take 128 registers)
+      const float yh[3] = {own(xh[0]), own(xh[1]), own(xh[2])};
+      const float yl[3] = {own(xl[0]), own(xl[1]), own(xl[2])};
+      const int me = own(lane);
       static_for<0, MB>([&](auto K) {
         constexpr int k = K;
-        if (k < m) {   // uniform; the diagonal term is zero (r = 0)
-          const ff r2 = W.dist2(xh, xl, k);
-          ff dk;
-          if constexpr (MATERN) dk = ff_mul(ff_mul(ff_exp_neg_lean(ff_mul(ff_sqrt(r2), mc)), r2), mc2);
-          else dk = ff_mul(ff{W.ah[k], W.al[k]}, r2);
-          if (k == lane) dk = ff{0.f, 0.f};
-          dot2_sub(gs, gc, dk.hi, dk.lo, S.vh[k], S.vl[k]);
-          if (Drow && mine && k < lane)
-            Drow[k] = MATERN ? A.mc2_ff[0] * r2.hi * expf(-A.mc_ff[0] * sqrtf(r2.hi)) * A.inv_l_ff[0]
-                             : W.ah[k] * r2.hi * il3f;
-        }
+        if constexpr (k % 2 == 0) W.step_end();
+        const ff r2 = W.dist2(yh, yl, k);
+        ff dk;
+        if constexpr (MATERN) dk = ff_mul(ff_mul(ff_exp_neg_lean(ff_mul(ff_sqrt(r2), mc)), r2), mc2);
+        else dk = ff_mul(ff{W.ah[k], W.al[k]}, r2);
+        if (k == me) dk = ff{0.f, 0.f};   // r = 0
+        dot2_sub(gs, gc, dk.hi, dk.lo, S.vh[k], S.vl[k]);
+        asm volatile("" : "+v"(gs), "+v"(gc));   // summed here: left to its use after the loop,
+                                                 // the sum would keep every dk alive
       });
-      if (Drow && mine) Drow[lane] = 0.f;
       wave_lds_sync();
       const ff g = ff_mul(ff_neg(ff_two_sum(gs, gc)), il);
       ff xil, xis{0.f, 0.f};
