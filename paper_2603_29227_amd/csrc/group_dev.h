@@ -61,6 +61,18 @@ __device__ __forceinline__ T group_lane_quick(T v) {
   return ((threadIdx.x & 4) == 0) == (S < 4) ? x : y;
 }
 
+// the greatest value of each group
+template <class T>
+__device__ __forceinline__ T group_max(T v) {
+  v = max(v, dpp<DPP_XOR1>(v));
+  v = max(v, dpp<DPP_XOR2>(v));
+  return max(v, dpp<DPP_MIRROR8>(v));
+}
+// whether v holds on all lanes of the group (which must be active together)
+__device__ __forceinline__ bool group_all(bool v) {
+  return ((__ballot(v) >> (threadIdx.x & 56)) & 0xff) == 0xff;
+}
+
 // the smallest (distance, id) pair of each group
 template <class T>
 __device__ __forceinline__ void group_min(T& d, int& id) {

@@ -5,8 +5,14 @@
 // boxes.  For box B, D_K(B) is the K-th smallest, over occupied cells c, of the
 // farthest distance from c's centre to B.  Every point of B then has K cells
 // within D_K(B), so only cells whose nearest distance to B is <= D_K(B) can be
-// among its K nearest; those cells (a superset, ascending ids) are B's list.  A
-// query scans its box's list and keeps the K nearest exactly.
+// among its K nearest; those cells (a superset) are B's list.  A query scans its box's
+// list and keeps the K nearest exactly.
+//
+// A list of up to INDEX_SORTED_MAX cells is ordered by the distance of their centres from
+// the box's, so that a query can stop where every later centre lies farther from it than its
+// K-th nearest so far (cand_scan_over in query_dev.h).  In the room at K = 8 lists hold 60
+// cells on average; a query meets 18 of them, and 10 enter its K nearest on the way (26 in
+// the order of ids).
 //
 // Cell centres sit at the middle of lattice boxes, so both distances depend only on
 // the integer key offset t between cell and box: per axis the centre lies t + 1/2
@@ -22,7 +28,8 @@
 // a wave-wide min merge give the K-th smallest so far; a cell in a later shell is at
 // least (2r + 3)^2 + 2 units away, so once the K-th smallest is within that, it is
 // final.  The list is then the cube of keys that can lie within the bound, scanned in
-// key order (which is id order) with a ballot prefix for the writes.  Built once per
+// key order (which is id order) with a ballot prefix for the writes, and ordered in LDS by
+// counting the entries before each (lists are short).  Built once per
 // model (structure only), in two passes: the count pass fixes each box's list length
 // (and so the list's size, which the caller then provides), the fill pass writes the
 // lists.
@@ -32,6 +39,7 @@
 #include <utility>
 
 #include "ksdf_internal.h"
+#include "wave_ops.h"
 
 namespace ksdf {
 namespace {
@@ -122,8 +130,9 @@ __device__ __forceinline__ void bound_cube(const IndexArgs& A, int i, int j, int
   }
 }
 
-// Visits the cube's keys in key order, lanes striding; f(id, in) for each batch of 64
-// entries, `in` true where the key holds a cell whose near distance is within bound.
+// Visits the cube's keys in key order, lanes striding; f(id, in, d2) for each batch of 64
+// entries, `in` true where the key holds a cell whose near distance is within bound, d2 the
+// squared distance of the key's centre from the box's in squared edges.
 template <class F>
 __device__ __forceinline__ void scan_cube(const IndexArgs& A, int i, int j, int k, long bound,
                                           F&& f) {
@@ -134,14 +143,17 @@ __device__ __forceinline__ void scan_cube(const IndexArgs& A, int i, int j, int 
   for (long e0 = 0; e0 < vol; e0 += 64) {
     const long e = e0 + lane;
     int c = -1;
+    float d2 = 0.f;
     if (e < vol) {
       const int x = lo[0] + (int)(e / ((long)n[1] * n[2]));
       const int y = lo[1] + (int)((e / n[2]) % n[1]);
       const int z = lo[2] + (int)(e % n[2]);
       const long near2 = near_units(abs(x - i)) + near_units(abs(y - j)) + near_units(abs(z - k));
       if (near2 <= bound) c = A.kmap[((long)x * A.dims[1] + y) * A.dims[2] + z];
+      const float dx = (float)(x - i), dy = (float)(y - j), dz = (float)(z - k);
+      d2 = dx * dx + dy * dy + dz * dz;
     }
-    f(c, c >= 0);
+    f(c, c >= 0, d2);
   }
 }
 
@@ -195,7 +207,7 @@ __global__ void __launch_bounds__(IDX_THREADS) index_count_kernel(IndexArgs A) {
     bound = dk + dk / 65536 + (long)(sqrtf((float)dk) * A.margin_abs);
   int count = 0;
   if (bound < LONG_MAX)
-    scan_cube(A, i, j, k, bound, [&](int, bool in) { count += __popcll(__ballot(in)); });
+    scan_cube(A, i, j, k, bound, [&](int, bool in, float) { count += __popcll(__ballot(in)); });
   if (lane == 0) {
     A.bound[b] = bound;
     A.counts[b] = count;
@@ -210,13 +222,31 @@ __global__ void __launch_bounds__(IDX_THREADS) index_fill_kernel(IndexArgs A) {
   box_coords(A, b, i, j, k);
   const long bound = A.bound[b];
   if (bound == LONG_MAX) return;
-  int pos = A.off[b];
-  scan_cube(A, i, j, k, bound, [&](int c, bool in) {
+  const int off = A.off[b], n = A.off[b + 1] - off;
+  __shared__ float key[BOXES_PER_BLOCK][INDEX_SORTED_MAX];
+  __shared__ int id[BOXES_PER_BLOCK][INDEX_SORTED_MAX];
+  const int w = threadIdx.x / 64;
+  const bool sorted = n <= INDEX_SORTED_MAX;
+  int pos = 0;
+  scan_cube(A, i, j, k, bound, [&](int c, bool in, float d2) {
     const unsigned long long bal = __ballot(in);
-    const int before = __popcll(bal & ((1ull << lane) - 1ull));
-    if (in) A.list[pos + before] = c;
+    const int at = pos + __popcll(bal & ((1ull << lane) - 1ull));
+    if (in && sorted) {
+      key[w][at] = d2;
+      id[w][at] = c;
+    } else if (in) {
+      A.list[off + at] = c;
+    }
     pos += __popcll(bal);
   });
+  if (!sorted) return;
+  wave_lds_sync();
+  for (int t = lane; t < n; t += 64) {
+    const float d = key[w][t];
+    int before = 0;
+    for (int u = 0; u < n; ++u) before += key[w][u] < d || (key[w][u] == d && u < t);
+    A.list[off + before] = id[w][t];
+  }
 }
 
 }  // namespace
@@ -258,6 +288,16 @@ int index_lattice(ksdf_model* m, const double* qlo, const double* qhi) {
 }
 
 namespace {
+// the coordinates' magnitude in boxes
+double magnitude(const ksdf_model* m) {
+  const CandidateIndex& X = m->index;
+  double mag = 0;
+  for (int d = 0; d < 3; ++d)
+    mag = std::max(mag, std::fabs(m->origin[d]) / m->h + std::max(std::abs(X.lo[d]),
+                                                                   std::abs(X.lo[d] + X.dims[d])));
+  return mag;
+}
+
 IndexArgs index_args(const ksdf_model* m) {
   const CandidateIndex& X = m->index;
   IndexArgs A{};
@@ -269,11 +309,7 @@ IndexArgs index_args(const ksdf_model* m) {
   // with |x| the coordinates' magnitude and d the distance (sqrt(bound) h / 2); in
   // (h/2)^2 units that is 8 sqrt(bound) (|x| / h) 2^-24 per operation.  The margin
   // takes 2^-16 per sqrt(unit) per box of magnitude, far above that.
-  double mag = 0;
-  for (int d = 0; d < 3; ++d)
-    mag = std::max(mag, std::fabs(m->origin[d]) / m->h + std::max(std::abs(X.lo[d]),
-                                                                   std::abs(X.lo[d] + X.dims[d])));
-  A.margin_abs = (float)(mag * std::ldexp(1.0, -16));
+  A.margin_abs = (float)(magnitude(m) * std::ldexp(1.0, -16));
   A.bound = X.bound;
   A.counts = X.counts;
   A.off = X.box_off;
@@ -281,6 +317,10 @@ IndexArgs index_args(const ksdf_model* m) {
   return A;
 }
 }  // namespace
+
+double cand_slack_of(const ksdf_model* m) {
+  return m->h * (std::ldexp(1.0, -10) + magnitude(m) * std::ldexp(1.0, -18));
+}
 
 int index_count(ksdf_model* m, hipStream_t s) {
   CandidateIndex& X = m->index;

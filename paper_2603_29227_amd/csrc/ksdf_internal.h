@@ -31,13 +31,16 @@ void set_error(const std::string& msg);
 
 // Candidate index over a lattice of cell-sized boxes: for lattice box B, every
 // occupied cell that can be among the K nearest cell centres of some point of B.
+constexpr int INDEX_SORTED_MAX = 1024;   // LDS: 8 KB a wave
+
 struct CandidateIndex {
   int lo[3] = {0, 0, 0};       // lattice key of box (0,0,0)
   int dims[3] = {0, 0, 0};
   long n_boxes = 0;
   long entries = 0;
   int* box_off = nullptr;      // [n_boxes+1]
-  int* box_list = nullptr;     // [entries] cell ids, ascending within a box
+  int* box_list = nullptr;     // [entries] cell ids, those of a box nearest its centre first
+                               // (lists over INDEX_SORTED_MAX: ascending)
   int* box_rank = nullptr;     // [n_boxes] position of each box in Z (Morton) order
   int* kmap = nullptr;         // [n_boxes] cell id at each lattice key, -1 where none
   long* bound = nullptr;       // [n_boxes] inclusion bound on near distances, (h/2)^2 units
@@ -175,6 +178,9 @@ int launch_count_queries(const ksdf_model* m, const int* argmin, long Q, float* 
 int launch_query(const ksdf_model* m, const void* points, long Q, const int8_t* sign, void* mean,
                  void* grad, void* var, void* var_f, void* grad_var, int* argmin, uint8_t* q_status, void* ws,
                  size_t ws_bytes, hipStream_t s, bool prebucketed = false);
+// margin of the candidate scans' end: coordinates of mag boxes' magnitude are rounded by up to
+// mag h 2^-24 each in FP32
+double cand_slack_of(const ksdf_model* m);
 size_t query_workspace_bytes(const ksdf_model* m, long Q);
 // The query's bucketing alone (the first step of launch_query_fast), for running it
 // beside the fit; launch_query_fast then skips it when called with prebucketed set.

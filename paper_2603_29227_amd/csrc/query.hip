@@ -46,6 +46,7 @@ struct QueryArgs {
   double h;
   int lo[3];
   int dims[3];
+  double cand_slack;  // margin of the candidate scan's end (cand_slack_of)
   long n_boxes;
   const int* box_off;
   const int* box_list;
@@ -160,22 +161,38 @@ __global__ void __launch_bounds__(64) query_plain_kernel(QueryArgs<T> A) {
     beg = A.box_off[bx];
     end = A.box_off[bx + 1];
   }
-  for (int t = beg + g; t < end; t += GL) {
-    int xi = inside ? A.box_list[t] : t;
-    T x = cand_d2(qx, qy, qz, centre_of(A, xi));
-    if (x < cd[KM - 1] || (x == cd[KM - 1] && xi < ci[KM - 1])) {
+  // two entries a lane at a time, until no later centre of a list in the order of distances
+  // from the box's centre can enter (cand_scan_over in query_dev.h)
+  const bool sorted = inside && end - beg <= INDEX_SORTED_MAX;
+  T mid[3];
 #pragma unroll
-      for (int r = 0; r < KM; ++r) {
-        if (x < cd[r] || (x == cd[r] && xi < ci[r])) {
-          const T tx = cd[r];
-          const int ti = ci[r];
-          cd[r] = x;
-          ci[r] = xi;
-          x = tx;
-          xi = ti;
+  for (int d = 0; d < 3; ++d) mid[d] = (T)(A.origin[d] + ((double)(key[d] + A.lo[d]) + 0.5) * A.h);
+  const T rho = sqrt(cand_d2(qx, qy, qz, mid));
+  for (int t0 = beg; t0 < end; t0 += 2 * GL) {   // uniform in the group
+    T at = (T)0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int t = t0 + g + u * GL;
+      int xi = inside ? A.box_list[min(t, end - 1)] : min(t, end - 1);
+      const auto ce = centre_of(A, xi);
+      at = cand_d2(mid[0], mid[1], mid[2], ce);
+      T x = cand_d2(qx, qy, qz, ce);
+      if (t < end && (x < cd[KM - 1] || (x == cd[KM - 1] && xi < ci[KM - 1]))) {
+#pragma unroll
+        for (int r = 0; r < KM; ++r) {
+          if (x < cd[r] || (x == cd[r] && xi < ci[r])) {
+            const T tx = cd[r];
+            const int ti = ci[r];
+            cd[r] = x;
+            ci[r] = xi;
+            x = tx;
+            xi = ti;
+          }
         }
       }
     }
+    const T far = (sqrt(group_max(cd[KM / GL - 1])) + rho) * (T)(1 + 0x1p-14) + (T)A.cand_slack;
+    if (sorted && group_all(at > far * far)) break;
   }
   const int n = min(A.k, end - beg);
   int mine[NC];   // the lane's candidates: ranks g and g + 8
@@ -391,6 +408,7 @@ QueryArgs<T> make_args(const ksdf_model* m, const void* points, long Q, const in
     A.dims[d] = m->index.dims[d];
   }
   A.h = m->h;
+  A.cand_slack = cand_slack_of(m);
   A.n_boxes = m->index.n_boxes;
   A.box_off = m->index.box_off;
   A.box_list = m->index.box_list;

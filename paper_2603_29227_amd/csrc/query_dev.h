@@ -43,6 +43,8 @@ struct FastArgs {
   const float* __restrict__ box;    // [n,8]: lo xyz, A+, hi xyz, pad
   float origin[3];
   float inv_h;
+  float h;             // box edge
+  float cand_slack;    // cand_scan_over's margin for the rounding of coordinates
   int sub;           // sub-boxes per box edge for bucketing (1, 2 or 4)
   int lo[3];
   int dims[3];
@@ -358,13 +360,46 @@ __device__ __forceinline__ float readlane_f(float v, int l) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
 
+// The end of a scan of a list in the order of the centres' distances from the box's centre: by
+// the triangle inequality a later centre is at least sqrt(d2) - rho from the query, with d2
+// the present entry's squared distance from the box's centre and rho the query's distance from
+// it, so none can enter once that exceeds the K-th nearest distance, sqrt(kth).  The margins
+// (a relative one for this test's own roundings, an absolute one for those of centres, box
+// centre and query) keep the top K exactly that of the whole list.
+__device__ __forceinline__ bool cand_scan_over(const FastArgs& A, float d2, float kth, float rho) {
+  const float t = fmaf(__builtin_amdgcn_sqrtf(kth) + rho, 1.f + 0x1p-14f, A.cand_slack);
+  return d2 > t * t;   // false while kth is infinite
+}
+
+// centre of the index box that holds a point
+__device__ __forceinline__ float4 box_centre(const FastArgs& A, float qx, float qy, float qz) {
+  return make_float4(fmaf(floorf((qx - A.origin[0]) * A.inv_h) + 0.5f, A.h, A.origin[0]),
+                     fmaf(floorf((qy - A.origin[1]) * A.inv_h) + 0.5f, A.h, A.origin[1]),
+                     fmaf(floorf((qz - A.origin[2]) * A.inv_h) + 0.5f, A.h, A.origin[2]), 0.f);
+}
+
+// (x, xi) into the sorted top KM; the pairs are compared with the old entries, not one after
+// the other, so an insertion is no chain
+template <int KM>
+__device__ __forceinline__ void cand_insert(float (&cd)[KM], int (&cid)[KM], float x, int xi) {
+  if (!(x < cd[KM - 1] || (x == cd[KM - 1] && xi < cid[KM - 1]))) return;
+  bool lt[KM];
+#pragma unroll
+  for (int r = 0; r < KM; ++r) lt[r] = x < cd[r] || (x == cd[r] && xi < cid[r]);
+#pragma unroll
+  for (int r = KM - 1; r > 0; --r) {
+    cd[r] = __builtin_amdgcn_fmed3f(cd[r - 1], x, cd[r]);
+    cid[r] = lt[r - 1] ? cid[r - 1] : (lt[r] ? xi : cid[r]);
+  }
+  cd[0] = fminf(x, cd[0]);
+  cid[0] = lt[0] ? xi : cid[0];
+}
+
 // Top-KM of (distance, id) over the list of index box b0, for a wave whose active lanes
 // all lie in that box (every lane of the wave calls it; `ref` is an active lane).  Lane
-// j loads entry j of each 64-entry chunk of the list; the chunk is sorted across the
-// wave (bitonic) by its distance to the query of lane ref, so that every lane meets
-// its nearest cells early and later entries rarely enter; the entries then reach all
-// lanes by readlane.  They do not arrive in id order, so equal distances are ordered
-// by id explicitly, which gives the same top-KM as the scan in id order.
+// j loads entry j of each 64-entry chunk of the list; the entries reach all lanes by
+// readlane, until no lane can take a later one.  They do not arrive in id order, so equal
+// distances are ordered by id explicitly, which gives the same top-KM as the scan in id order.
 template <int KM>
 __device__ __forceinline__ void candidates_shared_box(const FastArgs& A, bool active, float qx,
                                                       float qy, float qz, int b0, int ref,
@@ -372,48 +407,24 @@ __device__ __forceinline__ void candidates_shared_box(const FastArgs& A, bool ac
   const int lane = threadIdx.x & 63;
   const int beg = uniform(A.box_off[b0]), end = uniform(A.box_off[b0 + 1]);
   len = end - beg;
-  const float rx = readlane_f(qx, ref), ry = readlane_f(qy, ref), rz = readlane_f(qz, ref);
+  const bool sorted = len <= INDEX_SORTED_MAX;
+  const float4 bc = box_centre(A, readlane_f(qx, ref), readlane_f(qy, ref), readlane_f(qz, ref));
+  const float rho = __builtin_amdgcn_sqrtf(cand_d2(qx, qy, qz, bc));
   for (int t0 = beg; t0 < end; t0 += 64) {
     const int t = t0 + lane;
     const bool have = t < end;
     const int id = have ? A.box_list[t] : 0;
     const float4 ce = A.centre[id];
-    float key = have ? cand_d2(rx, ry, rz, ce) : INFINITY;
-    int src = lane;
-#pragma unroll
-    for (int size = 2; size <= 64; size <<= 1) {
-#pragma unroll
-      for (int j = size >> 1; j > 0; j >>= 1) {
-        const float ok = __shfl_xor(key, j, 64);
-        const int os = __shfl_xor(src, j, 64);
-        // ascending blocks keep the smaller pair in the lower lane, descending the larger
-        const bool keep_min = ((lane & j) == 0) == ((lane & size) == 0);
-        const bool other_less = ok < key || (ok == key && os < src);
-        if (other_less == keep_min) {
-          key = ok;
-          src = os;
-        }
-      }
-    }
+    const float d2 = cand_d2(bc.x, bc.y, bc.z, ce);
     const int cnt = min(64, end - t0);
     for (int e = 0; e < cnt; ++e) {
-      const int s = __builtin_amdgcn_readlane(src, e);
-      int xi = __builtin_amdgcn_readlane(id, s);
-      const float4 c = make_float4(readlane_f(ce.x, s), readlane_f(ce.y, s), readlane_f(ce.z, s), 0.f);
-      float x = cand_d2(qx, qy, qz, c);
-      if (active && (x < cd[KM - 1] || (x == cd[KM - 1] && xi < cid[KM - 1]))) {
-#pragma unroll
-        for (int r = 0; r < KM; ++r) {
-          if (x < cd[r] || (x == cd[r] && xi < cid[r])) {
-            const float tx = cd[r];
-            const int ti = cid[r];
-            cd[r] = x;
-            cid[r] = xi;
-            x = tx;
-            xi = ti;
-          }
-        }
-      }
+      const int xi = __builtin_amdgcn_readlane(id, e);
+      const float4 c = make_float4(readlane_f(ce.x, e), readlane_f(ce.y, e), readlane_f(ce.z, e), 0.f);
+      const float x = cand_d2(qx, qy, qz, c);
+      if (active) cand_insert<KM>(cd, cid, x, xi);
+      if (sorted && e % 4 == 3 &&
+          !__ballot(active && !cand_scan_over(A, readlane_f(d2, e), cd[KM - 1], rho)))
+        return;
     }
   }
 }
@@ -455,6 +466,9 @@ __device__ __forceinline__ void query_candidates(const FastArgs& A, bool active,
       beg = A.box_off[bkey];
       end = A.box_off[bkey + 1];
     }
+    const bool sorted = !outside && end - beg <= INDEX_SORTED_MAX;
+    const float4 bc = box_centre(A, qx, qy, qz);
+    const float rho = __builtin_amdgcn_sqrtf(cand_d2(qx, qy, qz, bc));
     for (int t0 = beg; t0 < end; t0 += 4) {
       int cc[4];
       float4 ce[4];
@@ -466,24 +480,9 @@ __device__ __forceinline__ void query_candidates(const FastArgs& A, bool active,
 #pragma unroll
       for (int u = 0; u < 4; ++u) ce[u] = A.centre[cc[u]];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bool in = t0 + u < end;
-        float x = in ? cand_d2(qx, qy, qz, ce[u]) : INFINITY;
-        int xi = in ? cc[u] : 0x7fffffff;
-        if (x < cd[KM - 1] || (x == cd[KM - 1] && xi < cid[KM - 1])) {
-#pragma unroll
-          for (int r = 0; r < KM; ++r) {
-            if (x < cd[r] || (x == cd[r] && xi < cid[r])) {
-              const float tx = cd[r];
-              const int ti = cid[r];
-              cd[r] = x;
-              cid[r] = xi;
-              x = tx;
-              xi = ti;
-            }
-          }
-        }
-      }
+      for (int u = 0; u < 4; ++u)
+        if (t0 + u < end) cand_insert<KM>(cd, cid, cand_d2(qx, qy, qz, ce[u]), cc[u]);
+      if (sorted && cand_scan_over(A, cand_d2(bc.x, bc.y, bc.z, ce[3]), cd[KM - 1], rho)) break;
     }
     n = min(A.k, end - beg);
   }
@@ -1385,6 +1384,8 @@ inline FastArgs make_fast_args(const ksdf_model* m, const void* points, long Q, 
     A.dims[d] = m->index.dims[d];
   }
   A.inv_h = (float)(1.0 / m->h);
+  A.h = (float)m->h;
+  A.cand_slack = (float)cand_slack_of(m);
   A.sub = sub_of(m, Q);
   A.n_boxes = m->index.n_boxes;
   A.box_off = m->index.box_off;

@@ -57,35 +57,25 @@ __device__ __forceinline__ void group_candidates(const FastArgs& A, bool active,
       end = A.box_off[bkey + 1];
     }
   }
-  for (int t0 = beg + g; t0 < end; t0 += 4 * GL) {
+  const bool sorted = !outside && end - beg <= INDEX_SORTED_MAX;
+  const float4 bc = box_centre(A, qx, qy, qz);
+  const float rho = __builtin_amdgcn_sqrtf(cand_d2(qx, qy, qz, bc));
+  for (int t0 = beg; t0 < end; t0 += 4 * GL) {   // uniform in the group
     int cc[4];
     float4 ce[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int t = min(t0 + u * GL, end - 1);
+      const int t = min(t0 + g + u * GL, end - 1);
       cc[u] = outside ? t : A.box_list[t];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) ce[u] = A.centre[cc[u]];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const bool in = t0 + u * GL < end;
-      float x = in ? cand_d2(qx, qy, qz, ce[u]) : INFINITY;
-      int xi = in ? cc[u] : 0x7fffffff;
-      if (x < cd[KM - 1] || (x == cd[KM - 1] && xi < ci[KM - 1])) {
-#pragma unroll
-        for (int r = 0; r < KM; ++r) {
-          if (x < cd[r] || (x == cd[r] && xi < ci[r])) {
-            const float tx = cd[r];
-            const int ti = ci[r];
-            cd[r] = x;
-            ci[r] = xi;
-            x = tx;
-            xi = ti;
-          }
-        }
-      }
-    }
+    for (int u = 0; u < 4; ++u)
+      if (t0 + g + u * GL < end) cand_insert<KM>(cd, ci, cand_d2(qx, qy, qz, ce[u]), cc[u]);
+    // every lane holds KM / 8 entries within the greatest of the lanes' KM / 8-th
+    const float kth = group_max(cd[KM / GL - 1]);
+    if (sorted && group_all(cand_scan_over(A, cand_d2(bc.x, bc.y, bc.z, ce[3]), kth, rho))) break;
   }
   n = active ? min(A.k, end - beg) : 0;
 #pragma unroll
