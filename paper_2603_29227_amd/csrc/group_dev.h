@@ -5,6 +5,7 @@
 // those of one thread per query bit for bit.
 #pragma once
 
+#include "ksdf_internal.h"
 #include "wave_ops.h"
 
 namespace ksdf {

@@ -6,6 +6,7 @@
 #include <cmath>
 
 #include "ff.h"
+#include "group_dev.h"
 #include "wave_ops.h"
 #include "ksdf_internal.h"
 
@@ -492,12 +493,12 @@ __device__ __forceinline__ void query_candidates(const FastArgs& A, bool active,
 // emax = max e, with e = 2^(c2 (d2ref - z^2)).  With MASK, entries past m belong to the
 // next cell (the store is padded): their offsets from this cell's centre can be far
 // nearer than d2ref, and exp2 would overflow, so their term is masked, not weighted by 0.
-template <bool MASK>
-__device__ __forceinline__ void u2_chunk(const float4 (&P)[CH], int i0, int m, float lx, float ly,
+template <bool MASK, int N>
+__device__ __forceinline__ void u2_chunk(const float4 (&P)[N], int i0, int m, float lx, float ly,
                                          float lz, float c2, float c2d, float& f, float& R,
                                          float& RZ, float& emax) {
 #pragma unroll
-  for (int j = 0; j < CH; ++j) {
+  for (int j = 0; j < N; ++j) {
     const bool in = !MASK || i0 + j < m;
     const float aw = P[j].w;
     const float dx = lx - P[j].x, dy = ly - P[j].y, dz = lz - P[j].z;
@@ -603,12 +604,12 @@ __device__ __forceinline__ void cell_u2_lane(const FastArgs& A, int b, int m, fl
 // Matern 3/2 pass-1 sums over one chunk: f = sum a g, R = sum |a| g, RZ = sum |a| g z
 // with g_i = (1 + c z_i) 2^(c log2(e) (dref - z_i)) and emax the largest exponential
 // factor; dref <= every z_i (the sample box's lower bound), so no factor exceeds 1.
-template <bool MASK>
-__device__ __forceinline__ void um_chunk(const float4 (&P)[CH], int i0, int m, float lx, float ly,
+template <bool MASK, int N>
+__device__ __forceinline__ void um_chunk(const float4 (&P)[N], int i0, int m, float lx, float ly,
                                          float lz, float mc, float mcl, float dref, float& f,
                                          float& R, float& RZ, float& emax) {
 #pragma unroll
-  for (int j = 0; j < CH; ++j) {
+  for (int j = 0; j < N; ++j) {
     const bool in = !MASK || i0 + j < m;
     const float aw = P[j].w;
     const float dx = lx - P[j].x, dy = ly - P[j].y, dz = lz - P[j].z;
@@ -705,6 +706,114 @@ __device__ __forceinline__ void cell_u_matern_lane(const FastArgs& A, int b, int
   if (f > 0.f) {
     u = __builtin_amdgcn_sqrtf(d2ref) - LN2 * __log2f(f) / mc;
     del = EPS32 * (8.f * R + 4.f * mc * RZ) / (mc * f);
+  }
+}
+
+// The samples of 64 cells, one per lane, for sparse queries whose waves share few cells.
+// Loads of one sample of every lane's cell touch 64 lines each, which bounds the walk (the
+// vector cache takes one line a cycle: pass 1 took 248 us for 262,144 trajectory points, and
+// takes 183).
+// So each eight lanes load eight consecutive samples of one of their cells after the other,
+// 128 bytes that lie together, and hand them over in LDS; the next eight are on their way
+// meanwhile.  Lane l's cell has the m samples from b (m = 0: none, b is still read);
+// f(P, i0, tail) is called with samples i0.. of each lane's cell, tail where some lane's end
+// before i0 + 8 (those lanes get their last sample again).  Every lane of the wave calls it.
+constexpr int CHL = 4;                    // samples in registers at a time
+constexpr int COOP_ROW = 65;              // float4; keeps the reads of a group in different banks
+constexpr int COOP_LDS = CH * COOP_ROW;   // float4 per wave
+template <class F>
+__device__ __forceinline__ void coop_samples(const float4* __restrict__ ps, float4* buf, int b, int m,
+                                             F&& f) {
+  const int lane = threadIdx.x & 63, s = lane & (CH - 1);
+  const int last = b + max(m, 1) - 1;
+  int at[CH], end[CH];
+  static_for<0, CH>([&](auto J) {
+    at[J] = group_lane<J>(b) + s;
+    end[J] = group_lane<J>(last);
+  });
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const f4* src = reinterpret_cast<const f4*>(ps);
+  f4* dst = reinterpret_cast<f4*>(buf);
+  f4 N[CH];
+#pragma unroll
+  for (int j = 0; j < CH; ++j) N[j] = src[min(at[j], end[j])];
+  for (int i0 = 0;; i0 += CH) {
+#pragma unroll
+    for (int j = 0; j < CH; ++j) dst[j * COOP_ROW + lane] = N[j];
+    wave_lds_sync();
+    const bool more = __ballot(i0 + CH < m) != 0;
+    // (past the last samples: those again)
+#pragma unroll
+    for (int j = 0; j < CH; ++j) N[j] = src[min(at[j] + (i0 + CH), end[j])];
+    const bool tail = __ballot(m > 0 && i0 + CH > m) != 0;
+#pragma unroll
+    for (int h = 0; h < CH; h += CHL) {   // a part at a time: registers
+      float4 P[CHL];
+#pragma unroll
+      for (int k = 0; k < CHL; ++k) {
+        const f4 v = dst[s * COOP_ROW + (lane - s) + h + k];
+        P[k] = make_float4(v.x, v.y, v.z, v.w);
+      }
+      f(P, i0 + h, tail);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wave_lds_sync();
+    if (!more) break;
+  }
+}
+
+// Where pass 1's sums against the sample box underflow: the lane's nearest sample instead
+__device__ __forceinline__ float nearest_sample_d2(const FastArgs& A, int b, int m, float lx, float ly,
+                                                   float lz) {
+  float d2 = INFINITY;
+  for (int i = 0; i < m; ++i) {
+    const float4 p = A.ps[b + i];
+    const float dx = lx - p.x, dy = ly - p.y, dz = lz - p.z;
+    d2 = fminf(d2, fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+  }
+  return d2;
+}
+
+// cell_u2_wave and cell_u_matern_wave for one cell per lane: the same operations in the same
+// order (the lanes with ev set; b readable on the others).
+template <bool MAT>
+__device__ __forceinline__ void cell_u_lanes(const FastArgs& A, float4* buf, int b, int m, float lx,
+                                             float ly, float lz, bool ev, float& d2ref, float& u,
+                                             float& del) {
+  const float c2 = A.c2, mc = A.mc, mcl = A.mc_l2e;
+  float f = 0.f, R = 0.f, RZ = 0.f;
+  u = INFINITY;
+  del = 0.f;
+  if (!__ballot(ev)) return;
+  bool todo = ev;
+  for (int pass = 0; pass < 2; ++pass) {
+    const float c2d = c2 * d2ref, dref = __builtin_amdgcn_sqrtf(d2ref);
+    float emax = 0.f, f1 = 0.f, R1 = 0.f, RZ1 = 0.f;
+    coop_samples(A.ps, buf, b, todo ? m : 0, [&](const float4 (&P)[CHL], int i0, bool tail) __attribute__((always_inline)) {
+      if constexpr (MAT) {
+        if (tail) um_chunk<true>(P, i0, m, lx, ly, lz, mc, mcl, dref, f1, R1, RZ1, emax);
+        else um_chunk<false>(P, i0, m, lx, ly, lz, mc, mcl, dref, f1, R1, RZ1, emax);
+      } else {
+        if (tail) u2_chunk<true>(P, i0, m, lx, ly, lz, c2, c2d, f1, R1, RZ1, emax);
+        else u2_chunk<false>(P, i0, m, lx, ly, lz, c2, c2d, f1, R1, RZ1, emax);
+      }
+    });
+    if (todo) {
+      f = f1;
+      R = R1;
+      RZ = RZ1;
+    }
+    todo = todo && !(emax >= 0x1p-24f);
+    if (!__ballot(todo)) break;
+    if (todo && pass == 0) d2ref = nearest_sample_d2(A, b, m, lx, ly, lz);
+  }
+  if (!ev || !(f > 0.f)) return;
+  if constexpr (MAT) {
+    u = __builtin_amdgcn_sqrtf(d2ref) - LN2 * __log2f(f) / mc;
+    del = EPS32 * (8.f * R + 4.f * mc * RZ) / (mc * f);
+  } else {
+    u = d2ref - A.two_l2 * LN2 * __log2f(f);
+    del = A.two_l2 * EPS32 * (6.f * R + 3.5f * c2 * RZ) / f;
   }
 }
 
@@ -806,8 +915,10 @@ __device__ __forceinline__ int resolve_min(const FastArgs& A, bool active, float
 // Candidates, per-candidate u^2 and the min-fusion for the 64 sorted queries sq ..
 // of a wave (lanes pass their own sq); every lane of the wave must call it together
 // (wave-uniform loops inside).
-template <int KM, bool LANE = false, bool MAT = false>
-__device__ __forceinline__ Pass1 query_pass1(const FastArgs& A, long sq) {
+// LANE: every lane its own cells; COOP: with their samples loaded by eight lanes each (buf:
+// COOP_LDS float4 of LDS for the wave).
+template <int KM, bool LANE = false, bool MAT = false, bool COOP = false>
+__device__ __forceinline__ Pass1 query_pass1(const FastArgs& A, long sq, float4* buf = nullptr) {
   const bool active = sq < A.Q;
   const long qi = active ? A.perm[sq] : 0;
   const float qx = A.pts[3 * qi], qy = A.pts[3 * qi + 1], qz = A.pts[3 * qi + 2];
@@ -878,30 +989,38 @@ __device__ __forceinline__ Pass1 query_pass1(const FastArgs& A, long sq) {
     }
   }
   } else {
-    // per lane: each lane walks its own candidates, nearest centre first, with its
-    // own (vector) loads; for sparse queries, whose waves would share few cells.
-    // The same arithmetic in the same order as the wave-uniform walk, so the same
-    // results.
-#pragma unroll
+    // per lane: each lane walks its own candidates, nearest centre first, for sparse
+    // queries, whose waves would share few cells.  The same arithmetic in the same order as
+    // the wave-uniform walk, so the same results.  (Rolled, with selects: unrolled 16 times
+    // the candidates' arrays went to scratch.)
+#pragma unroll 1
     for (int r = 0; r < KM; ++r) {
-      if (active && r < n) {
-        const int c = cid[r];
-        const int b = A.offsets[c];
-        const int m = A.offsets[c + 1] - b;
-        const float4 ctr = A.centre[c];
-        const float* bx = A.box + 8L * c;
-        const float lx = qx - ctr.x, ly = qy - ctr.y, lz = qz - ctr.z;
-        float d2ref = aabb_d2(bx, lx, ly, lz);
-        const float lb = cell_lower_bound(A, d2ref, bx[3]);
-        float u2 = INFINITY, del = 0.f;
-        if constexpr (MAT) {
-          if (!(lb > best + 2.f * best_del + 1e-6f)) cell_u_matern_lane(A, b, m, lx, ly, lz, d2ref, u2, del);
-        } else if (!(lb > best + 2.f * best_del + 1e-6f)) {
-          cell_u2_lane(A, b, m, lx, ly, lz, d2ref, u2, del);
-        }
-        cu2[r] = u2;
-        cdl[r] = del;
-        cref[r] = d2ref;
+      const bool on = active && r < n;
+      if (!__ballot(on)) break;
+      int c = 0;
+#pragma unroll
+      for (int k = 0; k < KM; ++k)
+        if (on && k == r) c = cid[k];
+      const int b = A.offsets[c];
+      const int m = A.offsets[c + 1] - b;
+      const float4 ctr = A.centre[c];
+      const float* bx = A.box + 8L * c;
+      const float lx = qx - ctr.x, ly = qy - ctr.y, lz = qz - ctr.z;
+      float d2ref = aabb_d2(bx, lx, ly, lz);
+      const float lb = cell_lower_bound(A, d2ref, bx[3]);
+      const bool ev = on && !(lb > best + 2.f * best_del + 1e-6f);
+      float u2 = INFINITY, del = 0.f;
+      if constexpr (COOP) cell_u_lanes<MAT>(A, buf, b, m, lx, ly, lz, ev, d2ref, u2, del);
+      else if (ev && MAT) cell_u_matern_lane(A, b, m, lx, ly, lz, d2ref, u2, del);
+      else if (ev) cell_u2_lane(A, b, m, lx, ly, lz, d2ref, u2, del);
+      if (on) {
+#pragma unroll
+        for (int k = 0; k < KM; ++k)
+          if (k == r) {
+            cu2[k] = u2;
+            cdl[k] = del;
+            cref[k] = d2ref;
+          }
         if (u2 < best) {
           best = u2;
           best_del = del;

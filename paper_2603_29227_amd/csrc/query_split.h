@@ -16,11 +16,12 @@
 namespace ksdf {
 namespace {
 
-template <int KM, int NT, bool LANE, bool MAT = false>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KM == 8 ? 5 : 1)))
+template <int KM, int NT, bool LANE, bool MAT = false, bool COOP = false>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KM == 8 ? (COOP ? 4 : 5) : 1)))
 query_p1_kernel(FastArgs A, P1Rec* rec, int* count) {
   const long sq = xcd_block(gridDim.x) * NT + threadIdx.x;
-  const Pass1 r = query_pass1<KM, LANE, MAT>(A, sq);
+  __shared__ float4 buf[COOP ? NT / 64 * COOP_LDS : 1];
+  const Pass1 r = query_pass1<KM, LANE, MAT, COOP>(A, sq, buf + (COOP ? threadIdx.x / 64 * COOP_LDS : 0));
   const bool active = (r.flags & 2) != 0;
   const int slot = wave_slot(count, r.bc < 0 ? A.n_cells : (A.p2rank ? A.p2rank[r.bc] : r.bc), active);
   if (active) {
@@ -84,6 +85,20 @@ __global__ void __launch_bounds__(NT) query_p2_kernel(FastArgs A, const P1Rec* r
   query_finish_t<MB, LANE, MF, MAT>(A, r);
 }
 
+// Per-lane cells: with the samples loaded by eight lanes each, but for K > 8 and cells over 64
+// samples, whose lanes end at unlike times and whose registers leave two waves per SIMD
+// (262,144 points, together / each its own: K = 8, m <= 64 335 / 396 us; K = 8, uneven m <= 128
+// 655 / 655; K = 16, m <= 64 575 / 642; K = 16, uneven m <= 128 974 / 864).
+template <int NT, bool LANE, bool MAT>
+void launch_p1(const ksdf_model* m, const FastArgs& A, P1Rec* rec, int* count, unsigned g, hipStream_t s) {
+  if (m->k_fuse <= 8)
+    hipLaunchKernelGGL((query_p1_kernel<8, NT, LANE, MAT, LANE>), dim3(g), dim3(NT), 0, s, A, rec, count);
+  else if (m->max_m <= 64)
+    hipLaunchKernelGGL((query_p1_kernel<16, NT, LANE, MAT, LANE>), dim3(g), dim3(NT), 0, s, A, rec, count);
+  else
+    hipLaunchKernelGGL((query_p1_kernel<16, NT, LANE, MAT>), dim3(g), dim3(NT), 0, s, A, rec, count);
+}
+
 template <int NT, bool LANE>
 void launch_split_nt(const ksdf_model* m, const FastArgs& A, P1Rec* rec, P1Rec* rec2, int* count,
                      int* cursor, int* tsum, void* pws, hipStream_t s) {
@@ -92,12 +107,8 @@ void launch_split_nt(const ksdf_model* m, const FastArgs& A, P1Rec* rec, P1Rec* 
   const long nc = (long)m->n_cells + 1;
   hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, count, nc, 0);
   if (pws) launch_pass1_pairs(m, A, rec, count, pws, s);
-  else if (A.matern && m->k_fuse <= 8)
-    hipLaunchKernelGGL((query_p1_kernel<8, NT, LANE, true>), dim3(g), dim3(NT), 0, s, A, rec, count);
-  else if (A.matern)
-    hipLaunchKernelGGL((query_p1_kernel<16, NT, LANE, true>), dim3(g), dim3(NT), 0, s, A, rec, count);
-  else if (m->k_fuse <= 8) hipLaunchKernelGGL((query_p1_kernel<8, NT, LANE>), dim3(g), dim3(NT), 0, s, A, rec, count);
-  else hipLaunchKernelGGL((query_p1_kernel<16, NT, LANE>), dim3(g), dim3(NT), 0, s, A, rec, count);
+  else if (A.matern) launch_p1<NT, LANE, true>(m, A, rec, count, g, s);
+  else launch_p1<NT, LANE, false>(m, A, rec, count, g, s);
   launch_scan(count, nc, tsum, cursor, s);
   hipLaunchKernelGGL(query_regroup_kernel, dim3((unsigned)((A.Q + 255) / 256)), dim3(256), 0, s, rec,
                      A.Q, m->n_cells, A.p2rank, cursor, A.rank, rec2);

@@ -38,3 +38,27 @@ def test_every_granularity_and_order_gives_the_same_answers(scene, n):
     one = model.query(q[:1].expand(n, 3).contiguous(), sg[:1].expand(n).contiguous(), grad_var=True)
     for k in OUT:
         assert torch.equal(one[k], want[k][:1].expand_as(one[k])), k
+
+
+@pytest.mark.parametrize("kernel", ["rbf", "matern32"])
+@pytest.mark.parametrize("m_max,k_fuse", [(1, 8), (7, 16), (9, 8), (63, 8), (64, 9), (65, 8), (128, 16)])
+def test_per_lane_cells_give_the_same_answers(kernel, m_max, k_fuse):
+    """Past the eight-lane kernel's limit and below 96 points a cell every lane walks its own
+    cells: cells of every remainder of eight samples, points far outside, the last wave partial."""
+    print(f"[gpu-case] lanes {kernel} m<={m_max} k={k_fuse}", flush=True)
+    wl = _sphere(m_max, n_queries=3001)
+    model, cells = _fitted(wl, kernel=kernel, k_fuse=k_fuse)
+    assert cells.m.max() == m_max
+    n = 196609
+    reps = -(-n // 3001)
+    q = torch.from_numpy(np.tile(wl.queries, (reps, 1))[:n]).cuda()
+    q[::97] *= 40
+    sg = torch.from_numpy(np.tile(wl.sign, reps)[:n]).cuda()
+    model.set_tuning(query_split=0)
+    want = model.query(q, sg, grad_var=True)
+    model.set_tuning(query_split=1, query_lanes=1)
+    for block in (64, 256):
+        model.set_tuning(query_block=block)
+        got = model.query(q, sg, grad_var=True)
+        for k in OUT:
+            assert torch.equal(got[k], want[k]), (k, block)
