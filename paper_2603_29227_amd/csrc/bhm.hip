@@ -26,7 +26,7 @@ constexpr int MAX_HINGES = 16;
 
 struct BhmArgs {
   double origin[3];
-  double box;
+  double box, inv_box;
   double spacing;
   int dims[3];
   int nh;
@@ -39,15 +39,29 @@ struct BhmArgs {
   float spacing_ff[2];
 };
 
-// The map box of a point: its lattice key, the flat box index and the map id (-1: no
-// map, or outside the lattice).
+// The map box of a point: its lattice key and the flat box index (-1: outside the lattice).
+template <class T>
+__device__ __forceinline__ long bhm_flat(const BhmArgs& A, const T x3[3], long key[3]) {
+  for (int d = 0; d < 3; ++d) {
+    // x / B to the last bit from 1 / B (two corrections by the exact remainder: Markstein
+    // 1990) where it is in range: the division itself takes three times the instructions
+    const double x = (double)x3[d] - A.origin[d];
+    double t = x * A.inv_box;
+    const double t1 = fma(fma(-t, A.box, x), A.inv_box, t);
+    const double t2 = fma(fma(-t1, A.box, x), A.inv_box, t1);
+    if (fabs(t) < 1e9) key[d] = (int)floor(t2);   // converts in one instruction
+    else key[d] = (long)floor(x / A.box);
+  }
+  bool in = true;
+  for (int d = 0; d < 3; ++d) in = in && key[d] >= 0 && key[d] < A.dims[d];
+  return in ? (key[0] * A.dims[1] + key[1]) * A.dims[2] + key[2] : -1;
+}
+// its map id (-1: none, or outside the lattice)
 template <class T>
 __device__ __forceinline__ int bhm_box(const BhmArgs& A, const T* pts, long q, long key[3]) {
-  for (int d = 0; d < 3; ++d)
-    key[d] = (long)floor(((double)pts[3 * q + d] - A.origin[d]) / A.box);
-  for (int d = 0; d < 3; ++d)
-    if (key[d] < 0 || key[d] >= A.dims[d]) return -1;
-  return A.box_bhm[(key[0] * A.dims[1] + key[1]) * A.dims[2] + key[2]];
+  const T x3[3] = {pts[3 * q], pts[3 * q + 1], pts[3 * q + 2]};
+  const long flat = bhm_flat(A, x3, key);
+  return flat < 0 ? -1 : A.box_bhm[flat];
 }
 
 // Log-odds of a point in FP64 (double points): per-axis factors, then the separable sum.
@@ -83,9 +97,10 @@ __device__ double bhm_logodds64(const BhmArgs& A, const double* pts, long q, con
 // The FP32 log-odds with the hinge count as a compile-time constant NH: every loop
 // unrolls and the per-axis factors stay in registers.  The same operations in the same
 // order as bhm_logodds32_any below.
-template <int NH>
+// (w: the weights in rows of ROW, then the bias)
+template <int NH, int ROW, class W>
 __device__ __forceinline__ float bhm_logodds32_t(const BhmArgs& A, const float* pts, long q,
-                                                 const long key[3], const double* w) {
+                                                 const long key[3], const W* w) {
   float e[3][NH];
   const float g = (float)A.gamma;
 #pragma unroll
@@ -101,14 +116,14 @@ __device__ __forceinline__ float bhm_logodds32_t(const BhmArgs& A, const float* 
       e[d][i] = expf(-g * tt * tt);
     }
   }
-  constexpr int m = NH * NH * NH;
+  constexpr int m = NH * NH * ROW;
   float s = (float)w[m], c = 0.f;   // bias feature; compensated outer sum
 #pragma unroll
   for (int i = 0; i < NH; ++i)
 #pragma unroll
     for (int j = 0; j < NH; ++j) {
       const float eij = e[0][i] * e[1][j];
-      const double* wr = w + (i * NH + j) * NH;
+      const W* wr = w + (i * NH + j) * ROW;
       float acc = 0.f;
 #pragma unroll
       for (int k = 0; k < NH; ++k) acc = fmaf((float)wr[k], e[2][k], acc);
@@ -153,18 +168,27 @@ __device__ float bhm_logodds32_any(const BhmArgs& A, const float* pts, long q, c
 // 7 hinges per axis (the indoor setting) in registers; other counts the general form
 __device__ __forceinline__ float bhm_logodds32(const BhmArgs& A, const float* pts, long q,
                                                const long key[3], const double* w) {
-  if (A.nh == 7) return bhm_logodds32_t<7>(A, pts, q, key, w);
+  if (A.nh == 7) return bhm_logodds32_t<7, 7>(A, pts, q, key, w);
   return bhm_logodds32_any(A, pts, q, key, w);
 }
 
-// Points sorted by map box within each block (bitonic sort of (map id, slot) keys in
-// LDS), so that a wave's points mostly share a map: a wave whose points all lie in one
-// map reads its weights through wave-uniform (scalar) loads, and one that spans a few
-// maps loads each weight from a few addresses.  A larger block lets a wave meet fewer
-// maps but costs occupancy (on the 256^3 room grid, blocks of 128, 256, 512 and 1024
-// points took 0.85, 0.58, 0.63 and 0.92 ms).  Each point's result goes back to its
-// own index.
+// Signs.  Most points lie in no map's box: they are answered at once, and a block's others are
+// gathered in LDS (in the points' order), so that whole waves evaluate maps or none do.  Float
+// points and 7 hinges: the block's maps (a few: neighbouring points share them; found through a
+// small hash table) are converted to FP32 into LDS once, in rows of 8, where every lane reads
+// its own map's.  Maps beyond BHM_MAPS, other hinge counts and double points: every lane loads
+// its map's weights.
+// The kernel moves 21 bytes a point; before, a bitonic sort of every block's map ids, six FP64
+// divisions a point and the loads and conversions of 343 weights a point took 590 us for the
+// 256^3 grid, a fifth of whose points have a map, and whose bytes take 75; now 383 us.
 constexpr int BS = 256;
+constexpr int BHM_MAPS = 16;                 // maps of a block in LDS
+constexpr int BHM_STRIDE = 7 * 7 * 8 + 8;    // floats per map: 49 rows of 8, the bias
+constexpr int BHM_HASH = 64, BHM_PROBES = 4;
+__device__ __forceinline__ int bhm_hash(int id, int p) {
+  return ((int)((unsigned)id * 2654435761u >> 26) + p) % BHM_HASH;
+}
+constexpr long BHM_MANY = 1L << 20;          // points from which a thread takes four
 // Workgroups go to the 8 XCDs (each with its own L2) in turn; neighbouring blocks of
 // points read the same maps, so each XCD takes one contiguous range of the blocks (a
 // bijection of [0, n); the results do not depend on it).
@@ -174,57 +198,107 @@ __device__ __forceinline__ long bhm_block(long n) {
   const long x = i % NX, k = i / NX;
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + k;
 }
-template <class T>
-__device__ __forceinline__ void bhm_sorted_slot(const BhmArgs& A, const T* pts, long Q, long* q_out,
-                                                int* id_out) {
-  __shared__ unsigned long long keys[BS];
-  const long blk = bhm_block(gridDim.x);
-  const long q = blk * BS + threadIdx.x;
-  long key[3];
-  const int id = q < Q ? bhm_box(A, pts, q, key) : INT_MAX - 1;
-  keys[threadIdx.x] = ((unsigned long long)(unsigned)(id + 1) << 32) | threadIdx.x;
-  for (int k = 2; k <= BS; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      __syncthreads();
-      const int t = threadIdx.x, o = t ^ j;
-      if (o > t) {
-        const unsigned long long a = keys[t], b = keys[o];
-        const bool up = (t & k) == 0;
-        if ((a > b) == up) {
-          keys[t] = b;
-          keys[o] = a;
-        }
-      }
-    }
-  __syncthreads();
-  const unsigned long long k = keys[threadIdx.x];
-  *q_out = blk * BS + (long)(k & 0xffffffffu);
-  *id_out = (int)(k >> 32) - 1;
-}
 
-template <class T>
+// PT points per thread
+template <class T, int PT>
 __global__ void __launch_bounds__(BS) bhm_sign_kernel(BhmArgs A, const T* pts, long Q, double tau,
                                                       int8_t* sign, double* logodds) {
-  long q;
-  int id;
-  bhm_sorted_slot(A, pts, Q, &q, &id);
-  if (q >= Q) return;
+  constexpr bool F32 = sizeof(T) == 4;
+  __shared__ int slot[BS * PT], map[BS * PT], count[PT][BS / 64];
+  __shared__ int hash[BHM_HASH], local[BHM_HASH], maps[BHM_MAPS], n_maps;
+  __shared__ alignas(16) float wl[F32 ? BHM_MAPS * BHM_STRIDE : 1];
+  const long base = bhm_block(gridDim.x) * (BS * PT);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+  const bool staged = F32 && A.nh == 7;
+  if (threadIdx.x < BHM_HASH) hash[threadIdx.x] = -1;
+  if (threadIdx.x == 0) n_maps = 0;
   long key[3];
-  bhm_box(A, pts, q, key);
-  const long m = (long)A.nh * A.nh * A.nh;
-  double l = 0.0;
-  const bool have = id >= 0;
-  if (have) {
-    // one map for the whole wave: its weights through scalar loads
-    const int w0 = __builtin_amdgcn_readfirstlane(id);
-    const bool uni = __ballot(id != w0) == 0ull;
-    const double* w = A.weights + (long)(uni ? w0 : id) * (m + 1);
-    if constexpr (sizeof(T) == 8) l = bhm_logodds64(A, pts, q, key, w);
-    else l = (double)bhm_logodds32(A, pts, q, key, w);
+  int id[PT], before[PT];
+  {
+    T x[PT][3];
+    long flat[PT];
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const long q = min(base + i * BS + threadIdx.x, Q - 1);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) x[i][d] = pts[3 * q + d];
+    }
+#pragma unroll
+    for (int i = 0; i < PT; ++i) flat[i] = bhm_flat(A, x[i], key);
+#pragma unroll
+    for (int i = 0; i < PT; ++i) id[i] = A.box_bhm[max(flat[i], 0L)];
+#pragma unroll
+    for (int i = 0; i < PT; ++i)
+      if (flat[i] < 0 || base + i * BS + threadIdx.x >= Q) id[i] = -1;
   }
-  // no local map: the box holds no occupied voxel, taken as free space
-  sign[q] = (!have || l < tau) ? 1 : -1;
-  if (logodds) logodds[q] = have ? l : -INFINITY;
+#pragma unroll
+  for (int i = 0; i < PT; ++i) {
+    const long q = base + i * BS + threadIdx.x;
+    const unsigned long long have = __ballot(id[i] >= 0);
+    before[i] = __popcll(have & ((1ull << lane) - 1ull));
+    if (lane == 0) count[i][wave] = __popcll(have);
+    if (q < Q && id[i] < 0) {
+      // no local map: the box holds no occupied voxel, taken as free space
+      sign[q] = 1;
+      if (logodds) logodds[q] = -INFINITY;
+    }
+  }
+  __syncthreads();
+  int total = 0;
+#pragma unroll
+  for (int i = 0; i < PT; ++i)
+#pragma unroll
+    for (int w = 0; w < BS / 64; ++w) {
+      if (w == wave && id[i] >= 0) {
+        slot[total + before[i]] = i * BS + threadIdx.x;
+        map[total + before[i]] = id[i];
+      }
+      total += count[i][w];
+    }
+  const long m = (long)A.nh * A.nh * A.nh;
+  if (staged) {
+    // each map's number in the block, its own or another lane's
+#pragma unroll
+    for (int i = 0; i < PT; ++i)
+      if (id[i] >= 0) {
+        for (int p = 0; p < BHM_PROBES; ++p) {
+          const int h = bhm_hash(id[i], p), was = atomicCAS(&hash[h], -1, id[i]);
+          if (was == -1) {
+            const int k = atomicAdd(&n_maps, 1);
+            local[h] = k;
+            if (k < BHM_MAPS) maps[k] = id[i];
+          }
+          if (was == -1 || was == id[i]) break;
+        }
+      }
+    __syncthreads();
+    const int n = min(n_maps, BHM_MAPS);
+    for (int e = threadIdx.x; e < n * 344; e += BS) {
+      const int k = e / 344, r = e - k * 344;
+      wl[k * BHM_STRIDE + (r < 343 ? r / 7 * 8 + r % 7 : 392)] = (float)A.weights[(long)maps[k] * 344 + r];
+    }
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < total; t += BS) {
+    const long q = base + slot[t];
+    const int c = map[t];
+    bhm_box(A, pts, q, key);
+    const double* w = A.weights + (long)c * (m + 1);
+    double l;
+    if constexpr (F32) {
+      int k = BHM_MAPS;
+      for (int p = 0; staged && p < BHM_PROBES; ++p) {
+        const int h = bhm_hash(c, p);
+        if (hash[h] == c) k = local[h];
+      }
+      if (k < BHM_MAPS) l = (double)bhm_logodds32_t<7, 8>(A, pts, q, key, wl + k * BHM_STRIDE);
+      else l = (double)bhm_logodds32(A, pts, q, key, w);
+    } else {
+      l = bhm_logodds64(A, pts, q, key, w);
+    }
+    sign[q] = l < tau ? 1 : -1;
+    if (logodds) logodds[q] = l;
+  }
 }
 
 // per-block sums of l at the hit points, in a fixed order (tree in LDS): FP64 for
@@ -325,6 +399,7 @@ bool make_bhm_args(const ksdf_bhm_layout* L, const int* box_bhm, const double* w
     A->dims[d] = L->dims[d];
   }
   A->box = L->box;
+  A->inv_box = 1.0 / L->box;
   A->spacing = L->box / (double)(L->hinges - 1);
   A->nh = L->hinges;
   A->gamma = L->gamma;
@@ -354,13 +429,19 @@ int launch_bhm_sign(const ksdf_bhm_layout* L, const int* box_bhm, const double* 
     return KSDF_ERR_INVALID_ARGUMENT;
   }
   if (Q == 0) return KSDF_OK;
-  const unsigned g = (unsigned)((Q + BS - 1) / BS);
-  if (dtype == KSDF_DTYPE_F64)
-    hipLaunchKernelGGL(bhm_sign_kernel<double>, dim3(g), dim3(BS), 0, s, A,
-                       static_cast<const double*>(points), Q, tau, sign, logodds);
-  else
-    hipLaunchKernelGGL(bhm_sign_kernel<float>, dim3(g), dim3(BS), 0, s, A,
-                       static_cast<const float*>(points), Q, tau, sign, logodds);
+  // four points a thread share the maps' conversion and fill more of the waves that evaluate
+  // them, where there are points enough for every compute unit's waves
+  const int pt = Q >= BHM_MANY ? 4 : 1;
+  const dim3 g((unsigned)((Q + BS * pt - 1) / (BS * pt)));
+  if (dtype == KSDF_DTYPE_F64) {
+    const double* p = static_cast<const double*>(points);
+    if (pt == 4) hipLaunchKernelGGL((bhm_sign_kernel<double, 4>), g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
+    else hipLaunchKernelGGL((bhm_sign_kernel<double, 1>), g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
+  } else {
+    const float* p = static_cast<const float*>(points);
+    if (pt == 4) hipLaunchKernelGGL((bhm_sign_kernel<float, 4>), g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
+    else hipLaunchKernelGGL((bhm_sign_kernel<float, 1>), g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
+  }
   KSDF_HIP_TRY(hipGetLastError());
   return KSDF_OK;
 }

@@ -88,3 +88,42 @@ def test_bhm_tau_update_and_query_sign():
     torch.cuda.synchronize()
     assert torch.equal(out["mean"], plain["mean"] * sign.float())
     model.close()
+
+
+@pytest.mark.parametrize("dtype,hinges", [(torch.float64, 7), (torch.float32, 7), (torch.float32, 5)])
+def test_bhm_sign_does_not_depend_on_the_call(dtype, hinges):
+    """A point's log-odds have the same bits whether its workgroup meets a few maps (staged in
+    LDS), more than it has room for, or only this point, and whether a thread takes one point or
+    four (from 2^20 points); points on the boxes' faces, far away, infinite or NaN are +1 or in
+    the box that the FP64 quotient's floor names."""
+    _say(f"bhm sign in several calls {dtype} {hinges}")
+    wl, b, q = _setup(hinges)
+    q = q[:9001]
+    key = np.floor((q - np.asarray(b["origin"])) / b["box"])
+    q[:500] = np.asarray(b["origin"]) + key[:500] * b["box"]                 # corners of boxes
+    q[500:506] = [[np.inf, 0, 0], [-np.inf, 1, 1], [np.nan, 0, 0], [1e30, 1, 1], [-3e9, 1, 1], [1, 1, 1e12]]
+    key = np.where(np.isfinite(q), np.floor((q - np.asarray(b["origin"])) / b["box"]), 0)
+    order = np.lexsort(key.T)
+    qt = torch.from_numpy(q[order]).to("cuda", dtype)
+    args = _args(b)
+    sign, lo = ksdf.bhm_sign(qt, *args, logodds=True)                        # neighbours share maps
+    assert bool((sign[torch.isneginf(lo)] == 1).all())
+    x = qt.double().cpu().numpy()
+    k = np.floor((x - np.asarray(b["origin"])) / b["box"])
+    inside = np.all(np.isfinite(x) & (k >= 0) & (k < np.asarray(b["dims"])), axis=1)
+    flat = np.ravel_multi_index(k[inside].astype(np.int64).T, b["dims"])
+    have = np.zeros(len(x), bool)
+    have[inside] = b["box_bhm"][flat] >= 0
+    fin = np.isfinite(x).all(1)
+    assert np.array_equal(~np.isneginf(lo.cpu().numpy())[fin], have[fin])
+    mix = torch.from_numpy(np.random.default_rng(1).permutation(len(q))).cuda()
+    s2, l2 = ksdf.bhm_sign(qt[mix].contiguous(), *args, logodds=True)        # and mostly do not
+    many = qt.repeat(-(-(1 << 20) // len(q)), 1)
+    s3, l3 = ksdf.bhm_sign(many, *args, logodds=True)
+    one = [ksdf.bhm_sign(qt[i:i + 1].contiguous(), *args, logodds=True) for i in range(0, len(q), 600)]
+    bits = lambda t: t.contiguous().view(torch.int64)   # noqa: E731
+    assert torch.equal(s2, sign[mix]) and torch.equal(bits(l2), bits(lo[mix]))
+    n = len(many) // len(q)
+    assert torch.equal(s3, sign.repeat(n)) and torch.equal(bits(l3), bits(lo.repeat(n)))
+    for i, (s, l) in zip(range(0, len(q), 600), one):
+        assert int(s[0]) == int(sign[i]) and torch.equal(bits(l), bits(lo[i:i + 1]))
