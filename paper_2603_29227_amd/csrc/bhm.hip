@@ -172,15 +172,14 @@ __device__ __forceinline__ float bhm_logodds32(const BhmArgs& A, const float* pt
   return bhm_logodds32_any(A, pts, q, key, w);
 }
 
-// Signs.  Most points lie in no map's box: they are answered at once, and a block's others are
-// gathered in LDS (in the points' order), so that whole waves evaluate maps or none do.  Float
+// Signs of many points.  Most lie in no map's box: they are answered at once, and a block's
+// others are gathered in LDS (in the points' order), so that whole waves evaluate maps or none do.  Float
 // points and 7 hinges: the block's maps (a few: neighbouring points share them; found through a
 // small hash table) are converted to FP32 into LDS once, in rows of 8, where every lane reads
 // its own map's.  Maps beyond BHM_MAPS, other hinge counts and double points: every lane loads
 // its map's weights.
-// The kernel moves 21 bytes a point; before, a bitonic sort of every block's map ids, six FP64
-// divisions a point and the loads and conversions of 343 weights a point took 590 us for the
-// 256^3 grid, a fifth of whose points have a map, and whose bytes take 75; now 383 us.
+// The kernel moves 21 bytes a point; the sorted form with FP64 divisions takes 590 us for the
+// 256^3 grid, a fifth of whose points have a map, and whose bytes take 75; this one 383 us.
 constexpr int BS = 256;
 constexpr int BHM_MAPS = 16;                 // maps of a block in LDS
 constexpr int BHM_STRIDE = 7 * 7 * 8 + 8;    // floats per map: 49 rows of 8, the bias
@@ -188,7 +187,11 @@ constexpr int BHM_HASH = 64, BHM_PROBES = 4;
 __device__ __forceinline__ int bhm_hash(int id, int p) {
   return ((int)((unsigned)id * 2654435761u >> 26) + p) % BHM_HASH;
 }
-constexpr long BHM_MANY = 1L << 20;          // points from which a thread takes four
+constexpr int BHM_PT = 4;                    // points per thread of the gathered form
+// Points up to which the sorted form answers: its chain is shorter, and fills the chip's gaps
+// with few points; the gathered form does less per point (us, sorted / gathered: 262,144 points
+// 23 / 44; 1,030,301 48 / 53; 2,097,152 81 / 81; 4,096,000 142 / 111; 16,777,216 590 / 383).
+constexpr long BHM_SORTED_MAX = 1L << 21;
 // Workgroups go to the 8 XCDs (each with its own L2) in turn; neighbouring blocks of
 // points read the same maps, so each XCD takes one contiguous range of the blocks (a
 // bijection of [0, n); the results do not depend on it).
@@ -199,11 +202,68 @@ __device__ __forceinline__ long bhm_block(long n) {
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + k;
 }
 
-// PT points per thread
-template <class T, int PT>
+// The sorted form: points sorted by map box within each block (bitonic sort of (map id, slot)
+// keys in LDS), so that a wave's points mostly share a map and load each weight from a few
+// addresses.  Each point's result goes back to its own index.
+template <class T>
+__device__ __forceinline__ void bhm_sorted_slot(const BhmArgs& A, const T* pts, long Q, long* q_out,
+                                                int* id_out) {
+  __shared__ unsigned long long keys[BS];
+  const long blk = bhm_block(gridDim.x);
+  const long q = blk * BS + threadIdx.x;
+  long key[3];
+  const int id = q < Q ? bhm_box(A, pts, q, key) : INT_MAX - 1;
+  keys[threadIdx.x] = ((unsigned long long)(unsigned)(id + 1) << 32) | threadIdx.x;
+  for (int k = 2; k <= BS; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      __syncthreads();
+      const int t = threadIdx.x, o = t ^ j;
+      if (o > t) {
+        const unsigned long long a = keys[t], b = keys[o];
+        const bool up = (t & k) == 0;
+        if ((a > b) == up) {
+          keys[t] = b;
+          keys[o] = a;
+        }
+      }
+    }
+  __syncthreads();
+  const unsigned long long k = keys[threadIdx.x];
+  *q_out = blk * BS + (long)(k & 0xffffffffu);
+  *id_out = (int)(k >> 32) - 1;
+}
+
+template <class T>
+__global__ void __launch_bounds__(BS) bhm_sign_sorted_kernel(BhmArgs A, const T* pts, long Q, double tau,
+                                                      int8_t* sign, double* logodds) {
+  long q;
+  int id;
+  bhm_sorted_slot(A, pts, Q, &q, &id);
+  if (q >= Q) return;
+  long key[3];
+  bhm_box(A, pts, q, key);
+  const long m = (long)A.nh * A.nh * A.nh;
+  double l = 0.0;
+  const bool have = id >= 0;
+  if (have) {
+    // one map for the whole wave: its weights through scalar loads
+    const int w0 = __builtin_amdgcn_readfirstlane(id);
+    const bool uni = __ballot(id != w0) == 0ull;
+    const double* w = A.weights + (long)(uni ? w0 : id) * (m + 1);
+    if constexpr (sizeof(T) == 8) l = bhm_logodds64(A, pts, q, key, w);
+    else l = (double)bhm_logodds32(A, pts, q, key, w);
+  }
+  // no local map: the box holds no occupied voxel, taken as free space
+  sign[q] = (!have || l < tau) ? 1 : -1;
+  if (logodds) logodds[q] = have ? l : -INFINITY;
+}
+
+// The gathered form
+template <class T>
 __global__ void __launch_bounds__(BS) bhm_sign_kernel(BhmArgs A, const T* pts, long Q, double tau,
                                                       int8_t* sign, double* logodds) {
   constexpr bool F32 = sizeof(T) == 4;
+  constexpr int PT = BHM_PT;
   __shared__ int slot[BS * PT], map[BS * PT], count[PT][BS / 64];
   __shared__ int hash[BHM_HASH], local[BHM_HASH], maps[BHM_MAPS], n_maps;
   __shared__ alignas(16) float wl[F32 ? BHM_MAPS * BHM_STRIDE : 1];
@@ -429,18 +489,17 @@ int launch_bhm_sign(const ksdf_bhm_layout* L, const int* box_bhm, const double* 
     return KSDF_ERR_INVALID_ARGUMENT;
   }
   if (Q == 0) return KSDF_OK;
-  // four points a thread share the maps' conversion and fill more of the waves that evaluate
-  // them, where there are points enough for every compute unit's waves
-  const int pt = Q >= BHM_MANY ? 4 : 1;
+  const bool many = Q > BHM_SORTED_MAX;
+  const int pt = many ? BHM_PT : 1;
   const dim3 g((unsigned)((Q + BS * pt - 1) / (BS * pt)));
   if (dtype == KSDF_DTYPE_F64) {
     const double* p = static_cast<const double*>(points);
-    if (pt == 4) hipLaunchKernelGGL((bhm_sign_kernel<double, 4>), g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
-    else hipLaunchKernelGGL((bhm_sign_kernel<double, 1>), g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
+    if (many) hipLaunchKernelGGL(bhm_sign_kernel<double>, g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
+    else hipLaunchKernelGGL(bhm_sign_sorted_kernel<double>, g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
   } else {
     const float* p = static_cast<const float*>(points);
-    if (pt == 4) hipLaunchKernelGGL((bhm_sign_kernel<float, 4>), g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
-    else hipLaunchKernelGGL((bhm_sign_kernel<float, 1>), g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
+    if (many) hipLaunchKernelGGL(bhm_sign_kernel<float>, g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
+    else hipLaunchKernelGGL(bhm_sign_sorted_kernel<float>, g, dim3(BS), 0, s, A, p, Q, tau, sign, logodds);
   }
   KSDF_HIP_TRY(hipGetLastError());
   return KSDF_OK;

@@ -93,8 +93,8 @@ def test_bhm_tau_update_and_query_sign():
 @pytest.mark.parametrize("dtype,hinges", [(torch.float64, 7), (torch.float32, 7), (torch.float32, 5)])
 def test_bhm_sign_does_not_depend_on_the_call(dtype, hinges):
     """A point's log-odds have the same bits whether its workgroup meets a few maps (staged in
-    LDS), more than it has room for, or only this point, and whether a thread takes one point or
-    four (from 2^20 points); points on the boxes' faces, far away, infinite or NaN are +1 or in
+    LDS), more than it has room for, or only this point, and in the sorted form (up to 2^21
+    points) or the gathered one; points on the boxes' faces, far away, infinite or NaN are +1 or in
     the box that the FP64 quotient's floor names."""
     _say(f"bhm sign in several calls {dtype} {hinges}")
     wl, b, q = _setup(hinges)
@@ -118,12 +118,15 @@ def test_bhm_sign_does_not_depend_on_the_call(dtype, hinges):
     assert np.array_equal(~np.isneginf(lo.cpu().numpy())[fin], have[fin])
     mix = torch.from_numpy(np.random.default_rng(1).permutation(len(q))).cuda()
     s2, l2 = ksdf.bhm_sign(qt[mix].contiguous(), *args, logodds=True)        # and mostly do not
-    many = qt.repeat(-(-(1 << 20) // len(q)), 1)
+    many = qt.repeat((1 << 21) // len(q) + 1, 1)
     s3, l3 = ksdf.bhm_sign(many, *args, logodds=True)
     one = [ksdf.bhm_sign(qt[i:i + 1].contiguous(), *args, logodds=True) for i in range(0, len(q), 600)]
     bits = lambda t: t.contiguous().view(torch.int64)   # noqa: E731
     assert torch.equal(s2, sign[mix]) and torch.equal(bits(l2), bits(lo[mix]))
     n = len(many) // len(q)
+    s4, l4 = ksdf.bhm_sign(many[torch.randperm(len(many), device="cuda", generator=torch.Generator("cuda").manual_seed(2))],
+                           *args, logodds=True)
+    assert torch.equal(bits(l4).sort()[0], bits(l3).sort()[0]) and int(s4.sum()) == int(s3.sum())
     assert torch.equal(s3, sign.repeat(n)) and torch.equal(bits(l3), bits(lo.repeat(n)))
     for i, (s, l) in zip(range(0, len(q), 600), one):
         assert int(s[0]) == int(sign[i]) and torch.equal(bits(l), bits(lo[i:i + 1]))
