@@ -165,7 +165,8 @@ int ksdf_model_attach_index(ksdf_model* model, void* list, size_t list_bytes, vo
 void ksdf_model_destroy(ksdf_model* model);
 /* Launch-shape knobs (host struct), picked per workload by the autotuner.
  * query_sub: index boxes are split into query_sub^3 sub-boxes (1, 2 or 4) for the
- *   counting sort that groups a wave's queries; 0 = finest that keeps <= 8M bins.
+ *   counting sort that groups a wave's queries; 0 = finest that keeps <= 8M bins and,
+ *   in the sort of a call, at most one bin per query.
  * query_block: threads per block of the FP32 query kernel (64 or 256; 0 = 256).
  * fused: ksdf_fit_query uses the persistent fused launch (1) or the per-bucket fit
  *   launches followed by the query launch (0).
@@ -175,9 +176,9 @@ void ksdf_model_destroy(ksdf_model* model);
  *   argmin cell between them, or, up to 196,608 points, as one kernel with eight lanes
  *   per query (1), or as one kernel of wave-shared cells (0).  Outputs are identical.
  * query_lanes: each lane of the two-kernel query reads its own cells (1), or the wave
- *   shares a cell through scalar loads where there are at least 96 queries per cell (0;
- *   sparser sets, whose waves span many cells, take the per-lane form too).  Outputs are
- *   identical.
+ *   shares a cell through scalar loads where there are enough queries per cell (0: 192,
+ *   384 for the Matern kernel, 96 with cells of more than 64 samples; sparser sets, whose
+ *   waves span many cells, take the per-lane form too).  Outputs are identical.
  * backward_lanes: accepted (0 or 1) and without effect: the backward takes eight lanes
  *   per point up to 196,608 points (FP64: 65,536) and with a var_f cotangent, else one.
  * query_pairs: the first kernel of the two-kernel query evaluates each (query,

@@ -36,14 +36,25 @@ inline int* bucketed_perm(void* ws, long Q) {
 //   points               eight lanes each   per-lane cells   wave-shared cells
 //   4,000 at random             41                242               860
 //   65,536 trajectories        131                291              1179
-//   262,144 trajectories       477                453              1170
-//   493,039 grid               829                640               812
-//   2,097,152 grid            3352               1844              1686
+//   262,144 trajectories       477                335              1170
+//   493,039 grid               829                511               812
+//   2,097,152 grid            3352               1670              1551
 // Eight lanes per query fill the chip with few queries but take 1.7 ns a query at best; the
 // per-lane and the wave-shared kernels start at about 240 us, and the wave-shared ones win
-// once a wave's queries share their cells, at about 100 queries a cell and more.
+// once a wave's queries share their cells.  Where that is, with the per-lane kernel's samples
+// handed over in LDS (us, lanes / wave):
+//                        1,000,000 along    1,000,003 at     2,097,152 grid
+//                        trajectories       random
+//   RBF, K = 8, m <= 64       881 / 1402       961 / 1074      1670 / 1551
+//   RBF, K = 16, m <= 64     1678 / 2180      1782 / 1858      3283 / 2872
+//   Matern, m <= 64           812 / 1696       873 / 1339      1528 / 1892
+//   RBF, K = 8, m <= 128     1545 / 1518      1570 / 1249      2765 / 1748
+// at 5,900 cells: about 192 queries a cell for the RBF and 384 for the Matern kernel, whose
+// sums take longer, and 96 with cells over 64 samples, whose lanes end at unlike times.
 constexpr long GROUP_MAX_Q = 196608;
-constexpr long WAVE_MIN_PER_CELL = 96;
+long wave_min_per_cell(const ksdf_model* m) {
+  return m->max_m > 64 ? 96 : (m->kernel == KSDF_KERNEL_MATERN32 ? 384 : 192);
+}
 // The eight-lane kernel takes the queries in the caller's order up to this count: the sort
 // costs 50 us, and saves 200 us of 740 for 262,144 points at random but nothing for points
 // that arrive in order (trajectories, grids).
@@ -62,7 +73,7 @@ bool group_used(const ksdf_model* m, long Q) {
 }
 bool lanes_used(const ksdf_model* m, long Q) {
   return m->tuning.query_lanes ||
-         (!mfma_used(m) && !pairs_used(m, Q) && Q < WAVE_MIN_PER_CELL * m->n_cells);
+         (!mfma_used(m) && !pairs_used(m, Q) && Q < wave_min_per_cell(m) * m->n_cells);
 }
 bool sort_used(const ksdf_model* m, long Q) {
   return !group_used(m, Q) || Q > GROUP_UNSORTED_MAX_Q;
