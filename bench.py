@@ -43,7 +43,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_room_grid.txt")
 KERNEL_SOURCES = {
     "query": ["query_fast.hip", "query_split.h", "query_split64_wave.hip",
               "query_split64_lane.hip", "query_split256_wave.hip", "query_split256_lane.hip",
-              "query_pairs.hip", "query_dev.h", "fit_dev.h", "ff.h", "ksdf_internal.h"],
+              "query_pairs.hip", "query_launch.hip", "query_dev.h", "group_dev.h", "wave_ops.h",
+              "fit_dev.h", "ff.h", "ksdf_internal.h"],
     "fused": ["fused.hip", "query_dev.h", "fit_dev.h", "ff.h", "ksdf_internal.h"],
 }
 ROOM_BOX = (np.zeros(3), np.array([10.0, 8.0, 3.0]))
@@ -176,7 +177,7 @@ def roofline_backward(m_mean, QT, kernel_ms, var_f, fp64_arith=False):
     flops = backward_flops(m_mean, var_f) * QT
     peak = PEAK_FP64_TFLOPS if fp64_arith else PEAK_FP32_TFLOPS
     ach = flops / (kernel_ms * 1e-3) / 1e12
-    return {"kernel": "bwd_wave_kernel<%s, *>" % ("true" if var_f else "false"),
+    return {"kernel": "bwd_group_kernel<float, true>" if var_f else "bwd_lane_kernel",
             "arith": "f64" if fp64_arith else "f32", "kernel_ms": round(kernel_ms, 4),
             "flop_per_launch": round(flops), "achieved": round(ach, 3), "peak": peak,
             "unit": "TFLOP/s", "frac": round(ach / peak, 4)}
@@ -508,7 +509,7 @@ def main():
     fit_roof = None
     if not fused:
         ff = fit_flops(m)
-        fit_roof = {"kernel": "fit32_kernel (all m buckets) + FP64 refits", "kernel_ms": r4(kmed["fit"]),
+        fit_roof = {"kernel": "fit_large_kernel, fit_small_kernel + FP64 refits", "kernel_ms": r4(kmed["fit"]),
                     "flop_per_launch": round(ff),
                     "achieved": round(ff / (kmed["fit"] * 1e-3) / 1e12, 3), "peak": PEAK_FP32_TFLOPS,
                     "frac": round(ff / (kmed["fit"] * 1e-3) / 1e12 / PEAK_FP32_TFLOPS, 5)}

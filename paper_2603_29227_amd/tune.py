@@ -157,7 +157,8 @@ def tune_query(model, queries: torch.Tensor, sign=None, reps: int = 3,
 
 def tune_backward(model, queries: torch.Tensor, sign, cotangents: dict, argmin, reps: int = 3,
                   cache_path: Optional[str] = DEFAULT_CACHE, log=None) -> dict:
-    """Time the backward launch shapes (per-lane or wave-shared cells)."""
+    """Time the backward under the values of its knob (backward_lanes, which no longer changes
+    the launch; kept so that cached tunings stay complete)."""
     c = cotangents
 
     def run():
