@@ -69,7 +69,10 @@ __device__ __forceinline__ bool fit64_cholesky(F&& entry, int m, double* Lp, dou
         ok = false;
         break;
       }
-      const double ljj = sqrt(d), inv = reciprocal(ljj, rsqrt(d));
+      const double ljj = sqrt(d);
+      // an infinite pivot (a sample of infinite variance) divides to 0, which the corrections
+      // would make NaN
+      const double inv = ljj < INFINITY ? reciprocal(ljj, rsqrt(d)) : 0.0;
       double lr[NB], lc[NB];
       static_for<bj, NB>([&](auto I) {
         constexpr int i = I;
@@ -100,7 +103,9 @@ __device__ __forceinline__ bool fit64_cholesky(F&& entry, int m, double* Lp, dou
 __device__ __forceinline__ WVec<double> fit64_solve(const double* Lp, const double* rd, int m,
                                                     const WVec<double>& b) {
   const int lane = threadIdx.x & 63;
-  double q[SLOTS], p[SLOTS], r[SLOTS];   // the rows' pivots and their reciprocals q
+  // the rows' pivots and their reciprocals q; an infinite pivot (q = 0) is taken as 0, from
+  // which quotient gives the 0 of a division by it
+  double q[SLOTS], p[SLOTS], r[SLOTS];
   int row[SLOTS];
   WVec<double> y, x;
 #pragma unroll
@@ -109,6 +114,7 @@ __device__ __forceinline__ WVec<double> fit64_solve(const double* Lp, const doub
     const bool in = t * 64 + lane < m;
     q[t] = in ? rd[row[t]] : 0.0;
     p[t] = Lp[pk(row[t], row[t])];
+    if (!(p[t] < INFINITY)) p[t] = 0.0;
     r[t] = in ? b.s[t] : 0.0;
     y.s[t] = 0.0;
     x.s[t] = 0.0;

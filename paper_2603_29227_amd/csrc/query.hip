@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(64) query_plain_kernel(QueryArgs<T> A) {
     const T c = s * (A.alpha * h - A.alpha * z + T(1));
     const T rz = z > T(0) ? T(1) : T(0);
     put(0, c * c);
-    put(1, sv[j]);
+    put(1, in ? sv[j] : T(0));   // not 0 times an infinite variance
     put(2, rz > T(0) ? d[0] / z : T(0));
     put(3, rz > T(0) ? d[1] / z : T(0));
     put(4, rz > T(0) ? d[2] / z : T(0));
