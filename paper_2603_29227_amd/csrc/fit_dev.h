@@ -163,11 +163,15 @@ __device__ void wave_matvec(const T* Ap, int m, const WVec<T>& x, WVec<T>& y) {
 // cond_2(A) <= (largest row sum) / (smallest sample variance) for A = K + Sigma: the entries
 // are positive (Perron) and K is positive semidefinite.  Where that lies a factor 1.25 below
 // the refit threshold the estimate below, which approaches cond_2 from below but for the
-// rounding of the FP32 solves (about cond 2^-24, 0.06 at the threshold of 1e6), cannot reach the threshold either, and its
-// four products and four solves are left out (a tenth of the fit of 64 samples).
+// rounding of the FP32 solves (about cond 2^-24, 0.06 at cond_2 = 1e6), cannot reach the
+// threshold either, and its four products and four solves are left out (a tenth of the fit of
+// 64 samples).  Only up to 1e6: beyond, the solves' rounding decides (at a threshold of 1e9 and
+// a variance of 1e-7 the estimate sends 339 cells of 4434 to FP64 whose bound lies below).
+constexpr float COND_BOUND_MAX = 1e6f;
 __device__ __forceinline__ float cond_upper_bound(float rowsum, float var) { return rowsum / var; }
 __device__ __forceinline__ bool cond_surely_below(float bound, double thr) {
-  return bound > 0.f && 1.25f * bound <= (float)thr;   // false for variances not above zero
+  // false for variances not above zero
+  return bound > 0.f && 1.25f * bound <= fminf((float)thr, COND_BOUND_MAX);
 }
 
 // 2-norm condition estimate of SPD A: lambda_max by power iteration with Rayleigh

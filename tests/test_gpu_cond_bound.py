@@ -1,0 +1,36 @@
+"""The bound that replaces the condition estimate holds where the FP32 solves are reliable only:
+with a threshold far above 1e6 the estimate is formed, and cells whose FP32 factor is no longer
+of use go on to FP64 although the bound of their condition lies below the threshold."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_29227_amd import ksdf, scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def test_a_high_threshold_is_held_against_the_estimate():
+    print("[gpu-case] condition estimate above 1e6", flush=True)
+    wl = scenes.small_room_workload(n_queries=16, cfg_id=47, uneven=True)
+    wl = dataclasses.replace(wl, m_max=128)
+    cells = ksdf.build_cells(wl.points, wl.origin, wl.h, wl.margin, wl.m_max, 1)
+    pts = torch.from_numpy(wl.points).cuda()
+    noise = 1e-7   # row sums of up to 128: a bound of 1.3e9
+
+    def refitted(threshold):
+        model = ksdf.Model(cells, len(pts), wl.origin, wl.h, ell=wl.ell, noise_var=noise,
+                           cond_threshold=threshold)
+        st = torch.zeros(cells.n, dtype=torch.uint8, device="cuda")
+        model.fit(pts, cell_status=st)
+        model.close()
+        return (st & ksdf.C_FP64).cpu().numpy().astype(bool)
+
+    failed = refitted(1e30)                       # the cells whose FP32 pivots fail
+    at = refitted(10 * 128 / noise)               # beyond every bound (1.25 * 128 / noise)
+    below = refitted(2e6)
+    assert np.all(at >= failed) and np.all(below >= at)
+    print(f"refits: pivots {failed.sum()}, estimate {at.sum()}, threshold 2e6 {below.sum()}", flush=True)
+    assert at.sum() > failed.sum()
