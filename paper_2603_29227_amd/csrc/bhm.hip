@@ -44,7 +44,8 @@ template <class T>
 __device__ __forceinline__ long bhm_flat(const BhmArgs& A, const T x3[3], long key[3]) {
   for (int d = 0; d < 3; ++d) {
     // x / B to the last bit from 1 / B (two corrections by the exact remainder: Markstein
-    // 1990) where it is in range: the division itself takes three times the instructions
+    // 1990) where it is in range: the division itself takes three times the instructions.
+    // (Edges so small that the remainder is not exact have a NaN for 1 / B: make_bhm_args.)
     const double x = (double)x3[d] - A.origin[d];
     double t = x * A.inv_box;
     const double t1 = fma(fma(-t, A.box, x), A.inv_box, t);
@@ -459,7 +460,8 @@ bool make_bhm_args(const ksdf_bhm_layout* L, const int* box_bhm, const double* w
     A->dims[d] = L->dims[d];
   }
   A->box = L->box;
-  A->inv_box = 1.0 / L->box;
+  // the remainder x - t B of a quotient near 1 or more is exact down to 2^-1022 + 53
+  A->inv_box = L->box >= 0x1p-960 ? 1.0 / L->box : (double)NAN;
   A->spacing = L->box / (double)(L->hinges - 1);
   A->nh = L->hinges;
   A->gamma = L->gamma;
