@@ -432,8 +432,9 @@ __device__ __forceinline__ void candidates_shared_box(const FastArgs& A, bool ac
 
 // K nearest occupied cell centres of the candidate-index box list of (qx,qy,qz), ties
 // by id (Sec. IV-B.1): the first n entries of cid, nearest first.  outside: the point
-// lies outside the index lattice (then every cell is scanned).  Every lane of the wave
-// calls it together.
+// lies outside the index lattice (then every cell is scanned).  A point with a NaN
+// coordinate is near no centre (n = 0): no distance of its compares, so none entered.
+// Every lane of the wave calls it together.
 template <int KM>
 __device__ __forceinline__ void query_candidates(const FastArgs& A, bool active, float qx, float qy,
                                                  float qz, int (&cid)[KM], int& n, bool& outside) {
@@ -457,7 +458,7 @@ __device__ __forceinline__ void query_candidates(const FastArgs& A, bool active,
     if (b0 >= 0 && !__ballot(active && bkey != b0)) {
       int len;
       candidates_shared_box<KM>(A, active, qx, qy, qz, b0, ref, cd, cid, len);
-      n = active ? min(A.k, len) : 0;
+      n = active && cid[0] != 0x7fffffff ? min(A.k, len) : 0;
       return;
     }
   }
@@ -485,7 +486,7 @@ __device__ __forceinline__ void query_candidates(const FastArgs& A, bool active,
         if (t0 + u < end) cand_insert<KM>(cd, cid, cand_d2(qx, qy, qz, ce[u]), cc[u]);
       if (sorted && cand_scan_over(A, cand_d2(bc.x, bc.y, bc.z, ce[3]), cd[KM - 1], rho)) break;
     }
-    n = min(A.k, end - beg);
+    n = cid[0] != 0x7fffffff ? min(A.k, end - beg) : 0;
   }
 }
 
