@@ -13,6 +13,7 @@ template <class T>
 struct BwdArgs {
   const T* __restrict__ pts;
   long Q;
+  long first;              // eight lanes per query: the launch's first query
   const int8_t* sign;
   const int* argmin;
   const T* d_mean;
@@ -116,9 +117,9 @@ __device__ __forceinline__ float point_grad_f32(const BwdArgs<float>& A, float s
 }  // namespace
 
 // eight lanes per query (backward_group.hip); perm null: the queries in the caller's order
-void launch_backward_group(const ksdf_model* m, const BwdArgs<float>& A, bool varf, const int* perm,
+void launch_backward_group(const ksdf_model* m, BwdArgs<float> A, bool varf, const int* perm,
                            hipStream_t s);
-void launch_backward_group(const ksdf_model* m, const BwdArgs<double>& A, bool varf,
-                           const int* perm, hipStream_t s);
+void launch_backward_group(const ksdf_model* m, BwdArgs<double> A, bool varf, const int* perm,
+                           hipStream_t s);
 
 }  // namespace ksdf

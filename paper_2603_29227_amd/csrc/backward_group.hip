@@ -65,7 +65,7 @@ template <class T, bool VARF>
 __global__ void __launch_bounds__(64) bwd_group_kernel(BwdArgs<T> A, const int* perm) {
   __shared__ BwdGroupLds<T, 17, VARF> S;
   const int lane = threadIdx.x & 63, g = lane & (GL - 1);
-  const long sq = xcd_block(gridDim.x) * GQ + lane / GL;
+  const long sq = A.first + xcd_block(gridDim.x) * GQ + lane / GL;
   const bool active = sq < A.Q;
   const long q = active ? (perm ? (long)perm[sq] : sq) : 0;
   int c = active ? A.argmin[q] : -1;
@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
   // rows 0..15 compensated sums, 16.. the factors of the plain ones
   __shared__ BwdGroupLds<float, 28, VARF> S;
   const int lane = threadIdx.x & 63, g = lane & (GL - 1);
-  const long sq = xcd_block(gridDim.x) * GQ + lane / GL;
+  const long sq = A.first + xcd_block(gridDim.x) * GQ + lane / GL;
   const bool active = sq < A.Q;
   const long q = active ? (perm ? (long)perm[sq] : sq) : 0;
   int c = active ? A.argmin[q] : -1;
@@ -593,24 +593,30 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
 
 }  // namespace
 
-void launch_backward_group(const ksdf_model* m, const BwdArgs<float>& A, bool varf, const int* perm,
+void launch_backward_group(const ksdf_model* m, BwdArgs<float> A, bool varf, const int* perm,
                            hipStream_t s) {
-  const dim3 grid((unsigned)((A.Q + GQ - 1) / GQ)), block(64);
-  if (m->kernel == KSDF_KERNEL_MATERN32) {
-    if (varf) hipLaunchKernelGGL((bwd_group_ff_kernel<true, true>), grid, block, 0, s, A, perm);
-    else hipLaunchKernelGGL((bwd_group_ff_kernel<true, false>), grid, block, 0, s, A, perm);
-  } else {
-    if (varf) hipLaunchKernelGGL((bwd_group_kernel<float, true>), grid, block, 0, s, A, perm);
-    else hipLaunchKernelGGL((bwd_group_ff_kernel<false, false>), grid, block, 0, s, A, perm);
-  }
+  group_launches(A.Q, [&](long first, unsigned n) {
+    const dim3 grid(n), block(64);
+    A.first = first;
+    if (m->kernel == KSDF_KERNEL_MATERN32) {
+      if (varf) hipLaunchKernelGGL((bwd_group_ff_kernel<true, true>), grid, block, 0, s, A, perm);
+      else hipLaunchKernelGGL((bwd_group_ff_kernel<true, false>), grid, block, 0, s, A, perm);
+    } else {
+      if (varf) hipLaunchKernelGGL((bwd_group_kernel<float, true>), grid, block, 0, s, A, perm);
+      else hipLaunchKernelGGL((bwd_group_ff_kernel<false, false>), grid, block, 0, s, A, perm);
+    }
+  });
 }
 
-void launch_backward_group(const ksdf_model* m, const BwdArgs<double>& A, bool varf,
-                           const int* perm, hipStream_t s) {
+void launch_backward_group(const ksdf_model* m, BwdArgs<double> A, bool varf, const int* perm,
+                           hipStream_t s) {
   (void)m;
-  const dim3 grid((unsigned)((A.Q + GQ - 1) / GQ)), block(64);
-  if (varf) hipLaunchKernelGGL((bwd_group_kernel<double, true>), grid, block, 0, s, A, perm);
-  else hipLaunchKernelGGL((bwd_group_kernel<double, false>), grid, block, 0, s, A, perm);
+  group_launches(A.Q, [&](long first, unsigned n) {
+    const dim3 grid(n), block(64);
+    A.first = first;
+    if (varf) hipLaunchKernelGGL((bwd_group_kernel<double, true>), grid, block, 0, s, A, perm);
+    else hipLaunchKernelGGL((bwd_group_kernel<double, false>), grid, block, 0, s, A, perm);
+  });
 }
 
 }  // namespace ksdf

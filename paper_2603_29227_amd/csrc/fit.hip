@@ -20,10 +20,11 @@ namespace {
 // coordinates: dA_ik/dl = A_ik r_ik^2 / l^3 (RBF) or c^2 r_ik^2 exp(-c r_ik) / l (Matern 3/2).
 // Its own kernel, one thread an entry: inside the fit its rows were 4-byte stores 64 rows
 // apart, and their branches split the adjoint's sum and spilled its terms.  43 us for the
-// room's 5516 cells of 64 samples.
-__global__ void __launch_bounds__(FIT_THREADS) fit_dA_kernel(FitArgs A, FitList l) {
-  if (l.count && (int)blockIdx.x >= *l.count) return;
-  const int c = l.cells[blockIdx.x];
+// room's 5516 cells of 64 samples.  first: the launch's first cell of the list.
+__global__ void __launch_bounds__(FIT_THREADS) fit_dA_kernel(FitArgs A, FitList l, int first) {
+  const int t = first + (int)blockIdx.x;
+  if (l.count && t >= *l.count) return;
+  const int c = l.cells[t];
   const int b = A.offsets[c], m = A.offsets[c + 1] - b;
   __shared__ float4 xh[MAXM], xl[MAXM];
   for (int i = threadIdx.x; i < m; i += FIT_THREADS) {
@@ -63,8 +64,11 @@ void launch_fit32(const FitArgs& A, const FitList (&l)[4], hipStream_t s) {
     launch_fit_small_rbf(A, 16, l[0], s);
   }
   if (!A.adjoint || !A.D32) return;
+  constexpr int MOST = 1 << 23;   // a launch holds fewer than 2^32 threads
   for (const FitList& k : l)
-    if (k.n > 0) hipLaunchKernelGGL(fit_dA_kernel, dim3((unsigned)k.n), dim3(FIT_THREADS), 0, s, A, k);
+    for (int first = 0; first < k.n; first += MOST)
+      hipLaunchKernelGGL(fit_dA_kernel, dim3((unsigned)std::min(k.n - first, MOST)), dim3(FIT_THREADS), 0, s,
+                         A, k, first);
 }
 
 __global__ void set_int_kernel(int* p, int v) { *p = v; }

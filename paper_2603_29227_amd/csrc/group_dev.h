@@ -13,6 +13,16 @@ namespace {
 
 constexpr int GL = 8;          // lanes per query
 constexpr int GQ = 64 / GL;    // queries per wave
+// queries of one launch: a launch holds fewer than 2^32 threads, so larger calls take several
+constexpr long GROUP_LAUNCH_MAX = 1L << 28;
+// f(first query, workgroups) for each launch of Q queries, 64 threads a workgroup
+template <class F>
+inline void group_launches(long Q, F&& f) {
+  for (long first = 0; first < Q; first += GROUP_LAUNCH_MAX) {
+    const long n = Q - first < GROUP_LAUNCH_MAX ? Q - first : GROUP_LAUNCH_MAX;
+    f(first, (unsigned)((n + GQ - 1) / GQ));
+  }
+}
 // elements between the queries' vectors and between the rows of exchanged terms in LDS
 // (padded, so that the eight queries of a wave fall in different banks)
 constexpr int GK_STRIDE = KSDF_MAX_M + 4;

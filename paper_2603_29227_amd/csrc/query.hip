@@ -25,6 +25,7 @@ template <class T>
 struct QueryArgs {
   const T* pts;
   long Q;
+  long first;         // the launch's first query
   const int8_t* sign;
   T* mean;
   T* grad;
@@ -138,7 +139,7 @@ __global__ void __launch_bounds__(64) query_plain_kernel(QueryArgs<T> A) {
   __shared__ QueryGroupLds<T> S;
   constexpr int NC = KM / GL;
   const int lane = threadIdx.x & 63, g = lane & (GL - 1), base = lane - g;
-  const long q = (long)blockIdx.x * GQ + lane / GL;
+  const long q = A.first + (long)blockIdx.x * GQ + lane / GL;
   const bool active = q < A.Q;
   const long qq = active ? q : 0;
   const T qx = A.pts[3 * qq], qy = A.pts[3 * qq + 1], qz = A.pts[3 * qq + 2];
@@ -430,15 +431,17 @@ int launch_query(const ksdf_model* m, const void* points, long Q, const int8_t* 
                  void* grad, void* var, void* var_f, void* grad_var, int* argmin, uint8_t* q_status, void* ws,
                  size_t ws_bytes, hipStream_t s, bool prebucketed) {
   if (Q == 0) return KSDF_OK;
-  const unsigned grid = (unsigned)((Q + GQ - 1) / GQ);
   if (m->precision == KSDF_FP64) {
     QueryArgs<double> A = make_args<double>(m, points, Q, sign, mean, grad, var, var_f, grad_var, argmin, q_status);
     A.ps = m->ps64;
     A.sv = m->sv64;
     A.L = m->L64;
     timer_mark(m, KSDF_TIMER_QUERY, 0, s);
-    if (m->k_fuse <= 8) hipLaunchKernelGGL((query_plain_kernel<double, 8>), dim3(grid), dim3(64), 0, s, A);
-    else hipLaunchKernelGGL((query_plain_kernel<double, 16>), dim3(grid), dim3(64), 0, s, A);
+    group_launches(Q, [&](long first, unsigned grid) {
+      A.first = first;
+      if (m->k_fuse <= 8) hipLaunchKernelGGL((query_plain_kernel<double, 8>), dim3(grid), dim3(64), 0, s, A);
+      else hipLaunchKernelGGL((query_plain_kernel<double, 16>), dim3(grid), dim3(64), 0, s, A);
+    });
     timer_mark(m, KSDF_TIMER_QUERY, 1, s);
   } else {
     return launch_query_fast(m, points, Q, sign, mean, grad, var, var_f, grad_var, argmin, q_status, ws,
