@@ -173,12 +173,15 @@ void ksdf_model_destroy(ksdf_model* model);
  * fit_min_bucket: FP32 cells with m <= this run in the fit kernel sized for it
  *   (16, 32 or 64): larger values merge small cells into fewer launches.
  * query_split: the FP32 query runs as two kernels with the queries regrouped by
- *   argmin cell between them, or, up to 196,608 points, as one kernel with eight lanes
- *   per query (1), or as one kernel of wave-shared cells (0).  Outputs are identical.
+ *   argmin cell between them, or, for smaller sets (up to 57,344 to 196,608 points, by the
+ *   kernel, K, the cells' samples and the points per cell; not with query_pairs or
+ *   query_mfma), as one kernel with eight lanes per query (1), or as one kernel of
+ *   wave-shared cells (0).  Outputs are identical.
  * query_lanes: each lane of the two-kernel query reads its own cells (1), or the wave
  *   shares a cell through scalar loads where there are enough queries per cell (0: 192,
- *   384 for the Matern kernel, 96 with cells of more than 64 samples; sparser sets, whose
- *   waves span many cells, take the per-lane form too).  Outputs are identical.
+ *   384 for the Matern kernel, 96 with cells of more than 64 samples, more in sets of up
+ *   to 196,608 points; sparser sets, whose waves span many cells, take the per-lane form
+ *   too).  Outputs are identical.
  * backward_lanes: accepted (0 or 1) and without effect: the backward takes eight lanes
  *   per point up to 196,608 points (FP64: 65,536) and with a var_f cotangent, else one.
  * query_pairs: the first kernel of the two-kernel query evaluates each (query,

@@ -31,34 +31,61 @@ inline int* bucketed_perm(void* ws, long Q) {
   return reinterpret_cast<int*>(static_cast<char*>(ws) + align256(Q * sizeof(int)));
 }
 
-// Which kernels answer a query of Q points (the outputs are the same bit for bit).  On the
-// room (5.9k cells of 64 samples, K = 8; us):
-//   points               eight lanes each   per-lane cells   wave-shared cells
-//   4,000 at random             41                242               860
-//   65,536 trajectories        131                291              1179
-//   262,144 trajectories       477                335              1170
-//   493,039 grid               829                511               812
-//   2,097,152 grid            3352               1670              1551
-// Eight lanes per query fill the chip with few queries but take 1.7 ns a query at best; the
-// per-lane and the wave-shared kernels start at about 240 us, and the wave-shared ones win
-// once a wave's queries share their cells.  Where that is, with the per-lane kernel's samples
-// handed over in LDS (us, lanes / wave):
-//                        1,000,000 along    1,000,003 at     2,097,152 grid
+// Which kernels answer a query of Q points (the outputs are the same bit for bit).  Eight lanes
+// per query fill the chip with few queries but take a time proportional to K and to the cells'
+// samples (64 samples, K = 8: 1.9 ns a query); the per-lane and the wave-shared kernels start at
+// 150 to 400 us and add 0.5 to 2 ns a query, the wave-shared ones the least once a wave's queries
+// share their cells.  us, eight lanes (the points sorted where the rule below sorts them) / per
+// lane / wave, points at random in the box of the surface (those that arrive in order take
+// eight lanes 140 to 320 us for 65,536):
+//                          points    74 to 80 cells    313 cells        5,400 cells
+//   RBF, m <= 32, K = 8    131,072  137 / 225 / 225  134 / 288 / 299  182 / 202 / 423
+//                          196,608  241 / 272 / 255  249 / 312 / 320  244 / 247 / 418
+//   RBF, m <= 64, K = 8     65,536  158 / 262 / 268  167 / 328 / 386  279 / 253 / 1084
+//                          131,072  285 / 319 / 312  313 / 349 / 384  561 / 302 / 856
+//                          196,608  413 / 386 / 374  420 / 424 / 433  428 / 361 / 736
+//   RBF, m <= 64, K = 16   131,072  406 / 433 / 418  432 / 475 / 517  771 / 397 / 1056
+//                          196,608  610 / 636 / 492  613 / 662 / 595  623 / 685 / 964
+//   RBF, m <= 128, K = 8    65,536  475 / 418 / 450  716 / 499 / 754  963 / 481 / 2986
+//                          131,072  643 / 621 / 569  641 / 632 / 712  682 / 654 / 2037
+//                          196,608  923 / 791 / 702  912 / 815 / 818  965 / 872 / 1918
+//   Matern, m <= 32         131,072  125 / 124 / 140  122 / 135 / 186  175 / 144 / 473
+//                          196,608  216 / 151 / 168  216 / 152 / 202  226 / 164 / 443
+//   Matern, m <= 64          65,536  148 / 134 / 187  164 / 148 / 258  275 / 170 / 1084
+//                          131,072  279 / 176 / 211  319 / 189 / 299  559 / 208 / 894
+//   Matern, m <= 128         49,152  341 / 235 / 381  479 / 263 / 638
+//                          131,072  608 / 389 / 467  606 / 417 / 567
+// and, past 196,608 points, in the room of 5.9k cells:
+//                        1,000,000 along    1,000,003 at     2,097,152 grid   (lanes / wave)
 //                        trajectories       random
 //   RBF, K = 8, m <= 64       881 / 1402       961 / 1074      1670 / 1551
 //   RBF, K = 16, m <= 64     1678 / 2180      1782 / 1858      3283 / 2872
 //   Matern, m <= 64           812 / 1696       873 / 1339      1528 / 1892
 //   RBF, K = 8, m <= 128     1545 / 1518      1570 / 1249      2765 / 1748
-// at 5,900 cells: about 192 queries a cell for the RBF and 384 for the Matern kernel, whose
-// sums take longer, and 96 with cells over 64 samples, whose lanes end at unlike times.
-constexpr long GROUP_MAX_Q = 196608;
+constexpr long GROUP_MOST_Q = 196608;
+// Points per cell from which waves share their cells also in sets of up to GROUP_MOST_Q points
+// (the Matern kernel's per-lane form is the shorter one up to 3,000 where cells end together)
+bool dense(const ksdf_model* m, long Q) {
+  return Q >= (m->kernel == KSDF_KERNEL_MATERN32 && m->max_m <= 64 ? 3072L : 1024L) * m->n_cells;
+}
+// Most points for eight lanes each: about where their time meets that of the others
+long group_max_q(const ksdf_model* m, long Q) {
+  if (m->kernel == KSDF_KERNEL_MATERN32) return m->max_m <= 32 ? 131072 : (m->max_m <= 64 ? 65536 : 57344);
+  if (m->max_m <= 32) return GROUP_MOST_Q;
+  if (m->max_m <= 64) return dense(m, Q) ? 147456 : GROUP_MOST_Q;
+  return dense(m, Q) ? 98304 : 147456;
+}
+// Points per cell from which waves share their cells in larger sets: about 192 for the RBF and
+// 384 for the Matern kernel, whose sums take longer, and 96 with cells over 64 samples, whose
+// lanes end at unlike times
 long wave_min_per_cell(const ksdf_model* m) {
   return m->max_m > 64 ? 96 : (m->kernel == KSDF_KERNEL_MATERN32 ? 384 : 192);
 }
 // The eight-lane kernel takes the queries in the caller's order up to this count: the sort
-// costs 50 us, and saves 200 us of 740 for 262,144 points at random but nothing for points
-// that arrive in order (trajectories, grids).
-constexpr long GROUP_UNSORTED_MAX_Q = 131072;
+// costs 20 to 50 us, and saves what points at random lose by meeting their cells unsorted: 200
+// us of 740 for 262,144 of them with 64 samples a cell, and with 128 samples 361 of 716 for
+// 65,536 and 835 of 1476 for 131,072 (316 and 585 us for points that arrive in order).
+long group_unsorted_max_q(const ksdf_model* m) { return m->max_m > 64 ? 65536 : 131072; }
 
 bool pairs_used(const ksdf_model* m, long Q) {
   return m->tuning.query_split && m->tuning.query_pairs && query_pairs_usable(m, Q);
@@ -69,14 +96,17 @@ bool mfma_used(const ksdf_model* m) {
          m->max_m <= 64;
 }
 bool group_used(const ksdf_model* m, long Q) {
-  return m->tuning.query_split && Q <= GROUP_MAX_Q && !mfma_used(m) && !pairs_used(m, Q);
+  return m->tuning.query_split && Q <= group_max_q(m, Q) && !mfma_used(m) && !pairs_used(m, Q);
 }
 bool lanes_used(const ksdf_model* m, long Q) {
-  return m->tuning.query_lanes ||
-         (!mfma_used(m) && !pairs_used(m, Q) && Q < wave_min_per_cell(m) * m->n_cells);
+  if (m->tuning.query_lanes) return true;
+  if (mfma_used(m) || pairs_used(m, Q)) return false;
+  // (K of 9 to 16 of the RBF: the per-lane form's registers leave too few waves in flight)
+  if (Q <= GROUP_MOST_Q && (m->k_fuse <= 8 || m->kernel == KSDF_KERNEL_MATERN32) && !dense(m, Q)) return true;
+  return Q < wave_min_per_cell(m) * m->n_cells;
 }
 bool sort_used(const ksdf_model* m, long Q) {
-  return !group_used(m, Q) || Q > GROUP_UNSORTED_MAX_Q;
+  return !group_used(m, Q) || Q > group_unsorted_max_q(m);
 }
 // limits of the sorts, checked for every launch so that a model beyond them is refused
 // whatever the query count
