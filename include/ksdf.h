@@ -183,7 +183,8 @@ void ksdf_model_destroy(ksdf_model* model);
  *   to 196,608 points; sparser sets, whose waves span many cells, take the per-lane form
  *   too).  Outputs are identical.
  * backward_lanes: accepted (0 or 1) and without effect: the backward takes eight lanes
- *   per point up to 196,608 points (FP64: 65,536) and with a var_f cotangent, else one.
+ *   per point up to 196,608 points (FP64: 40,960, or 24,576 with cells of up to 16 samples)
+ *   and, but for FP64 models of such cells, with a var_f cotangent, else one.
  * query_pairs: the first kernel of the two-kernel query evaluates each (query,
  *   candidate cell) pair once, with the pairs grouped by cell (1), instead of each
  *   wave walking the union of its lanes' candidates (0).  Every candidate is then

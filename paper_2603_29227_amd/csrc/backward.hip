@@ -29,141 +29,199 @@ namespace {
 
 constexpr int BT = 256;
 
-// One query's VJP on its argmin cell without a var_f cotangent (those run eight lanes per
-// query, backward_group.hip), per-thread loops: FP64 RBF models with many queries.
-template <class T>
-__device__ __forceinline__ void query_vjp(const BwdArgs<T>& A, long q, int c, T out_dx[3],
+// One query's VJP on its argmin cell, per-thread loops: FP64 RBF models with many queries.
+// With VARF (a var_f cotangent is given), v is per-thread storage for k, then L^{-1} k, then
+// beta = A^{-1} k.
+constexpr int VARF_SMALL_M = 16;
+template <bool VARF>
+__device__ __forceinline__ void query_vjp(const BwdArgs<double>& A, long q, int c, double* v, double out_dx[3],
                                           double out_th[2]) {
-  const T lt = A.ell;
-  const T x0 = A.pts[3 * q], x1 = A.pts[3 * q + 1], x2 = A.pts[3 * q + 2];
-  const T s = A.sign ? (T)A.sign[q] : T(1);
-  T gm, gv;
+  const double lt = A.ell;
+  const double x0 = A.pts[3 * q], x1 = A.pts[3 * q + 1], x2 = A.pts[3 * q + 2];
+  const double s = A.sign ? (double)A.sign[q] : 1.0;
+  double gm, gv;
   mean_var_cotangents(A, q, gm, gv);
-  T gg[3] = {T(0), T(0), T(0)};
+  double gg[3] = {0.0, 0.0, 0.0};
   if (A.d_grad)
     for (int d = 0; d < 3; ++d) gg[d] = A.d_grad[3 * q + d];
+  const double gf = VARF && A.d_var_f ? A.d_var_f[q] : 0.0;
   const int b = A.offsets[c], m = A.offsets[c + 1] - b;
-  const T* p = A.ps + 4L * b;
-  const T* sv = A.sv + b;
-  constexpr int XS = sizeof(T) == 4 ? 4 : 2;   // FP32 store: float-float pairs, hi first
-  const T* xi = A.xi + XS * (long)b;
+  const double* p = A.ps + 4L * b;
+  const double* sv = A.sv + b;
+  const double* Lc = A.L + A.loff[c];
+  const double* xi = A.xi + 2L * b;
   const double* cc = A.centre64 + 3L * c;
-  const T l0 = x0 - (T)cc[0], l1 = x1 - (T)cc[1], l2 = x2 - (T)cc[2];
-  const T inv2l2 = T(1) / A.two_l2;
+  const double l0 = x0 - cc[0], l1 = x1 - cc[1], l2 = x2 - cc[2];
+  const double inv2l2 = 1.0 / A.two_l2;
   // scaling reference: the exact nearest sample (any reference gives the same result)
-  T d2 = (T)INFINITY;
+  double d2 = INFINITY;
   for (int i = 0; i < m; ++i) {
-    const T dx = l0 - p[4 * i], dy = l1 - p[4 * i + 1], dz = l2 - p[4 * i + 2];
+    const double dx = l0 - p[4 * i], dy = l1 - p[4 * i + 1], dz = l2 - p[4 * i + 2];
     d2 = fmin(d2, dx * dx + dy * dy + dz * dz);
   }
-  const T zmin = sqrt(d2);
+  const double ginv = exp(-d2 * inv2l2);
+  const double zmin = sqrt(d2);
   // pass A: f', w', Z, softmin moments, k
-  T f = 0, w[3] = {0, 0, 0}, Za = 0, S = 0, M1 = 0, M2 = 0;
+  double f = 0, w[3] = {0, 0, 0}, Za = 0, S = 0, M1 = 0, M2 = 0;
   for (int i = 0; i < m; ++i) {
-    const T dx = l0 - p[4 * i], dy = l1 - p[4 * i + 1], dz = l2 - p[4 * i + 2];
-    const T z2 = dx * dx + dy * dy + dz * dz;
-    const T e = exp(-(z2 - d2) * inv2l2);
-    const T ae = p[4 * i + 3] * e;
+    const double dx = l0 - p[4 * i], dy = l1 - p[4 * i + 1], dz = l2 - p[4 * i + 2];
+    const double z2 = dx * dx + dy * dy + dz * dz;
+    const double e = exp(-(z2 - d2) * inv2l2);
+    const double ae = p[4 * i + 3] * e;
     f += ae;
     w[0] += ae * dx;
     w[1] += ae * dy;
     w[2] += ae * dz;
     Za += ae * z2;
-    const T t = sqrt(z2) - zmin;
-    const T sm = exp(-A.alpha * t);
+    const double t = sqrt(z2) - zmin;
+    const double sm = exp(-A.alpha * t);
     S += sm;
     M1 += sm * t;
     M2 += sm * t * t;
+    if constexpr (VARF) v[i] = e * ginv;
   }
-  const T u2 = f > T(0) ? d2 - A.two_l2 * log(f) : T(-1);
-  const bool mean_live = u2 > T(0);
-  const T u = mean_live ? sqrt(u2) : T(0);
-  const T wn = sqrt(w[0] * w[0] + w[1] * w[1] + w[2] * w[2]);
-  T y[3] = {0, 0, 0};
-  if (wn > T(0)) {
-    const T gw = (gg[0] * w[0] + gg[1] * w[1] + gg[2] * w[2]) / wn;
+  double vv = 0;
+  if constexpr (VARF) {
+    // forward substitution: v <- L^{-1} k
+    for (int i = 0; i < m; ++i) {
+      const double* row = Lc + (long)i * (i + 1) / 2;
+      double t = v[i];
+      for (int j = 0; j < i; ++j) t -= row[j] * v[j];
+      v[i] = t * row[i];
+      vv += v[i] * v[i];
+    }
+    // backward substitution: v <- L^{-T} v = A^{-1} k (row-oriented, last row first)
+    for (int i = m - 1; i >= 0; --i) {
+      const double* row = Lc + (long)i * (i + 1) / 2;
+      v[i] *= row[i];
+      for (int j = 0; j < i; ++j) v[j] -= row[j] * v[i];
+    }
+  }
+  const double u2 = f > 0.0 ? d2 - A.two_l2 * log(f) : -1.0;
+  const bool mean_live = u2 > 0.0;
+  const double u = mean_live ? sqrt(u2) : 0.0;
+  const double wn = sqrt(w[0] * w[0] + w[1] * w[1] + w[2] * w[2]);
+  double y[3] = {0, 0, 0};
+  if (wn > 0.0) {
+    const double gw = (gg[0] * w[0] + gg[1] * w[1] + gg[2] * w[2]) / wn;
     for (int d = 0; d < 3; ++d) y[d] = (gg[d] - gw * w[d] / wn) / wn;
   }
-  const T m1 = M1 / S;
-  const T h = zmin + m1;
-  const T Vz = M2 / S - m1 * m1;
+  const bool varf_live = VARF && (1.0 - vv) > 0.0;
+  const double m1 = M1 / S;
+  const double h = zmin + m1;
+  const double Vz = M2 / S - m1 * m1;
   // pass B: softmin coefficients c_i; V, P, d var / d alpha, sum c^2
-  T V = 0, P = 0, dVa = 0, C2 = 0;
+  double V = 0, P = 0, dVa = 0, C2 = 0;
   for (int i = 0; i < m; ++i) {
-    const T dx = l0 - p[4 * i], dy = l1 - p[4 * i + 1], dz = l2 - p[4 * i + 2];
-    const T z = sqrt(dx * dx + dy * dy + dz * dz);
-    const T si = exp(-A.alpha * (z - zmin)) / S;
-    const T Bi = A.alpha * (h - z) + T(1);
-    const T ci = si * Bi;
+    const double dx = l0 - p[4 * i], dy = l1 - p[4 * i + 1], dz = l2 - p[4 * i + 2];
+    const double z = sqrt(dx * dx + dy * dy + dz * dz);
+    const double si = exp(-A.alpha * (z - zmin)) / S;
+    const double Bi = A.alpha * (h - z) + 1.0;
+    const double ci = si * Bi;
     V += sv[i] * ci * ci;
     P += sv[i] * ci * si;
     C2 += ci * ci;
-    dVa += T(2) * sv[i] * ci * (si * (h - z) * (Bi + T(1)) - A.alpha * si * Vz);
+    dVa += 2.0 * sv[i] * ci * (si * (h - z) * (Bi + 1.0) - A.alpha * si * Vz);
   }
   // pass C: per-sample accumulations
-  T dxv[3] = {0, 0, 0}, Hy[3] = {0, 0, 0}, Wz[3] = {0, 0, 0};
-  T El = 0, Es = 0, Eld[3] = {0, 0, 0}, Esd[3] = {0, 0, 0};
+  double dxv[3] = {0, 0, 0}, Hy[3] = {0, 0, 0}, Wz[3] = {0, 0, 0}, bk[3] = {0, 0, 0};
+  double bkz = 0, bb = 0, El = 0, Es = 0, Eld[3] = {0, 0, 0}, Esd[3] = {0, 0, 0};
   for (int i = 0; i < m; ++i) {
-    const T di[3] = {l0 - p[4 * i], l1 - p[4 * i + 1], l2 - p[4 * i + 2]};
-    const T z2 = di[0] * di[0] + di[1] * di[1] + di[2] * di[2];
-    const T z = sqrt(z2);
-    const T e = exp(-(z2 - d2) * inv2l2);
-    const T ae = p[4 * i + 3] * e;
-    const T si = exp(-A.alpha * (z - zmin)) / S;
-    const T ci = si * (A.alpha * (h - z) + T(1));
-    const T dvdz = T(2) * A.alpha * (-sv[i] * ci * (ci + si) + si * V + ci * P);
-    const T dy = di[0] * y[0] + di[1] * y[1] + di[2] * y[2];
+    const double di[3] = {l0 - p[4 * i], l1 - p[4 * i + 1], l2 - p[4 * i + 2]};
+    const double z2 = di[0] * di[0] + di[1] * di[1] + di[2] * di[2];
+    const double z = sqrt(z2);
+    const double e = exp(-(z2 - d2) * inv2l2);
+    const double ae = p[4 * i + 3] * e;
+    const double si = exp(-A.alpha * (z - zmin)) / S;
+    const double ci = si * (A.alpha * (h - z) + 1.0);
+    const double dvdz = 2.0 * A.alpha * (-sv[i] * ci * (ci + si) + si * V + ci * P);
+    const double dy = di[0] * y[0] + di[1] * y[1] + di[2] * y[2];
+    double kb = 0;
+    if constexpr (VARF) kb = v[i] * e * ginv;
     for (int d = 0; d < 3; ++d) {
-      if (z > T(0)) dxv[d] += dvdz * di[d] / z;
+      if (z > 0.0) dxv[d] += dvdz * di[d] / z;
       Hy[d] += ae * dy * di[d];
       Wz[d] += ae * z2 * di[d];
-      Eld[d] += e * xi[XS * i] * di[d];
-      Esd[d] += e * xi[XS * i + 1] * di[d];
+      if constexpr (VARF) bk[d] += kb * di[d];
+      Eld[d] += e * xi[2 * i] * di[d];
+      Esd[d] += e * xi[2 * i + 1] * di[d];
     }
-    El += e * xi[XS * i];
-    Es += e * xi[XS * i + 1];
+    if constexpr (VARF) {
+      bkz += kb * z2;
+      bb += v[i] * v[i];
+    }
+    El += e * xi[2 * i];
+    Es += e * xi[2 * i + 1];
   }
-  const T l3 = lt * lt * lt;
+  double bDb = 0;
+  if (VARF && A.D && gf != 0.0 && varf_live) {
+    const double* Dc = A.D + A.loff[c];
+    for (int i = 1; i < m; ++i) {
+      const double* row = Dc + (long)i * (i + 1) / 2;
+      double t = 0;
+      for (int j = 0; j < i; ++j) t += row[j] * v[j];
+      bDb += 2.0 * v[i] * t;
+    }
+  }
+  const double l3 = lt * lt * lt;
   // d_points
   for (int d = 0; d < 3; ++d) {
-    T r = s * (f * y[d] - Hy[d] / (lt * lt)) + gv * dxv[d];
+    double r = s * (f * y[d] - Hy[d] / (lt * lt)) + gv * dxv[d];
     if (mean_live) r += s * gm * w[d] / (f * u);
+    if (varf_live) r += gf * 2.0 * bk[d] / (lt * lt);
     out_dx[d] = r;
   }
   // weight cotangent . xi (through the fit)
-  T aXl = s * (y[0] * Eld[0] + y[1] * Eld[1] + y[2] * Eld[2]);
-  T aXs = s * (y[0] * Esd[0] + y[1] * Esd[1] + y[2] * Esd[2]);
+  double aXl = s * (y[0] * Eld[0] + y[1] * Eld[1] + y[2] * Eld[2]);
+  double aXs = s * (y[0] * Esd[0] + y[1] * Esd[1] + y[2] * Esd[2]);
   if (mean_live) {
-    const T cm = -s * gm * lt * lt / (u * f);
+    const double cm = -s * gm * lt * lt / (u * f);
     aXl += cm * El;
     aXs += cm * Es;
   }
-  T dl = 0, ds = 0;
+  double dl = 0, ds = 0;
   if (mean_live) dl += s * gm * (u2 - Za / f) / (lt * u);
   dl += s * (y[0] * Wz[0] + y[1] * Wz[1] + y[2] * Wz[2]) / l3;
-  if (A.alpha_tied) dl += gv * dVa * (-T(2) * A.alpha / lt);
+  if (A.alpha_tied) dl += gv * dVa * (-2.0 * A.alpha / lt);
+  if (varf_live) dl += gf * (-2.0 * bkz / l3 + bDb);
   dl -= aXl;
   if (A.uniform_noise) {
     ds += gv * C2;
+    if (varf_live) ds += gf * bb;
     ds -= aXs;
   }
-  out_th[0] = (double)dl;
-  out_th[1] = (double)ds;
+  out_th[0] = dl;
+  out_th[1] = ds;
 }
 
+// the per-query hyperparameter terms: FP64 models keep doubles; FP32 models keep
+// float pairs (dl, ds), summed afterwards in float-float
 template <class T>
-__global__ void __launch_bounds__(BT) bwd_plain_kernel(BwdArgs<T> A) {
+__device__ __forceinline__ void store_theta(const BwdArgs<double>& A, long q, const double th[2]) {
+  if constexpr (sizeof(T) == 8) {
+    A.part[2 * q] = th[0];
+    A.part[2 * q + 1] = th[1];
+  } else {
+    reinterpret_cast<float2*>(A.part)[q] = make_float2((float)th[0], (float)th[1]);
+  }
+}
+
+// FP64 RBF models with many queries.  VARF: of up to VARF_SMALL_M samples a cell.
+template <bool VARF>
+__global__ void __launch_bounds__(BT) bwd_plain_kernel(BwdArgs<double> A) {
   const long q = (long)blockIdx.x * BT + threadIdx.x;
   if (q >= A.Q) return;
   int c = A.argmin[q];
   if (c >= A.n_cells) c = -1;   // not a cell of this model: no contribution
-  T dx[3] = {T(0), T(0), T(0)};
-  double th[2] = {0.0, 0.0};
+  double dx[3] = {0.0, 0.0, 0.0}, th[2] = {0.0, 0.0};
   if (c < 0 && A.c_mean) {
-    T gm, gv;
+    double gm, gv;
     mean_var_cotangents(A, q, gm, gv);   // the cost alone
   }
-  if (c >= 0) query_vjp<T>(A, q, c, dx, th);
+  if (c >= 0) {
+    double v[VARF ? VARF_SMALL_M : 1];
+    query_vjp<VARF>(A, q, c, v, dx, th);
+  }
   for (int d = 0; d < 3; ++d) A.d_points[3 * q + d] = dx[d];
   store_theta(A, q, th);
 }
@@ -907,15 +965,22 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Eight lanes per query (backward_group.hip) or one thread per query, which needs some
 // hundred thousand of them to fill the chip.  With a var_f cotangent a thread's kernel
-// vector lives in memory, so those always take eight lanes.  Room of 64-sample cells, eight
-// lanes against one thread (us): FP32 64,000 trajectory points 79 / 117, 262,144 260 / 245,
-// 1e6 941 / 755, with var_f 262,144 at random 800 / 9202; Matern 3/2 262,144 287 / 350;
-// FP64 64,000 143 / 145, a 128^3 grid 3293 / 1529, with var_f 65,536 877 / 2135.
-constexpr long GROUP_MAX_Q32 = 196608, GROUP_MAX_Q64 = 65536;
+// vector lives in memory, so those take eight lanes (but see below).  Eight lanes against one
+// thread (us), room of 64-sample cells: FP32 64,000 trajectory points 79 / 117, 262,144 260 /
+// 245, 1e6 941 / 755, with var_f 262,144 at random 800 / 9202; Matern 3/2 262,144 287 / 350.
+// FP64 models:                 points  8 samples   12         64           128
+//   without var_f              32,000    20 / 18   25 / 24    58 / 92     104 / 176
+//                              65,536    30 / 19   39 / 24   100 / 93     181 / 178
+//   with var_f                 65,536    46 / 28   72 / 53   432 / 1454  1805 / 7138
+//                             524,288   321 / 124 516 / 265 3225 / 11808
+// so that with var_f cells of few samples (whose vector stays in the cache) take one thread
+// (32 samples: 152 / 352 and 1109 / 2720).
+constexpr long GROUP_MAX_Q32 = 196608, GROUP_MAX_Q64 = 40960, GROUP_MAX_Q64_SMALL = 24576;
 bool group_used(const ksdf_model* m, long Q, bool varf) {
-  if (m->precision == KSDF_FP64)
-    return m->kernel == KSDF_KERNEL_RBF && (varf || Q <= GROUP_MAX_Q64);
-  return varf || Q <= GROUP_MAX_Q32;
+  if (m->precision != KSDF_FP64) return varf || Q <= GROUP_MAX_Q32;
+  if (m->kernel != KSDF_KERNEL_RBF) return false;
+  const bool small = m->max_m <= VARF_SMALL_M;
+  return (varf && !small) || Q <= (small && !varf ? GROUP_MAX_Q64_SMALL : GROUP_MAX_Q64);
 }
 // Whether the points are taken in argmin-cell order (FP32 models): one thread per query
 // always; eight lanes only with var_f, where the factor is read three times (262,144 points
@@ -1023,7 +1088,8 @@ int launch_backward(const ksdf_model* m, const void* points, long Q, const int8_
       if (varf) hipLaunchKernelGGL(bwd_matern64_kernel<true>, dim3(grid), dim3(BT), 0, s, A);
       else hipLaunchKernelGGL(bwd_matern64_kernel<false>, dim3(grid), dim3(BT), 0, s, A);
     } else if (Q > 0) {
-      hipLaunchKernelGGL(bwd_plain_kernel<double>, dim3(grid), dim3(BT), 0, s, A);
+      if (varf) hipLaunchKernelGGL(bwd_plain_kernel<true>, dim3(grid), dim3(BT), 0, s, A);
+      else hipLaunchKernelGGL(bwd_plain_kernel<false>, dim3(grid), dim3(BT), 0, s, A);
     }
     timer_mark(m, KSDF_TIMER_BACKWARD, 1, s);
   } else {

@@ -131,3 +131,28 @@ def test_hyperparameter_sums_where_one_block_ends(precision):
     eps = 2.0 ** (-40 if precision == "fp32" else -46)
     for n in (1, 255, 256, 257, 4096, 4097):
         assert bool(((sums(0, n) - sums(0, n // 2) - sums(n // 2, n)).abs() <= eps * each).all()), n
+
+
+@pytest.mark.parametrize("m_max", [1, 7, 16])
+def test_fp64_var_f_backward_of_small_cells_by_one_thread(m_max):
+    """FP64 models of up to 16 samples a cell: past 40,960 points one thread answers a point with
+    a var_f cotangent too.  Its sums are the eight lanes' but for the order within the two
+    triangular solves and the fused steps, a few 2^-53 of the parts of a point's gradient."""
+    print(f"[gpu-case] one thread with var_f m<={m_max}", flush=True)
+    wl = _sphere(m_max, n_queries=2003, dtype=np.float64)
+    model, _, dt = _setup(wl, "fp64", var_f=True)
+    q, sg = torch.from_numpy(wl.queries).to("cuda", dt), torch.from_numpy(wl.sign).cuda()
+    g = torch.Generator(device="cuda").manual_seed(1)
+    n, reps = len(q), 40960 // len(q) + 1
+    cot = [torch.randn(*s, generator=g, device="cuda", dtype=dt) for s in ((n,), (n, 3), (n,), (n,))]
+    am = model.query(q, sg)["argmin"]
+    a, ah = model.backward(q, sg, *cot, argmin=am)
+    rep = lambda t: t.repeat(reps, *([1] * (t.dim() - 1)))   # noqa: E731
+    b, bh = model.backward(rep(q), rep(sg), *(rep(c) for c in cot), argmin=rep(am))
+    assert torch.equal(b[:n], b[-n:])
+    big = a.abs().amax(1, keepdim=True)
+    # 2^-53 of the parts, which exceed a gradient by what cancels between them and by the
+    # cells' condition (below 2^18: 16 samples of variance 1e-4 and more)
+    eps = 2.0 ** -53
+    assert bool(((a - b[:n]).abs() <= eps * 2 ** 18 * (big + big.median())).all())
+    assert torch.allclose(ah * reps, bh, rtol=eps * 2 ** 18, atol=0)
