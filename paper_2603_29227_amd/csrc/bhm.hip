@@ -189,10 +189,22 @@ __device__ __forceinline__ int bhm_hash(int id, int p) {
   return ((int)((unsigned)id * 2654435761u >> 26) + p) % BHM_HASH;
 }
 constexpr int BHM_PT = 4;                    // points per thread of the gathered form
-// Points up to which the sorted form answers: its chain is shorter, and fills the chip's gaps
-// with few points; the gathered form does less per point (us, sorted / gathered: 262,144 points
-// 23 / 44; 1,030,301 48 / 53; 2,097,152 81 / 81; 4,096,000 142 / 111; 16,777,216 590 / 383).
-constexpr long BHM_SORTED_MAX = 1L << 21;
+// The sorted form's chain is shorter, and fills the chip's gaps with few points; the gathered
+// form does less per point while its front (map ids, gathers) is a good part of the work, or its
+// maps are staged.  us, sorted / gathered, a grid over a room with boxes of 0.16 m, and points on
+// the surface, all of them in a map:
+//     points         7 hinges, float  3, float   3, double   5, float    5, double     7, double
+//     2,197,000 grid    80 / 85       55 / 45    65 / 56    127 / 158   180 / 184    475 / 467
+//       surface       1254 / 1049    271 / 270  317 / 317  1355 / 1383 1504 / 1538  4508 / 4353
+//     16,777,216 grid  511 / 326     337 / 210  455 / 346   751 / 632  1240 / 1086  2984 / 2651
+//       surface       9430 / 7403   2012 / 1979 2476 / 2450 10610 / 10405 11649 / 11727 37122 / 36590
+//     boxes of 0.5 m  4452 / 3491   1664 / 1665 2001 / 1964  7660 / 7749 8181 / 8491 23024 / 25189
+// (the last row on the surface).  16 hinges: 22.0 / 24.7 ms for the grid of floats, 388 / 516 on
+// the surface.
+inline bool bhm_gathered(long Q, int hinges, bool f32) {
+  if (hinges <= 3 || (f32 && hinges == 7)) return Q > 1L << 21;
+  return hinges <= 6 && Q > 1L << 23;
+}
 // Workgroups go to the 8 XCDs (each with its own L2) in turn; neighbouring blocks of
 // points read the same maps, so each XCD takes one contiguous range of the blocks (a
 // bijection of [0, n); the results do not depend on it).
@@ -491,7 +503,7 @@ int launch_bhm_sign(const ksdf_bhm_layout* L, const int* box_bhm, const double* 
     return KSDF_ERR_INVALID_ARGUMENT;
   }
   if (Q == 0) return KSDF_OK;
-  const bool many = Q > BHM_SORTED_MAX;
+  const bool many = bhm_gathered(Q, L->hinges, dtype == KSDF_DTYPE_F32);
   const int pt = many ? BHM_PT : 1;
   const dim3 g((unsigned)((Q + BS * pt - 1) / (BS * pt)));
   if (dtype == KSDF_DTYPE_F64) {

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2603_29227_amd import ksdf
+from paper_2603_29227_amd import ksdf, scenes
 
 pytestmark = pytest.mark.gpu
 
@@ -33,3 +33,26 @@ def test_box_of_a_point_by_the_quotients_floor(box, copies):
     lo = lo.cpu().numpy().reshape(copies, -1)
     assert np.array_equal(~np.isneginf(lo), np.broadcast_to(have, lo.shape))
     assert bool((sign.cpu().numpy().reshape(copies, -1)[:, ~have] == 1).all())
+
+
+@pytest.mark.parametrize("hinges,dtype,most", [(3, torch.float32, 1 << 21), (3, torch.float64, 1 << 21),
+                                               (7, torch.float32, 1 << 21), (4, torch.float32, 1 << 23),
+                                               (5, torch.float64, 1 << 23), (6, torch.float32, 1 << 23),
+                                               (7, torch.float64, 1 << 23), (8, torch.float32, 1 << 23)])
+def test_the_forms_agree_where_one_ends(hinges, dtype, most):
+    """A point's log-odds have the same bits in a small call and in calls of the most points that
+    the sorted form takes and of one more, for each kind of call that has its own limit."""
+    print(f"[gpu-case] bhm forms {hinges} {dtype} {most}", flush=True)
+    wl = scenes.small_room_workload(n_queries=4099)
+    b = scenes.bhm_weights(wl, hinges=hinges)
+    args = (b["origin"], b["box"], b["dims"], b["hinges"], b["gamma"], torch.from_numpy(b["box_bhm"]).cuda(),
+            torch.from_numpy(b["weights"]).cuda())
+    q = torch.cat([torch.from_numpy(wl.points[:4099]), torch.from_numpy(wl.queries)]).to("cuda", dtype)
+    sign, lo = ksdf.bhm_sign(q, *args, logodds=True)
+    assert not bool(torch.isneginf(lo[:4099]).any()) and bool(torch.isneginf(lo).any())
+    reps = most // len(q) + 1
+    many = q.repeat(reps, 1)
+    for n in (most, most + 1):
+        s, l = ksdf.bhm_sign(many[:n].contiguous(), *args, logodds=True)
+        assert torch.equal(s, sign.repeat(reps)[:n])
+        assert torch.equal(l.view(torch.int64), lo.repeat(reps)[:n].view(torch.int64))
