@@ -5,12 +5,12 @@ edge: 1, 2, 4), query block size (64 or 256 threads), persistent fused fit+query
 launch or per-bucket fits followed by the query launch, the smallest fit m bucket
 (16, 32, 64: cells below it run in the kernel sized for it), the query in one kernel
 or in two with the queries regrouped by argmin cell between them, and whether each
-lane reads its own cells (sparse queries) in the query and in the backward.  The
-outputs do not depend on the choice.
+lane reads its own cells (sparse queries) in the query.  The outputs do not depend on
+the choice.
 
 Three calls are tuned separately, each on the caller's own data (median of a few
 timed runs after a warm-up): ``tune`` the fit + query step, ``tune_query`` a query
-alone, ``tune_backward`` the backward.  Results are cached in a JSON file keyed by
+alone, ``tune_backward`` the backward (which has one launch shape: timed, not searched).  Results are cached in a JSON file keyed by
 device (architecture and compute-unit count), the call and a workload signature
 (cell count, m histogram, query count to a power of two, precision, K), so a later
 process applies them without timing (``apply``).
@@ -157,15 +157,15 @@ def tune_query(model, queries: torch.Tensor, sign=None, reps: int = 3,
 
 def tune_backward(model, queries: torch.Tensor, sign, cotangents: dict, argmin, reps: int = 3,
                   cache_path: Optional[str] = DEFAULT_CACHE, log=None) -> dict:
-    """Time the backward under the values of its knob (backward_lanes, which no longer changes
-    the launch; kept so that cached tunings stay complete)."""
+    """Time the backward's launch and keep its knob (backward_lanes, which does not change the
+    launch) as it is, so that cached tunings stay complete."""
     c = cotangents
 
     def run():
         model.backward(queries, sign, c.get("d_mean"), c.get("d_grad"), c.get("d_var"),
                        c.get("d_var_f"), argmin=argmin)
 
-    best, ms, table = _search(model, ["backward_lanes"], run, reps, log)
+    best, ms, table = _search(model, [], run, reps, log)
     b_t = {"backward_lanes": best["backward_lanes"]}
     _store(cache_path, signature(model, len(queries), "backward"), b_t, ms)
     return {"tuning": b_t, "ms": round(ms, 4), "table": [{"ms": round(t, 4), **c} for t, c in table]}
