@@ -68,9 +68,6 @@ void model_layout(ksdf_model* m, Carver& cv) {
   cv.take(&m->centre64, 3 * n);
   cv.take(&m->box32, 8 * n);
   cv.take(&m->cstatus, n);
-  cv.take(&m->ps64, 4 * nnz);
-  cv.take(&m->sv64, nnz);
-  cv.take(&m->L64, lsize);
   cv.take(&m->bucket_cells, n);
   cv.take(&m->bucket_rank, n);
   cv.take(&m->fused_order, n);
@@ -84,13 +81,17 @@ void model_layout(ksdf_model* m, Carver& cv) {
     if (m->precision == KSDF_FP32) cv.take(&m->D32, lsize + KSDF_PAD_FACTOR);
     else cv.take(&m->D64, lsize);
   }
+  if (m->precision == KSDF_FP64) {
+    cv.take(&m->ps64, 4 * nnz);
+    cv.take(&m->sv64, nnz);
+    cv.take(&m->L64, lsize);
+  }
   if (m->precision == KSDF_FP32) {
     // padded so the wave-uniform chunked loads of the last cell stay in bounds
     cv.take(&m->ps32, 4 * (nnz + KSDF_PAD_SAMPLES));
     cv.take(&m->plo32, 4 * (nnz + KSDF_PAD_SAMPLES));
     cv.take(&m->sv32, nnz + KSDF_PAD_SAMPLES);
     cv.take(&m->L32, lsize + KSDF_PAD_FACTOR);
-    cv.take(&m->cond32, n);
     cv.take(&m->fb_list, n);
     cv.take(&m->fb_count, 1);
     if (m->dense_inv) cv.take(&m->Linv32, 4096 * n);

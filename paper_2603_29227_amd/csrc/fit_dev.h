@@ -35,7 +35,6 @@ struct FitArgs {
   float* sv32;
   float* L32;
   float* box32;
-  float* cond32;
   int* fb_list;
   int* fb_count;
   // FP64 store
@@ -643,7 +642,6 @@ __device__ bool fit32_cell(const FitArgs& A, int c, float* smem) {
   write_cell<float, float>(Lf, xh, sv, a, m, ok && !need64, A.ps32 + 4L * b, A.sv32 + b,
                            A.L32 + A.loff[c], A.box32 + 8L * c, A.plo32 + 4L * b, xl, al);
   if (threadIdx.x == 0) {
-    A.cond32[c] = cond;
     A.cstatus[c] = 0;
     if (A.user_status && !need64) A.user_status[c] = 0;
   }
@@ -690,7 +688,7 @@ inline FitArgs make_fit_args(ksdf_model* m, const void* pts, int dtype, const vo
   A.noise = m->noise_var;
   A.cond_thr = m->cond_thr;
   A.user_status = user_status;
-  A.ps32 = m->ps32; A.plo32 = m->plo32; A.sv32 = m->sv32; A.L32 = m->L32; A.box32 = m->box32; A.cond32 = m->cond32;
+  A.ps32 = m->ps32; A.plo32 = m->plo32; A.sv32 = m->sv32; A.L32 = m->L32; A.box32 = m->box32;
   A.fb_list = m->fb_list; A.fb_count = m->fb_count;
   A.ps64 = m->ps64; A.sv64 = m->sv64; A.L64 = m->L64;
   A.cstatus = m->cstatus;

@@ -557,7 +557,6 @@ __device__ __forceinline__ bool fit32_quad(const FitArgs& A, int c, QuadFitLds& 
     box[3] = apos;
     box[4] = hi3[0]; box[5] = hi3[1]; box[6] = hi3[2];
     box[7] = 0.f;
-    A.cond32[c] = cond;
     A.cstatus[c] = 0;
     if (A.user_status && !need64) A.user_status[c] = 0;
   }

@@ -485,7 +485,6 @@ __device__ __forceinline__ bool fit32_wave(const FitArgs& A, int c, WaveFitLds<M
     box[3] = apos;
     box[4] = hi[0]; box[5] = hi[1]; box[6] = hi[2];
     box[7] = 0.f;
-    A.cond32[c] = cond;
     A.cstatus[c] = 0;
     if (A.user_status && !need64) A.user_status[c] = 0;
   }

@@ -91,11 +91,10 @@ struct ksdf_model {
   float* Linv32 = nullptr;      // [n,64,64] dense L^{-1}, column-major, zero-padded (max m <= 64)
   mutable bool linv_ok = false; // Linv32 holds the inverse of the current L32
   float* box32 = nullptr;       // [n,8] sample AABB lo xyz, A+ (sum of positive a), hi xyz, pad
-  float* cond32 = nullptr;      // [n] condition estimate (FP32 factor)
   int* fb_list = nullptr;       // [n] cells to refit in FP64
   int* fb_count = nullptr;      // [1]
 
-  // FP64 store (KSDF_FP64 models, and FP64 refits of FP32 models)
+  // FP64 store (KSDF_FP64 models; the FP64 refits of FP32 models factor in LDS)
   double* ps64 = nullptr;       // [nnz,4]
   double* sv64 = nullptr;       // [nnz]
   double* L64 = nullptr;        // packed rows of L; diagonal holds 1/L_jj
