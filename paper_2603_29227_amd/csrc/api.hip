@@ -283,17 +283,16 @@ extern "C" int ksdf_model_create(int n_cells, const int* offsets, const int* sam
     for (int c = 0; c < n_cells; ++c)
       for (int d = 0; d < 3; ++d) c32[4 * c + d] = (float)m->h_centre[3 * c + d];
     // cells grouped by m bucket for the FP32 fit kernels
-    const int edges[4] = {16, 32, 64, 128};
+    const int edges[7] = {0, 4, 8, 16, 32, 64, 128};
     std::vector<int> order;
     order.reserve(n_cells);
-    m->bucket_start[0] = 0;
-    for (int bk = 0; bk < 4; ++bk) {
+    for (int bk = 0; bk < 6; ++bk) {
       for (int c = 0; c < n_cells; ++c) {
         const int mc = offsets[c + 1] - offsets[c];
-        const int lo = bk == 0 ? 0 : edges[bk - 1];
-        if (mc > lo && mc <= edges[bk]) order.push_back(c);
+        if (mc > edges[bk] && mc <= edges[bk + 1]) order.push_back(c);
       }
-      m->bucket_start[bk + 1] = (int)order.size();
+      if (bk < 2) m->bucket_small[bk] = (int)order.size();
+      else m->bucket_start[bk - 1] = (int)order.size();
     }
     // fused-launch fit order: largest m first (longest tasks start earliest)
     std::vector<int> byM(order.rbegin(), order.rend());

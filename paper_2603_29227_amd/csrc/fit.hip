@@ -52,17 +52,25 @@ __global__ void __launch_bounds__(FIT_THREADS) fit_dA_kernel(FitArgs A, FitList 
 }
 
 // The FP32 fits of the cells of up to 16, 32, 64 and 128 samples, and their packed dA/dl where
-// the model keeps it
-void launch_fit32(const FitArgs& A, const FitList (&l)[4], hipStream_t s) {
-  if (A.kernel == KSDF_KERNEL_MATERN32) {
-    launch_fit_large_matern(A, l[3], l[2], s);
-    launch_fit_small_matern(A, 32, l[1], s);
-    launch_fit_small_matern(A, 16, l[0], s);
-  } else {
-    launch_fit_large_rbf(A, l[3], l[2], s);
-    launch_fit_small_rbf(A, 32, l[1], s);
-    launch_fit_small_rbf(A, 16, l[0], s);
-  }
+// the model keeps it.  le4, le8: where the first list is known to the host, how many at its
+// start have up to 4 and up to 8 samples.  Those get launches of their own (a fit in a matrix of
+// 16 rows does the work of 16 samples: 5456 cells of one sample, Matern 3/2 with adjoint, took
+// 37 us with loops that ended at the samples and 78 us so) where they are too many for the next
+// launch to take them along: fewer would cost more for the launch than they save.
+constexpr int SMALL_CELLS_MIN = 1024;
+void launch_fit32(const FitArgs& A, const FitList (&l)[4], int le4, int le8, hipStream_t s) {
+  const bool matern = A.kernel == KSDF_KERNEL_MATERN32;
+  const auto large = matern ? launch_fit_large_matern : launch_fit_large_rbf;
+  const auto small = matern ? launch_fit_small_matern : launch_fit_small_rbf;
+  large(A, l[3], l[2], s);
+  small(A, 32, l[1], s);
+  const int n = l[0].n;
+  // [0, a) in matrices of 4 rows, [a, b) of 8, the rest of 16
+  const int a = le4 >= SMALL_CELLS_MIN || le4 == n ? le4 : 0;
+  const int b = le8 - a >= SMALL_CELLS_MIN || le8 == n ? le8 : a;
+  small(A, 16, FitList{l[0].cells + b, l[0].count, n - b}, s);
+  small(A, 8, FitList{l[0].cells + a, nullptr, b - a}, s);
+  small(A, 4, FitList{l[0].cells, nullptr, a}, s);
   if (!A.adjoint || !A.D32) return;
   constexpr int MOST = 1 << 23;   // a launch holds fewer than 2^32 threads
   for (const FitList& k : l)
@@ -316,7 +324,7 @@ int launch_refit(ksdf_model* m, const void* pts, int dtype, const void* svar, fl
     FitList l[4];
     for (int bk = 0; bk < 4; ++bk)
       l[bk] = FitList{blist + (long)bk * budget, bcount + bk, std::min(n[bk], budget)};
-    launch_fit32(A, l, s);
+    launch_fit32(A, l, 0, 0, s);
     A.list = m->fb_list;
     A.list_count = m->fb_count;
     A.emit32 = 1;
@@ -375,7 +383,8 @@ int launch_fit(ksdf_model* m, const void* pts, int dtype, const void* svar, uint
                           {lists + lo32, nullptr, minb < 64 ? bs[2] - lo32 : 0},
                           {lists + lo64, nullptr, bs[3] - lo64},
                           {lists + bs[3], nullptr, bs[4] - bs[3]}};
-    launch_fit32(A, l, s);
+    const bool own = minb < 32;
+    launch_fit32(A, l, own ? m->bucket_small[0] : 0, own ? m->bucket_small[1] : 0, s);
     A.list = m->fb_list;
     A.list_count = m->fb_count;
     A.emit32 = 1;

@@ -658,8 +658,8 @@ struct FitList {
   const int* count;
   int n;
 };
-// FP32 fits (fit_rbf.hip, fit_matern.hip): of up to mb = 16 or 32 samples; of 65 to 128 (q) and
-// of up to 64 (w)
+// FP32 fits (fit_rbf.hip, fit_matern.hip): of up to mb = 4, 8, 16 or 32 samples; of 65 to 128
+// (q) and of up to 64 (w)
 void launch_fit_small_rbf(const FitArgs& A, int mb, const FitList& l, hipStream_t s);
 void launch_fit_small_matern(const FitArgs& A, int mb, const FitList& l, hipStream_t s);
 void launch_fit_large_rbf(const FitArgs& A, const FitList& q, const FitList& w, hipStream_t s);

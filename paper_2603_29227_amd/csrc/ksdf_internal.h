@@ -109,10 +109,12 @@ struct ksdf_model {
   double* xi64 = nullptr;       // [nnz,2] (FP64 models)
   float* D32 = nullptr;         // packed dA/dl (FP32 models)
   double* D64 = nullptr;        // packed dA/dl (FP64 models)
-  int* bucket_cells = nullptr;  // [n] cell ids grouped by m bucket (<=16, <=32, <=64, <=128)
+  int* bucket_cells = nullptr;  // [n] cell ids grouped by m bucket (<=16, <=32, <=64, <=128),
+                                // within the first by m <= 4, <= 8 (bucket_small counts both)
   int* bucket_rank = nullptr;   // [n] position of each cell in bucket_cells
   int* fused_order = nullptr;   // [n] cell ids by m descending (fused launch fit order)
   int bucket_start[5] = {0, 0, 0, 0, 0};
+  int bucket_small[2] = {0, 0};
 
   ksdf::CandidateIndex index;
   ksdf_tuning tuning{0, 256, 1, 16, 1, 0, 0, 0, 0};

@@ -51,3 +51,38 @@ def test_a_fit_has_the_same_bits_in_every_bucket(kernel, noise_var):
     ids, count = model.refit(pts, torch.ones(n, device="cuda"), torch.ones(n, device="cuda"), 0.5, n)
     assert int(count) == n
     assert all(torch.equal(a, b) for a, b in zip(answers(model), want))
+
+
+@pytest.mark.parametrize("kernel", ["rbf", "matern32"])
+@pytest.mark.parametrize("m_max,shares", [(1, None), (4, None), (5, None), (8, None), (12, (0.3, 0.3)),
+                                          (16, (0.3, 0.05)), (16, (0.05, 0.4))])
+def test_cells_of_few_samples(kernel, m_max, shares):
+    """Cells of up to 4 and up to 8 samples are factored in matrices of 4 and 8 rows where they are
+    many (over 1,024) or no others are fewer than 17: the bits are those of the larger matrices,
+    adjoint vectors and dA/dl among them."""
+    print(f"[gpu-case] small cells {kernel} m<={m_max} {shares}", flush=True)
+    wl = scenes.small_room_workload(n_queries=3001, cfg_id=47, uneven=False)
+    cap, lo = None, (0, 0, 0)
+    if shares:
+        lo, dims = (-4, -4, -4), (64, 64, 32)
+        u = np.random.default_rng(3).random(dims)
+        cap = np.where(u < shares[0], 1 + (u * 1000).astype(int) % 4,
+                       np.where(u < sum(shares), 5 + (u * 1000).astype(int) % 4, m_max)).astype(np.uint8)
+    cells = ksdf.build_cells(wl.points, wl.origin, wl.h, wl.margin, m_max, 1, cap, lo)
+    assert cells.m.max() == m_max
+    pts = torch.from_numpy(wl.points).cuda()
+    q, sg = torch.from_numpy(wl.queries).cuda(), torch.from_numpy(wl.sign).cuda()
+    cot = [torch.rand(*s, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+           for s in ((len(q),), (len(q), 3), (len(q),), (len(q),))]
+    model = ksdf.Model(cells, len(pts), wl.origin, wl.h, ell=wl.ell, noise_var=wl.noise_var, kernel=kernel,
+                       adjoint_var_f=True)
+
+    def answers(bucket):
+        model.set_tuning(fit_min_bucket=bucket)
+        model.fit(pts)
+        out = model.query(q, sg, grad_var=True)
+        return [out[k] for k in OUT] + list(model.backward(q, sg, *cot, argmin=out["argmin"]))
+
+    small, large = answers(16), answers(32)
+    assert all(torch.equal(a, b) for a, b in zip(small, large))
+    model.close()
