@@ -663,13 +663,16 @@ __device__ __forceinline__ void vjp_f32(const BwdArgs<float>& A, float x0, float
     const float4 h = P4[b + i], lo = PL[b + i];
     return h.w + lo.w;
   };
+  // Past the cell's last sample: that one again, with terms of 0.  (What follows it is another
+  // cell's or past the last cell not set: 0 times an infinity or NaN there would be NaN here.)
+  const auto at = [m](int i) { return min(i, m - 1); };
   ff d2f{INFINITY, 0.f};
   for (int i0 = 0; i0 < m; i0 += BCH) {
 #pragma unroll
     for (int j = 0; j < BCH; ++j) {
       float di[3];
       ff z2;
-      diff(i0 + j, di, z2);   // the store is padded
+      diff(at(i0 + j), di, z2);
       if (i0 + j < m && (z2.hi < d2f.hi || (z2.hi == d2f.hi && z2.lo < d2f.lo))) d2f = z2;
     }
   }
@@ -684,10 +687,10 @@ __device__ __forceinline__ void vjp_f32(const BwdArgs<float>& A, float x0, float
       const bool ok = i0 + j < m;
       float di[3];
       ff z2f;
-      diff(i0 + j, di, z2f);
+      diff(at(i0 + j), di, z2f);
       const float z2 = z2f.hi + z2f.lo;
       const float e = ok ? kval(z2f, d2f) : 0.f;
-      const float ae = weight(i0 + j) * e;
+      const float ae = weight(at(i0 + j)) * e;
       f.add(ae);
       w[0].add(ae * di[0]);
       w[1].add(ae * di[1]);
@@ -727,15 +730,15 @@ __device__ __forceinline__ void vjp_f32(const BwdArgs<float>& A, float x0, float
       const bool ok = i0 + j < m;
       float di[3];
       ff z2f;
-      diff(i0 + j, di, z2f);
-      const float4 xq = X4[b + i0 + j];
-      const float svj = ok ? SV[b + i0 + j] : 0.f;
+      diff(at(i0 + j), di, z2f);
+      const float4 xq = X4[b + at(i0 + j)];
+      const float svj = ok ? SV[b + at(i0 + j)] : 0.f;
       const float x0j = ok ? xq.x + xq.z : 0.f;
       const float x1j = ok ? xq.y + xq.w : 0.f;
       const float z2 = z2f.hi + z2f.lo;
       const float z = sqrtf(z2);
       const float e = ok ? kval(z2f, d2f) : 0.f;
-      const float ae = weight(i0 + j) * e;
+      const float ae = weight(at(i0 + j)) * e;
       const float si = ok ? __builtin_amdgcn_exp2f(-ca * (z - zmin)) * iS : 0.f;
       const float Bi = al * (h - z) + 1.f;
       const float ci = si * Bi;
