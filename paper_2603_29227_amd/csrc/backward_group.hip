@@ -166,10 +166,11 @@ __global__ void __launch_bounds__(64) bwd_group_kernel(BwdArgs<T> A, const int* 
       const T si = in ? exp(-A.alpha * (z - zmin)) / Ss : T(0);
       const T Bi = A.alpha * (h - z) + T(1);
       const T ci = si * Bi;
-      put(0, sv[j] * ci);
+      const T svj = in ? sv[j] : T(0);   // not 0 times an infinite variance
+      put(0, svj * ci);
       put(1, ci);
       put(2, si);
-      put(3, T(2) * sv[j] * ci);
+      put(3, T(2) * svj * ci);
       put(4, si * (h - z) * (Bi + T(1)) - A.alpha * si * Vz);
       wave_lds_sync();
       group_fma(S.t, lane_entry(lanes8(0, 0, 1, 3, 0, 0, 0, 0)),
@@ -192,7 +193,7 @@ __global__ void __launch_bounds__(64) bwd_group_kernel(BwdArgs<T> A, const int* 
       const T ae = p[4 * j + 3] * e;
       const T si = in ? exp(-A.alpha * (z - zmin)) / Ss : T(0);
       const T ci = si * (A.alpha * (h - z) + T(1));
-      const T dvdz = T(2) * A.alpha * (-sv[j] * ci * (ci + si) + si * V + ci * P);
+      const T dvdz = in ? T(2) * A.alpha * (-sv[j] * ci * (ci + si) + si * V + ci * P) : T(0);
       const T dy = di[0] * y[0] + di[1] * y[1] + di[2] * y[2];
       const T vi = VARF && in ? k[i] : T(0);
       for (int d = 0; d < 3; ++d) {
@@ -466,7 +467,7 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
       sample(ph, pl, in, di, pa, z2, z, t, e, zf);
       const int j = in ? i : 0;
       const float4 xq = X4[b + j];
-      const float svj = A.sv[b + j];
+      const float svj = in ? A.sv[b + j] : 0.f;   // not 0 times an infinite variance
       const float xl = xq.x + xq.z, xs = xq.y + xq.w;
       const float ae = pa * e;
       const float si = in ? __builtin_amdgcn_exp2f(-ca * t) * iS : 0.f;
