@@ -166,8 +166,12 @@ __device__ void wave_matvec(const T* Ap, int m, const WVec<T>& x, WVec<T>& y) {
 // threshold either, and its four products and four solves are left out (a tenth of the fit of
 // 64 samples).  Only up to 1e6: beyond, the solves' rounding decides (at a threshold of 1e9 and
 // a variance of 1e-7 the estimate sends 339 cells of 4434 to FP64 whose bound lies below).
-constexpr float COND_BOUND_MAX = 1e6f;
-__device__ __forceinline__ float cond_upper_bound(float rowsum, float var) { return rowsum / var; }
+// And only for row sums up to 1e18: the estimate's squared norms, up to 128 row sums squared,
+// overflow beyond, which sends the cell to FP64.
+constexpr float COND_BOUND_MAX = 1e6f, COND_BOUND_ROWSUM_MAX = 1e18f;
+__device__ __forceinline__ float cond_upper_bound(float rowsum, float var) {
+  return rowsum <= COND_BOUND_ROWSUM_MAX ? rowsum / var : INFINITY;
+}
 __device__ __forceinline__ bool cond_surely_below(float bound, double thr) {
   // false for variances not above zero
   return bound > 0.f && 1.25f * bound <= fminf((float)thr, COND_BOUND_MAX);
