@@ -1293,7 +1293,7 @@ __device__ __forceinline__ void query_finish_t(const FastArgs& A, const Pass1& p
             // softmin with t_i = alpha (z_i - zref) >= 0
             const float ti = A.alpha * (z - zref);
             const float sm = in ? __builtin_amdgcn_exp2f(-A.alpha_l2e * (z - zref)) : 0.f;
-            const float q = sm * sm * SV[j];
+            const float q = sm * sm * (in ? SV[j] : 0.f);   // not 0 times an infinite variance
             S += sm;
             T1 = fmaf(sm, ti, T1);
             X0 += q;

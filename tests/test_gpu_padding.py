@@ -1,10 +1,12 @@
 """A cell's outputs come from its own samples: what lies behind its last one in memory, another
 cell's samples or past the last cell whatever the memory held before, takes no part."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
 
-from paper_2603_29227_amd import ksdf
+from paper_2603_29227_amd import ksdf, scenes
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +42,43 @@ def test_gradients_do_not_read_past_the_last_cell(m):
         assert bool(torch.isfinite(dx).all()) and bool(torch.isfinite(dh).all()), value
         assert torch.equal(dx.view(reps, n, 3)[0], few) and torch.equal(dx.view(reps, n, 3)[-1], few)
         model.close()
+
+
+@pytest.mark.parametrize("kernel", ["rbf", "matern32"])
+@pytest.mark.parametrize("m_max", [7, 13, 61, 127])
+@pytest.mark.parametrize("form", [None, dict(query_split=0), dict(query_split=1, query_lanes=0),
+                                  dict(query_split=1, query_lanes=1)])
+def test_an_infinite_variance_stays_in_its_cell(form, m_max, kernel):
+    """A sample of infinite variance has no part in another cell's softmin variance, in each form
+    of the query (None: eight lanes a point)."""
+    print(f"[gpu-case] infinite variance {form} m<={m_max} {kernel}", flush=True)
+    wl = dataclasses.replace(scenes.sphere_workload(n_samples=9000, n_queries=4001), m_max=m_max)
+    cells = ksdf.build_cells(wl.points, wl.origin, wl.h, wl.margin, m_max, 1)
+    n = len(wl.points)
+    # the first sample of every third cell, the last one of every fifth
+    at = np.full(n, False)
+    for c in range(cells.n):
+        s = cells.samples[cells.offsets[c]:cells.offsets[c + 1]]
+        at[s[0]] |= c % 3 == 0
+        at[s[-1]] |= c % 5 == 0
+    holds = np.logical_or.reduceat(at[cells.samples], cells.offsets[:-1])
+    assert 0 < holds.sum() < cells.n
+    gone = torch.from_numpy(at).cuda()
+    pts, q = (torch.from_numpy(x).to("cuda", torch.float32) for x in (wl.points, wl.queries))
+    if form and form["query_split"]:
+        q = q.repeat(49, 1)   # 196,049 points
+    model = ksdf.Model(cells, n, wl.origin, wl.h, ell=wl.ell, noise_var=wl.noise_var, kernel=kernel)
+    out = []
+    for big in (float("inf"), 1e30):
+        model.fit(pts, torch.where(gone, big, wl.noise_var).to(torch.float32))
+        if form:
+            model.set_tuning(**form)
+        out.append({k: v.clone() for k, v in model.query(q, grad_var=True).items()})
+    a, b = out
+    has = a["argmin"] >= 0
+    assert torch.equal(a["argmin"], b["argmin"]) and int(has.sum()) > 1000
+    there = torch.from_numpy(holds).cuda()[a["argmin"].clamp_min(0).long()] & has
+    assert int(there.sum()) > 100 and int((has & ~there).sum()) > 100
+    for k in ("var", "grad_var"):
+        assert torch.equal(a[k][has & ~there], b[k][has & ~there]), k
+    model.close()
