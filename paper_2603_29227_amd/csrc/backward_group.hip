@@ -453,8 +453,11 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
     const float h = zmin + m1;
     const float Vz = M2 * iS - m1 * m1;
     // pass B: Hy (3), Wz (3), El, Es | Eld (3), Esd (3) compensated; plain: V, P, C2, dVa
-    // and the point derivative's parts.  d var / d z_j = 2 alpha (-sigma_j^2 c_j (c_j + s_j)
-    // + s_j V + c_j P) needs V and P of the same pass, so its parts stay apart (Q1, Q2, Q3).
+    // and (RBF) the point derivative's parts.  d var / d z_j = 2 alpha (-sigma_j^2 c_j (c_j +
+    // s_j) + s_j V + c_j P) needs V and P of the same pass, so its parts stay apart (Q1, Q2, Q3)
+    // for the RBF kernel; for the Matern kernel they are added per sample in a pass of their own,
+    // which keeps the digits that cancel (a variance's gradient alone over the uneven room's cells
+    // of up to 128 samples: 7.4e-7 off FP64, 9.5e-7 with the parts apart).
     CAcc cb0, cb1;
     float a0 = 0.f, a1 = 0.f;
     put(14, 0.f);
@@ -482,7 +485,7 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
         put(3 + d, MAT ? ae * z * di[d] : ae * z2 * di[d]);
         put(8 + d, e * xl * di[d]);
         put(11 + d, e * xs * di[d]);
-        put(24 + d, di[d]);
+        if constexpr (!MAT) put(24 + d, di[d]);
       }
       put(6, kp * xl);
       put(7, kp * xs);
@@ -491,17 +494,25 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
       put(18, si);
       put(19, 2.f * svj * ci);
       put(20, si * (h - z) * (Bi + 1.f) - al * si * Vz);
-      put(21, var_part1_f32(svj, ci, si, rz));
-      put(22, si * rz);
-      put(23, ci * rz);
+      if constexpr (!MAT) {
+        put(21, var_part1_f32(svj, ci, si, rz));
+        put(22, si * rz);
+        put(23, ci * rz);
+      }
       wave_lds_sync();
       group_cadd(S.t, g, cb0);
       group_cadd(S.t, 8 + g, cb1);
-      // V, P, C2, dVa, Q1 (3), Q2 | Q2 (2), Q3 (3)
-      group_fma(S.t, lane_entry(lanes8(16, 16, 17, 19, 21, 21, 21, 22)),
-                lane_entry(lanes8(17, 18, 17, 20, 24, 25, 26, 24)), a0);
-      group_fma(S.t, lane_entry(lanes8(22, 22, 23, 23, 23, 27, 27, 27)),
-                lane_entry(lanes8(25, 26, 24, 25, 26, 27, 27, 27)), a1);
+      if constexpr (MAT) {
+        // V, P, C2, dVa
+        group_fma(S.t, lane_entry(lanes8(16, 16, 17, 19, 27, 27, 27, 27)),
+                  lane_entry(lanes8(17, 18, 17, 20, 27, 27, 27, 27)), a0);
+      } else {
+        // V, P, C2, dVa, Q1 (3), Q2 | Q2 (2), Q3 (3)
+        group_fma(S.t, lane_entry(lanes8(16, 16, 17, 19, 21, 21, 21, 22)),
+                  lane_entry(lanes8(17, 18, 17, 20, 24, 25, 26, 24)), a0);
+        group_fma(S.t, lane_entry(lanes8(22, 22, 23, 23, 23, 27, 27, 27)),
+                  lane_entry(lanes8(25, 26, 24, 25, 26, 27, 27, 27)), a1);
+      }
       wave_lds_sync();
     });
     const float s0 = cb0.val(), s1 = cb1.val();
@@ -515,6 +526,33 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
     const float Q1[3] = {group_lane<4>(a0), group_lane<5>(a0), group_lane<6>(a0)};
     const float Q2[3] = {group_lane<7>(a0), group_lane<0>(a1), group_lane<1>(a1)};
     const float Q3[3] = {group_lane<2>(a1), group_lane<3>(a1), group_lane<4>(a1)};
+    // d var / dx; without a variance cotangent only where it is not finite (0 times it is NaN)
+    float dxv[3] = {0.f, 0.f, 0.f};
+    if constexpr (MAT) {
+      if (gv != 0.f || !(V < INFINITY)) {
+        acc = 0.f;
+        each([&](int i, float4 ph, float4 pl) {
+          const bool in = i < m;
+          float di[3], pa, z2, z, t, e;
+          ff zf;
+          sample(ph, pl, in, di, pa, z2, z, t, e, zf);
+          const float svj = in ? A.sv[b + i] : 0.f;
+          const float si = in ? __builtin_amdgcn_exp2f(-ca * t) * iS : 0.f;
+          const float ci = si * (al * (h - z) + 1.f);
+          const float dvdz = in ? 2.f * al * (-svj * ci * (ci + si) + si * V + ci * Pp) : 0.f;
+#pragma unroll
+          for (int d = 0; d < 3; ++d) put(d, dvdz * di[d]);
+          put(3, z > 0.f ? 1.f / z : 0.f);
+          wave_lds_sync();
+          group_fma(S.t, lane_entry(lanes8(0, 1, 2, 27, 27, 27, 27, 27)),
+                    lane_entry(lanes8(3, 3, 3, 27, 27, 27, 27, 27)), acc);
+          wave_lds_sync();
+        });
+        dxv[0] = group_lane<0>(acc);
+        dxv[1] = group_lane<1>(acc);
+        dxv[2] = group_lane<2>(acc);
+      }
+    }
     // the GP variance's sums: bk (3), bkz, bb
     float bk[3] = {0.f, 0.f, 0.f}, bkz = 0.f, bb = 0.f, bDb = 0.f;
     if constexpr (VARF) {
@@ -546,8 +584,7 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
     const float l3 = lt * lt * lt;
     for (int d = 0; d < 3; ++d) {
       if constexpr (MAT) {
-        const float dxv = 2.f * al * (Q1[d] + V * Q2[d] + Pp * Q3[d]);
-        float r = s * (fev * y[d] - mc * Hy[d]) + gv * dxv;
+        float r = s * (fev * y[d] - mc * Hy[d]) + gv * dxv[d];
         if (mean_live) r += s * gm * mc * wv[d] / fv;
         if (varf_live) r += gf * 2.f * mc * mc * bk[d];
         out_dx[d] = r;
