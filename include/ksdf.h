@@ -166,7 +166,8 @@ void ksdf_model_destroy(ksdf_model* model);
 /* Launch-shape knobs (host struct), picked per workload by the autotuner.
  * query_sub: index boxes are split into query_sub^3 sub-boxes (1, 2 or 4) for the
  *   counting sort that groups a wave's queries; 0 = finest that keeps <= 8M bins and,
- *   in the sort of a call, at most one bin per query.
+ *   in the sort of a call, at most one bin per query, but never coarser than one bin
+ *   per index box.
  * query_block: threads per block of the FP32 query kernel (64 or 256; 0 = 256).
  * fused: ksdf_fit_query uses the persistent fused launch (1) or the per-bucket fit
  *   launches followed by the query launch (0).
@@ -285,7 +286,9 @@ int ksdf_query(const ksdf_model* model, const void* points, long Q, const int8_t
  * step can run while the cells are still being fitted (Sec. IV-B: the K nearest GPs
  * of a point depend on the cell lattice only, not on the fit).
  * ksdf_query_bucket sorts the Q points by candidate-index box and sub-box into
- * `workspace` (the counting sort that opens every FP32 query); it reads the points and
+ * `workspace` (the counting sort that opens an FP32 query; sets that take eight lanes per
+ * point, see query_split, are sorted above 131,072 points only, 65,536 with cells of more
+ * than 64 samples, and for smaller ones the call does nothing); it reads the points and
  * the model's candidate index, not the fitted cells, and may therefore run on another
  * stream beside ksdf_fit_cells.  ksdf_query_bucketed then runs the rest of ksdf_query
  * on that workspace, with the same arguments, outputs and errors as ksdf_query, and

@@ -181,6 +181,12 @@ __device__ __forceinline__ float bhm_logodds32(const BhmArgs& A, const float* pt
 // its map's weights.
 // The kernel moves 21 bytes a point; the sorted form with FP64 divisions takes 590 us for the
 // 256^3 grid, a fifth of whose points have a map, and whose bytes take 75; this one 383 us.
+// BHM_MAPS: points on the surface meet up to 16 maps a block, a grid few, and the weights' LDS
+// (1.6 KB a map) takes waves from the CU.  us for 4, 8, 12, 16, 24, 32 maps, 16,777,216 points:
+//   boxes of 0.16 m   grid     351    322   315   325   332   447
+//                     surface 10302  9947  8716  7413  7373  7471
+//   boxes of 0.5 m    grid     526    338   343   357   417   566
+//                     surface 6267   5606  4158  3483  3498  3727
 constexpr int BS = 256;
 constexpr int BHM_MAPS = 16;                 // maps of a block in LDS
 constexpr int BHM_STRIDE = 7 * 7 * 8 + 8;    // floats per map: 49 rows of 8, the bias

@@ -20,8 +20,10 @@
 // is the leading block of an MB x MB factorisation, and the unrolled loops run over all MB
 // columns without a branch: the zeros they add change no bit, and a test of each column
 // against m cost more than the columns it left out (64 branches per loop, behind which no
-// load was moved ahead, and spilled registers): a cell of 63 samples took 172 us with the
-// tests and takes 98, and the room's 5516 cells 744 and 410 us.
+// load was moved ahead, and more spilled registers): a cell of 63 samples took 172 us with the
+// tests and takes 98, and the room's 5516 cells 744 and 410 us.  The bodies of up to 32 rows spill
+// nothing to memory; the kernel of this body's 64 rows and the four-wave fit (fit_large_kernel)
+// spills 53 VGPRs, 116 bytes of scratch a lane, and 863 SGPRs (into VGPR lanes).
 #pragma once
 
 #include <type_traits>
