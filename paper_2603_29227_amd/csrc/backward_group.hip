@@ -463,14 +463,18 @@ __global__ void __launch_bounds__(64) bwd_group_ff_kernel(BwdArgs<float> A, cons
     put(14, 0.f);
     put(15, 0.f);
     put(27, 0.f);
+    float svn = A.sv[b + min(g, m - 1)];   // the next sample's variance and adjoint vectors,
+    float4 xqn = X4[b + min(g, m - 1)];    // on their way while this one's are used
     each([&](int i, float4 ph, float4 pl) {
       const bool in = i < m;
+      const float svc = svn;
+      const float4 xq = xqn;
+      svn = A.sv[b + min(i + GL, m - 1)];
+      xqn = X4[b + min(i + GL, m - 1)];
       float di[3], pa, z2, z, t, e;
       ff zf;
       sample(ph, pl, in, di, pa, z2, z, t, e, zf);
-      const int j = in ? i : 0;
-      const float4 xq = X4[b + j];
-      const float svj = in ? A.sv[b + j] : 0.f;   // not 0 times an infinite variance
+      const float svj = in ? svc : 0.f;   // not 0 times an infinite variance
       const float xl = xq.x + xq.z, xs = xq.y + xq.w;
       const float ae = pa * e;
       const float si = in ? __builtin_amdgcn_exp2f(-ca * t) * iS : 0.f;
