@@ -970,7 +970,8 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 // hundred thousand of them to fill the chip.  With a var_f cotangent a thread's kernel
 // vector lives in memory, so those take eight lanes (but see below).  Eight lanes against one
 // thread (us), room of 64-sample cells: FP32 64,000 trajectory points 79 / 117, 262,144 260 /
-// 245, 1e6 941 / 755, with var_f 262,144 at random 800 / 9202; Matern 3/2 262,144 287 / 350.
+// 245, 1e6 941 / 755, with var_f 262,144 at random 800 / 9202; Matern 3/2 196,608
+// 171 / 242, with a variance cotangent 227 / 244.
 // FP64 models:                 points  8 samples   12         64           128
 //   without var_f              32,000    20 / 18   25 / 24    58 / 92     104 / 176
 //                              65,536    30 / 19   39 / 24   100 / 93     181 / 178
